@@ -5,15 +5,16 @@
 // The caller's HIP source defines
 //   __device__ double NAME(const double *x, int d, const double *params);
 // it is compiled at run time for gfx950 with hipRTC (packed FP32 instructions
-// off, as for the library) together with a batched evaluation kernel, one
-// thread per point.  Derivatives come from batches of perturbed points built
-// by the library's own kernels: per base point x the rows
+// off, as for the library) together with the batched evaluation kernels, one
+// thread per point.  Derivatives come from batches of perturbed points: per
+// base point x the rows
 //   0             x
 //   1 + 2i, 2+2i  x + eps e_i, x - eps e_i                (i < d)
 //   1 + 2d, 2+2d  x + eps v, x - eps v, v = (1..1)/sqrt(d)  (rotation probe)
 //   3 + 2d + 4t   x +- eps e_i +- eps e_j, t-th pair i < j  (full Hessian only)
-// are evaluated in one launch, and a combine kernel forms the central
-// differences: g_i = (f+ - f-)/(2 eps), H_ii = (f+ - 2 f0 + f-)/eps^2,
+// are evaluated in one launch (each row formed in LDS where the function reads
+// it, or in memory when it is too long for that), and a combine kernel forms
+// the central differences: g_i = (f+ - f-)/(2 eps), H_ii = (f+ - 2 f0 + f-)/eps^2,
 // H_ij = (f++ - f+- - f-+ + f--)/(4 eps^2), and the probe
 // b = (v^T H v - mean H_ii)/(d - 1).
 #include <hip/hiprtc.h>
@@ -31,8 +32,9 @@
 
 struct sb_user_fn {
   hipModule_t mod = nullptr;
-  hipFunction_t eval = nullptr;
+  hipFunction_t eval = nullptr, staged = nullptr;
   int device = -1;
+  int lds_static = 0;  // LDS the user's source declares itself
 };
 
 namespace sb {
@@ -461,6 +463,74 @@ static bool valid_name(const char *name) {
   return true;
 }
 
+// The staged evaluation kernel, completed with the user function's call.  One
+// wave per workgroup, npt <= 64 points, a point per lane.  The function reads
+// its point at one coordinate after the other: from rows in memory the lanes
+// of a wave touch 64 cache lines a coordinate and the L2 sets the pace (d = 64,
+// 4096 points x 131 rows: 27.8 ms), so the rows are brought into LDS first,
+// coalesced, and read from there.  Finite-difference rows (R > 0) are formed in
+// LDS from the base rows with the additions of fd_points_kernel, which the
+// memory of all perturbed points would otherwise be written and read for.
+// d = 64, 4096 points: 30.7 -> 1.7 ms a call.  Bound now by latency: four waves
+// of 64 rows fill a CU's LDS, so one wave per SIMD waits for its own scalar
+// loads of params and its chain of dependent FP64 additions.
+static const char kStagedHead[] = R"hip(
+extern "C" __global__ __launch_bounds__(64) void sb_user_staged_kernel(
+    long long N, int d, int ds, int npt, long long R, const double *X, double eps,
+    const double *params, double *l) {
+#pragma clang fp contract(off)
+  extern __shared__ __attribute__((aligned(16))) double sb_user_rows[];
+  const int lane = threadIdx.x;
+  const long long e0 = (long long)blockIdx.x * npt;
+  const int n = N - e0 < npt ? (int)(N - e0) : npt;
+  const long long b0 = R > 0 ? e0 / R : e0, r0 = R > 0 ? e0 - b0 * R : 0;
+  if (R > 0) {
+    // consecutive points share their base row: one load per base and column
+    for (int j = lane; j < d; j += 64) {
+      const double *x = X + b0 * d + j;
+      double v = *x;
+      long long r = r0;
+      for (int p = 0; p < n; ++p) {
+        if (r == R) {
+          r = 0;
+          x += d;
+          v = *x;
+        }
+        ++r;
+        sb_user_rows[p * ds + j] = v;
+      }
+    }
+  } else {
+    const double *x = X + b0 * d;
+#pragma unroll 4
+    for (int q = lane; q < n * d; q += 64) sb_user_rows[(q / d) * ds + q % d] = x[q];
+  }
+  __syncthreads();
+  if (lane >= n) return;
+  double *x = sb_user_rows + lane * ds;
+  if (R > 0) {
+    const long long r = (r0 + lane) % R;
+    if (r > 0 && r <= 2ll * d) {
+      const int i = (int)((r - 1) / 2);
+      x[i] = ((r - 1) % 2 == 0) ? x[i] + eps : x[i] - eps;
+    } else if (r > 2ll * d && r <= 2ll * d + 2) {
+      const double step = eps * (1.0 / sqrt((double)d));
+      for (int j = 0; j < d; ++j) x[j] = (r == 2ll * d + 1) ? x[j] + step : x[j] - step;
+    } else if (r > 0) {
+      long long t = (r - 3 - 2ll * d) / 4;
+      const int sgn = (int)((r - 3 - 2ll * d) % 4);  // ++, +-, -+, --
+      int i = 0;
+      while (t >= d - 1 - i) {
+        t -= d - 1 - i;
+        ++i;
+      }
+      const int j = i + 1 + (int)t;
+      x[i] = (sgn < 2) ? x[i] + eps : x[i] - eps;
+      x[j] = (sgn % 2 == 0) ? x[j] + eps : x[j] - eps;
+    }
+  }
+  l[e0 + lane] = )hip";
+
 extern "C" {
 
 int32_t sb_user_compile(const char *source, const char *name, sb_user_fn **out) {
@@ -474,6 +544,9 @@ int32_t sb_user_compile(const char *source, const char *name, sb_user_fn **out) 
           "  if (b < B) l[b] = ";
   code += name;
   code += "(X + b * ldx, d, params);\n}\n";
+  code += kStagedHead;
+  code += name;
+  code += "(x, d, params);\n}\n";
   hiprtcProgram prog;
   if (hiprtcCreateProgram(&prog, code.c_str(), "sb_user.hip", 0, nullptr, nullptr) !=
       HIPRTC_SUCCESS)
@@ -497,7 +570,10 @@ int32_t sb_user_compile(const char *source, const char *name, sb_user_fn **out) 
   sb_user_fn *fn = new sb_user_fn;
   if (hipGetDevice(&fn->device) != hipSuccess || hipModuleLoadData(&fn->mod, obj.data()) !=
                                                        hipSuccess ||
-      hipModuleGetFunction(&fn->eval, fn->mod, "sb_user_eval_kernel") != hipSuccess) {
+      hipModuleGetFunction(&fn->eval, fn->mod, "sb_user_eval_kernel") != hipSuccess ||
+      hipModuleGetFunction(&fn->staged, fn->mod, "sb_user_staged_kernel") != hipSuccess ||
+      hipFuncGetAttribute(&fn->lds_static, HIP_FUNC_ATTRIBUTE_SHARED_SIZE_BYTES, fn->staged) !=
+          hipSuccess) {
     if (fn->mod) hipModuleUnload(fn->mod);
     delete fn;
     return fail(SB_E_DEVICE, "loading the compiled user likelihood failed");
@@ -512,11 +588,52 @@ void sb_user_release(sb_user_fn *fn) {
   delete fn;
 }
 
-static int user_eval(const sb_user_fn *fn, int64_t B, int d, const double *X, int64_t ldx,
-                     const double *params, double *l, hipStream_t s) {
+// Points per workgroup of the staged kernel and the LDS row stride: 64 rows, or
+// as many as kStageBytes hold.  Rows keep the alignment they have in memory (16
+// bytes for even d) at a stride whose 16-byte pieces are odd in number (odd
+// for odd d), so that a column of rows spreads over the banks.  0: the row is
+// too long (fewer than four would fit: below that the direct kernel, all its
+// lanes on rows in memory, is as fast) or the source's own LDS leaves no room.
+constexpr int kStageBytes = 64 * 1024;
+static int stage_points(const sb_user_fn *fn, int d, int *stride) {
+  const int64_t ds = d % 2 ? d : (d % 4 == 2 ? d : (int64_t)d + 2);
+  *stride = (int)ds;
+  int n = 64;
+  while (n >= 4 && n * ds * 8 + fn->lds_static > kStageBytes) n >>= 1;
+  return n >= 4 ? n : 0;
+}
+
+static int check_device(const sb_user_fn *fn) {
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess || dev != fn->device)
     return fail(SB_E_DEVICE, "the user likelihood was compiled for device %d", fn->device);
+  return SB_OK;
+}
+
+// l at N points staged through LDS: the rows of X (R = 0), or (R > 0) the R
+// finite-difference rows of each row of X, formed in place.
+static int user_eval_staged(const sb_user_fn *fn, int64_t N, int d, int64_t R, int npt,
+                            int stride, const double *X, double eps, const double *params,
+                            double *l, hipStream_t s) {
+  int st = check_device(fn);
+  if (st) return st;
+  long long n = (long long)N, r = (long long)R;
+  int dd = d, ds = stride, np = npt;
+  void *args[] = {&n, &dd, &ds, &np, &r, &X, &eps, &params, &l};
+  if (hipModuleLaunchKernel(fn->staged, (unsigned)ceil_div(N, npt), 1, 1, 64, 1, 1,
+                            (unsigned)npt * (unsigned)stride * 8u, s, args, nullptr) !=
+      hipSuccess)
+    return fail(SB_E_DEVICE, "launching the user likelihood failed");
+  return SB_OK;
+}
+
+static int user_eval(const sb_user_fn *fn, int64_t B, int d, const double *X, int64_t ldx,
+                     const double *params, double *l, hipStream_t s) {
+  int stride = 0;
+  const int npt = stage_points(fn, d, &stride);
+  if (npt && ldx == d) return user_eval_staged(fn, B, d, 0, npt, stride, X, 0.0, params, l, s);
+  int st = check_device(fn);
+  if (st) return st;
   long long b = (long long)B, lx = (long long)ldx;
   int dd = d;
   void *args[] = {&b, &dd, &X, &lx, &params, &l};
@@ -554,10 +671,16 @@ int32_t sb_user_fd_dev(const sb_user_fn *fn, int64_t B, int32_t d, const double 
   Arena ar(workspace, ws_bytes);
   double *P = ar.take<double>((size_t)(B * R * d));
   double *F = ar.take<double>((size_t)(B * R));
-  hipLaunchKernelGGL(fd_points_kernel, dim3((unsigned)ceil_div(B * R, 256)), dim3(256), 0, s, B,
-                     d, R, X, eps, P);
-  SB_LAUNCH_CHECK();
-  int st = user_eval(fn, B * R, d, P, d, params, F, s);
+  int stride = 0, st;
+  const int npt = stage_points(fn, d, &stride);
+  if (npt) {
+    st = user_eval_staged(fn, B * R, d, R, npt, stride, X, eps, params, F, s);
+  } else {
+    hipLaunchKernelGGL(fd_points_kernel, dim3((unsigned)ceil_div(B * R, 256)), dim3(256), 0, s,
+                       B, d, R, X, eps, P);
+    SB_LAUNCH_CHECK();
+    st = user_eval(fn, B * R, d, P, d, params, F, s);
+  }
   if (st) return st;
   hipLaunchKernelGGL(fd_combine_kernel, dim3((unsigned)ceil_div(B * d, 256)), dim3(256), 0, s, B,
                      d, R, F, eps, l, grad, hdiag, probe_b);

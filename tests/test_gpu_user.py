@@ -377,3 +377,35 @@ def test_geometry_decisions_match_oracle(L, off, rot_tol, want):
           f"f_perp {float(geo['fperp'].cpu()[0]):.3e} / {ref['fperp'][0]:.3e}", flush=True)
     assert geo["decision"] == list(ref["decision"]) == [want]
     assert abs(geo["log_z"] - ref["log_z"]) < 1e-7
+
+
+WIDE_SRC = r"""
+// -sum_i c_i (x_i - m_i)^2 with params = [c (d), m (d)]
+__device__ double wide(const double *x, int d, const double *p) {
+  double s = 0.0;
+  for (int i = 0; i < d; ++i) s += p[i] * (x[i] - p[d + i]) * (x[i] - p[d + i]);
+  return -s;
+}
+"""
+
+
+@pytest.mark.parametrize("d,B", [(1, 130), (2, 65), (126, 2), (128, 3), (255, 2), (257, 1),
+                                 (1022, 1), (2046, 1), (2049, 1)])
+def test_user_rows_of_every_width(L, d, B):
+    """Rows staged through LDS, 64 to 4 points per workgroup by width, ragged last workgroups,
+    and (d = 2049) rows too long to stage: l and the FD gradient of a separable quadratic whose
+    every coordinate has its own weight.  Each of the d terms and the sum rounds a few times
+    (8 d eps |f|); the difference divides that by eps."""
+    rng = np.random.default_rng(1000 + d)
+    c, m = rng.uniform(0.5, 2.0, d), rng.uniform(-1, 1, d)
+    X = rng.uniform(-2, 2, (B, d))
+    fn = L.UserLogL(WIDE_SRC, "wide")
+    pd = dev(np.concatenate([c, m]))
+    ref = -np.sum(c * (X - m) ** 2, axis=1)
+    fs = np.max(np.abs(ref)) + 1.0
+    tol = 8 * d * EPSM * fs
+    assert np.max(np.abs(fn.logl(dev(X), pd).cpu().numpy() - ref)) <= tol
+    eps = 1e-3
+    out = fn.fd(dev(X), eps, pd)
+    assert np.max(np.abs(out["l"].cpu().numpy() - ref)) <= tol
+    assert np.max(np.abs(out["grad"].cpu().numpy() + 2 * c * (X - m))) <= 2 * tol / eps
