@@ -608,7 +608,7 @@ static int32_t logl_grad_core(const sb_model_dev *mdl, int64_t B, const void *X,
   o.yneg = direct;
   o.qpart = qp;
   const TuneProbe pr{a, o};
-  TileCfg t = autotune_tiles(dtype, m, B, (hipStream_t)stream, tune ? &pr : nullptr, false);
+  TileCfg t = autotune_tiles(dtype, m, B, (hipStream_t)stream, tune ? &pr : nullptr);
   if ((st = launch_quad_gemm(dtype, m, a, B, nullptr, o, t, (hipStream_t)stream))) return st;
   FinishArgs f;
   f.M = B;

@@ -276,18 +276,14 @@ int download(std::vector<T> &dst, const T *src, size_t n, hipStream_t s) {
   return SB_OK;
 }
 
-// Tile shape of a grouped GEMM phase: the autotuner's choice for the batch's
-// largest padded dimension and the phase's row count (timed on private
-// buffers: this is a host-level entry point, which allocates anyway), among
-// the 16-wide k-tiles the grouped kernels run (most of a batch's problems are
-// far narrower than its widest, where a 32-wide k-tile is mostly padding:
-// 64 x 128 x 32 ran the 512-problem batch in 856 ms, 64 x 64 x 16 in 693).
-TileCfg batch_tiles(int dtype, int dp_max, int K_max, int64_t rows, hipStream_t s) {
-  Model m;
-  m.d = dp_max;
-  m.K = K_max;
-  TileCfg t = autotune_tiles(dtype, m, rows, s, nullptr, true, 16);
-  if (t.bm != 64 && t.bm != 128) t.bm = 64;  // (the grouped kernels: 64 or 128 rows)
+// Tile of a grouped GEMM phase.  A batch mixes dimensions (8 to 512 in the
+// 512-problem workload), and small tiles waste least on its narrow problems:
+// 64 x 64, whose k-tile of 32 skips what lies behind a row's end, and which is
+// within 4% of the best FP64 tile at d = 512 and 1024 as well.  The BF16 rays
+// take 128 x 128 (64 x 64 feeds the matrix cores too little per LDS read).
+TileCfg batch_tiles(int dtype) {
+  TileCfg t;
+  t.bm = t.bn = dtype == DT_BF16 ? 128 : 64;
   return t;
 }
 
@@ -424,8 +420,8 @@ int run_evidence_batch(int n, const sb_loglik *ll, const sb_box *box, const sb_c
   }
 
   // grouped GEMM tables of discovery and bulk
-  const TileCfg tdisc = batch_tiles(ddt, dp_max, K_max, NPtot, s);
-  const TileCfg tbulk = batch_tiles(bdt, dp_max, K_max, Btot, s);
+  const TileCfg tdisc = batch_tiles(ddt);
+  const TileCfg tbulk = batch_tiles(bdt);
   SegTable sdisc, sbulk;
   for (int q = 0; q < n; ++q) {
     sdisc.add(probs[q], q, probs[q].R * probs[q].n_pts, tdisc.bm, tdisc.bn);
@@ -884,7 +880,7 @@ int run_evidence_batch(int n, const sb_loglik *ll, const sb_box *box, const sb_c
     chunk_g0.push_back(NR);
   }
   int64_t PC = 0, HC = 0, YC = 0, QC = 0, SC = 0, TC = 0;
-  const TileCfg tpol = batch_tiles(DT_F64, dp_max, K_max, std::min<int64_t>(NR, row_cap), s);
+  const TileCfg tpol = batch_tiles(DT_F64);
   std::vector<SegTable> ctabs(chunk_g0.size() > 0 ? chunk_g0.size() - 1 : 0);
   for (size_t c = 0; c + 1 < chunk_g0.size(); ++c) {
     const int64_t g0 = chunk_g0[c], g1 = chunk_g0[c + 1];

@@ -23,43 +23,46 @@ typedef double d4v __attribute__((ext_vector_type(4)));
 typedef float f4v __attribute__((ext_vector_type(4)));
 typedef __bf16 bf8v __attribute__((ext_vector_type(8)));
 
+// Matrix-core operation of operand type TOp.  A fragment is a 16-byte chunk of
+// a row (CE values of k); the four 16-lane groups of a wave hold four
+// consecutive chunks, and instruction `step` multiplies value(s) `step` of each:
+// a fixed order of k within 64 bytes of a row, the same for both operands.
 template <typename TOp>
 struct Mfma;
 template <>
 struct Mfma<double> {
   using acc_t = double;
   using accv = d4v;
-  static constexpr int KPI = 4;  // k per instruction
-  static constexpr int KPL = 1;  // k values per lane
+  typedef double chunk __attribute__((ext_vector_type(2)));
+  static constexpr int CE = 2, STEPS = 2;
   // accumulator item v of lane l holds row lr + 4v (lr = l/16), column l%16
   __device__ static int row(int lr, int v) { return lr + 4 * v; }
-  __device__ static accv mma(const double *a, const double *b, accv c) {
-    return __builtin_amdgcn_mfma_f64_16x16x4f64(a[0], b[0], c, 0, 0, 0);
+  __device__ static accv mma(const chunk &a, const chunk &b, int step, accv c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a[step], b[step], c, 0, 0, 0);
   }
 };
 template <>
 struct Mfma<float> {
   using acc_t = float;
   using accv = f4v;
-  static constexpr int KPI = 4;
-  static constexpr int KPL = 1;
+  typedef float chunk __attribute__((ext_vector_type(4)));
+  static constexpr int CE = 4, STEPS = 4;
   // accumulator item v of lane l holds row 4 lr + v (lr = l/16), column l%16
   __device__ static int row(int lr, int v) { return 4 * lr + v; }
-  __device__ static accv mma(const float *a, const float *b, accv c) {
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a[0], b[0], c, 0, 0, 0);
+  __device__ static accv mma(const chunk &a, const chunk &b, int step, accv c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a[step], b[step], c, 0, 0, 0);
   }
 };
 template <>
 struct Mfma<bf16_t> {
   using acc_t = float;
   using accv = f4v;
-  static constexpr int KPI = 32;
-  static constexpr int KPL = 8;
+  typedef uint16_t chunk __attribute__((ext_vector_type(8)));
+  static constexpr int CE = 8, STEPS = 1;
   __device__ static int row(int lr, int v) { return 4 * lr + v; }
-  __device__ static accv mma(const bf16_t *a, const bf16_t *b, accv c) {
-    bf8v va = *reinterpret_cast<const bf8v *>(a);
-    bf8v vb = *reinterpret_cast<const bf8v *>(b);
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, vb, c, 0, 0, 0);
+  __device__ static accv mma(const chunk &a, const chunk &b, int, accv c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8v, a),
+                                                   __builtin_bit_cast(bf8v, b), c, 0, 0, 0);
   }
 };
 
@@ -69,7 +72,18 @@ template <>
 __device__ inline float to_op<float>(float v) { return v; }
 template <>
 __device__ inline bf16_t to_op<bf16_t>(float v) { return f32_to_bf16(v); }
-__device__ inline double to_op_d(double v) { return v; }
+
+// Sum over the 16 lanes of a row, in the order of a butterfly from 1 lane up to
+// 8 (quads agree after two steps, so the mirrored quad of the half row serves as
+// the lane four apart).
+template <typename T>
+__device__ inline T row16_sum(T v) {
+  v += dpp_val<kDppXor1>(v);
+  v += dpp_val<kDppXor2>(v);
+  v += dpp_val<kDppHalfMirror>(v);
+  v += dpp_val<kDppRor8>(v);
+  return v;
+}
 
 struct GemmParams {
   ASrc a;
@@ -85,232 +99,91 @@ struct GemmParams {
   int yneg = 0;  // store -Y (a single Gaussian's gradient); q still uses Y
 };
 
-// Value of point `row` at coordinate j (type TIn), without the mean.
-template <typename TIn>
-__device__ inline TIn point_value(const ASrc &a, int64_t row, int64_t d, int j) {
-  if (a.kind == 0) {
-    int64_t r = a.rowmap ? (int64_t)a.rowmap[row] : row;
-    return ((const TIn *)a.X)[r * a.ldx + j];
-  }
-  {
-    // ray point p + t (q - p), t = (j + 1/2) / n_pts; no contraction into an
-    // FMA so that the value is the same two-rounding expression everywhere.
-#pragma clang fp contract(off)
-    int64_t ray = row / a.n_pts;
-    int jj = (int)(row % a.n_pts);
-    TIn t = ((TIn)jj + (TIn)0.5) / (TIn)a.n_pts;
-    TIn p = ((const TIn *)a.P0)[ray * d + j];
-    TIn q = ((const TIn *)a.P1)[ray * d + j];
-    return p + t * (q - p);
-  }
-}
-
-template <typename TIn, typename TOp, int BM, int BN, int BK>
-__global__ __launch_bounds__(256) void quad_gemm_kernel(GemmParams g) {
-  using MF = Mfma<TOp>;
-  using TAcc = typename MF::acc_t;
-  using accv = typename MF::accv;
-  constexpr int PAD = (sizeof(TOp) == 8) ? 2 : (sizeof(TOp) == 4 ? 4 : 8);
-  constexpr int LDA = BK + PAD;
-  constexpr int WM = BM / 2, WN = BN / 2, TM = WM / 16, TN = WN / 16;
-  __shared__ __attribute__((aligned(16))) TOp As[BM * LDA];
-  __shared__ __attribute__((aligned(16))) TOp Bs[BN * LDA];
-  __shared__ TAcc qs[2][BM];
-
-  const int64_t M = g.count ? (int64_t)(*g.count) : g.M;
-  const int64_t m0 = (int64_t)blockIdx.x * BM;
-  if (m0 >= M) return;
-  const int k = blockIdx.y / g.ntn;
-  const int n0 = (blockIdx.y % g.ntn) * BN;
-  const int d = g.d;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1;
-  const TIn *mu = g.a.zero_mu ? nullptr : (const TIn *)g.mu + (size_t)k * d;
-  const TOp *Pk = (const TOp *)g.P + (size_t)k * d * d;
-
-  accv acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j) acc[i][j] = accv{0, 0, 0, 0};
-
-  for (int k0 = 0; k0 < d; k0 += BK) {
-    // A tile: delta = x - mu, converted to the operand type
-    for (int e = tid; e < BM * BK; e += 256) {
-      int i = e / BK, kk = e % BK;
-      int64_t row = m0 + i;
-      int j = k0 + kk;
-      TIn v = 0;
-      if (row < M && j < d) {
-        v = point_value<TIn>(g.a, row, d, j);
-        if (mu) v = v - mu[j];
-      }
-      if constexpr (sizeof(TOp) == 8)
-        As[i * LDA + kk] = v;
-      else
-        As[i * LDA + kk] = to_op<TOp>((float)v);
-    }
-    // B tile: rows n of P_k (Bs[n][j] = P_k[n0+n][k0+j]) so Y_n = sum_j P[n][j] delta_j
-    for (int e = tid; e < BN * BK; e += 256) {
-      int n = e / BK, kk = e % BK;
-      int nn = n0 + n, j = k0 + kk;
-      TOp v;
-      if (nn < d && j < d)
-        v = Pk[(size_t)nn * d + j];
-      else
-        v = TOp(0);
-      Bs[n * LDA + kk] = v;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < BK; kk += MF::KPI) {
-      const int kl = kk + MF::KPL * (lane >> 4);
-      const TOp *af[TM];
-      const TOp *bfp[TN];
-#pragma unroll
-      for (int i = 0; i < TM; ++i) af[i] = &As[(wm * WM + i * 16 + (lane & 15)) * LDA + kl];
-#pragma unroll
-      for (int j = 0; j < TN; ++j) bfp[j] = &Bs[(wn * WN + j * 16 + (lane & 15)) * LDA + kl];
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = MF::mma(af[i], bfp[j], acc[i][j]);
-    }
-    __syncthreads();
-  }
-
-  // Epilogue: store Y, accumulate delta * Y per row over this tile's columns.
-  const int lr = lane >> 4, lc = lane & 15;
-  TAcc qrow[TM][4];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) qrow[i][v] = 0;
-  TAcc *Y = (TAcc *)g.Y;
-#pragma unroll
-  for (int i = 0; i < TM; ++i) {
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int il = wm * WM + i * 16 + MF::row(lr, v);
-      const int64_t row = m0 + il;
-      if (row >= M) continue;
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const int n = n0 + wn * WN + j * 16 + lc;
-        if (n >= d) continue;
-        TAcc yv = acc[i][j][v];
-        if (Y) Y[row * g.ldy + (int64_t)k * d + n] = g.yneg ? -yv : yv;
-        TIn x = point_value<TIn>(g.a, row, d, n);
-        TAcc dl = (TAcc)(mu ? x - mu[n] : x);
-        qrow[i][v] += dl * yv;
-      }
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      TAcc t = qrow[i][v];
-      t += __shfl_xor(t, 1, 64);
-      t += __shfl_xor(t, 2, 64);
-      t += __shfl_xor(t, 4, 64);
-      t += __shfl_xor(t, 8, 64);
-      qrow[i][v] = t;
-    }
-  if (lc == 0) {
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) qs[wn][wm * WM + i * 16 + MF::row(lr, v)] = qrow[i][v];
-  }
-  __syncthreads();
-  if (g.qpart) {
-    TAcc *qp = (TAcc *)g.qpart;
-    for (int i = tid; i < BM; i += 256) {
-      int64_t row = m0 + i;
-      if (row < M) qp[(row * g.K + k) * g.ntn + (blockIdx.y % g.ntn)] = qs[0][i] + qs[1][i];
-    }
-  }
-}
-
 int quad_gemm_ntn(int dtype, int d, TileCfg t) { return (int)ceil_div(d, t.bn); }
 
-template <typename TIn, typename TOp, int BM, int BN, int BK>
-static int launch_scalar(const GemmParams &p, hipStream_t s) {
-  dim3 grid((unsigned)ceil_div(p.M, BM), (unsigned)(p.K * p.ntn));
-  if (grid.x == 0 || grid.y == 0) return SB_OK;
-  hipLaunchKernelGGL((quad_gemm_kernel<TIn, TOp, BM, BN, BK>), grid, dim3(256), 0, s, p);
-  SB_LAUNCH_CHECK();
-  return SB_OK;
-}
-
-// ------------------------------------------------------- vectorised GEMM
+// ------------------------------------------------------------ the kernel
 //
-// Same tile, fragment and epilogue layout as quad_gemm_kernel, for d a
-// multiple of the 16-byte vector widths: every thread owns fixed A rows and
-// B rows for the whole K loop (row pointers and the row map resolved once),
-// loads 16-byte vectors, and prefetches k-tile t+1 into registers while the
-// MFMAs of tile t run from LDS.
-
-template <typename T>
-struct V16;
-template <>
-struct V16<double> {
-  typedef double v __attribute__((ext_vector_type(2)));
-  static constexpr int N = 2;
-};
-template <>
-struct V16<float> {
-  typedef float v __attribute__((ext_vector_type(4)));
-  static constexpr int N = 4;
-};
-template <>
-struct V16<bf16_t> {
-  typedef uint16_t v __attribute__((ext_vector_type(8)));
-  static constexpr int N = 8;
+// BM x BN outputs per workgroup, four waves in a 2 x 2 grid, k-tiles of BK.
+// Every thread owns fixed 16-byte columns of fixed A and B rows for the whole
+// k loop.  Rows start at any element: the loads are 16 bytes wide whatever d
+// and the strides are (global memory takes them at any alignment), and only
+// the chunk that crosses the end of a row goes element by element.  k-tile
+// t + 1 is loaded into registers beside the MFMAs of k-tile t.  An LDS row is BK
+// values without padding, its 16-byte chunk c at c ^ swz(row): stores along a
+// row and fragment reads down eight rows both touch every bank once, and a
+// fragment read feeds two (FP64) or four (FP32) MFMAs.  Against rows padded by
+// 16 bytes, read one value at a time, and an element-by-element form for odd d:
+// FP64 16384 x 1024, K = 8 5.24 -> 4.37 ms (63 of the 73 TFLOP/s a large library
+// product reaches here); 1000 x 203, K = 3 26.9 -> 14.5 us; BF16 ray points at
+// d = 500 2.1 -> 0.65 ms.  A second LDS stage (one barrier per k-tile) cost more
+// occupancy than it saved waits: 4.50 ms and 15.7 us at the same shapes.  Large
+// shapes are bound by the matrix cores; small ones (8192 x 256: 27.5 us, 13.7 us
+// of MFMAs) by the fill and drain of their one round of workgroups.
+template <typename T, int N>
+struct VecU {  // N values of T at T's own alignment
+  typedef T v __attribute__((ext_vector_type(N), aligned(sizeof(T))));
 };
 
 template <typename TIn, typename TOp, int BM, int BN, int BK, int KIND, bool GROUP>
-__global__ __launch_bounds__(256) void quad_gemm_vec_kernel(GemmParams g) {
+__global__ __launch_bounds__(256, 2) void quad_gemm_vec_kernel(GemmParams g) {
   using MF = Mfma<TOp>;
   using TAcc = typename MF::acc_t;
   using accv = typename MF::accv;
-  using VI = typename V16<TIn>::v;
-  using VO = typename V16<TOp>::v;
-  constexpr int NI = V16<TIn>::N, NO = V16<TOp>::N;
-  constexpr int PAD = (sizeof(TOp) == 8) ? 2 : (sizeof(TOp) == 4 ? 4 : 8);
-  constexpr int LDA = BK + PAD;
+  using chunk = typename MF::chunk;
+  constexpr int NI = 16 / sizeof(TIn), CE = MF::CE;
+  using VI = typename VecU<TIn, NI>::v;
+  using VO = typename VecU<TOp, CE>::v;
+  constexpr int C = BK / CE, R = C < 8 ? 8 / C : 1;  // chunks per row, rows per 128 bytes
   constexpr int WM = BM / 2, WN = BN / 2, TM = WM / 16, TN = WN / 16;
-  constexpr int VRA = BK / NI, VRB = BK / NO;
+  constexpr int VRA = BK / NI, VRB = BK / CE;
   constexpr int NA = BM * VRA / 256, NB = BN * VRB / 256;
   static_assert(NA >= 1 && NB >= 1 && (BM * VRA) % 256 == 0 && (BN * VRB) % 256 == 0, "tile");
-  static_assert(256 % VRA == 0 && 256 % VRB == 0, "tile");
-  __shared__ __attribute__((aligned(16))) TOp As[BM * LDA];
-  __shared__ __attribute__((aligned(16))) TOp Bs[BN * LDA];
+  static_assert(256 % VRA == 0 && 256 % VRB == 0 && BK % (4 * CE) == 0, "tile");
+  __shared__ __attribute__((aligned(16))) TOp As[BM * BK];
+  __shared__ __attribute__((aligned(16))) TOp Bs[BN * BK];
   __shared__ TAcc qs[2][BM];
+  __shared__ int64_t roff_s[BM];  // element offset of each row's operand data
+  __shared__ TIn tpar_s[KIND == 1 ? BM : 1];
+  auto lds = [](int row, int kel) {
+    return row * BK + (((kel / CE) ^ ((row / R) % (C < 8 ? C : 8))) * CE) + kel % CE;
+  };
 
   // ---- tile context: rows [m0, M) (global row indices), component k, columns n0..
   int64_t M, m0;
   int k, nt, ntn, d, n_pts;
   const TIn *mu;
   const TOp *Pk;
-  const TIn *X0 = (const TIn *)g.a.X;      // kind 0 rows / kind 1 ray start points
+  const TIn *X0 = (const TIn *)(KIND == 0 ? g.a.X : g.a.P0);
   const TIn *X1 = (const TIn *)g.a.P1;     // kind 1 ray end points
   int64_t pt_first = 0, roff = 0;          // kind 1: first point row, endpoint base
   int64_t ybase = 0, qbase = 0;            // grouped: packed Y / q-partial bases
   int64_t ystr = 0, qstr = 0;              // grouped: Y / q-partial row strides
   if constexpr (!GROUP) {
+    // XCD-aware order: workgroup w runs on XCD w % 8.  With a multiple of
+    // eight column blocks (component, n-tile) each XCD owns a fixed set and
+    // walks the row tiles in order, so a row tile's column blocks share one L2.
+    const int64_t w = blockIdx.x;
+    const int ncol = g.K * g.ntn;
+    int col;
+    int64_t mt;
+    if (ncol % 8 == 0) {
+      const int per = ncol / 8;
+      col = (int)(w % 8) + 8 * (int)((w / 8) % per);
+      mt = (w / 8) / per;
+    } else {
+      col = (int)(w % ncol);
+      mt = w / ncol;
+    }
     M = g.count ? (int64_t)(*g.count) : g.M;
-    m0 = (int64_t)blockIdx.x * BM;
+    m0 = mt * BM;
     if (m0 >= M) return;
     ntn = g.ntn;
-    k = blockIdx.y / ntn;
-    nt = blockIdx.y % ntn;
+    k = col / ntn;
+    nt = col % ntn;
     d = g.d;
     n_pts = g.a.n_pts;
     mu = g.a.zero_mu ? nullptr : (const TIn *)g.mu + (size_t)k * d;
     Pk = (const TOp *)g.P + (size_t)k * d * d;
-    if constexpr (KIND == 1) X0 = (const TIn *)g.a.P0;
   } else {
     const GroupView &gv = g.gv;
     const int sgi = gv.tile_seg[blockIdx.x];
@@ -334,7 +207,6 @@ __global__ __launch_bounds__(256) void quad_gemm_vec_kernel(GemmParams g) {
     ybase = sg.yoff - sg.row0 * ystr;
     qbase = sg.qoff - sg.row0 * qstr;
     if constexpr (KIND == 1) {
-      X0 = (const TIn *)g.a.P0;
       pt_first = sg.row0;
       roff = pr.roff0;
     }
@@ -342,88 +214,87 @@ __global__ __launch_bounds__(256) void quad_gemm_vec_kernel(GemmParams g) {
   const int n0 = nt * BN;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
-
-  // Row pointers of global row `row`: its X row (kind 0) or its ray's two
-  // endpoints and parameter t (kind 1).
-  auto row_src = [&](int64_t row, const TIn *&a, const TIn *&b, TIn &t) {
-    if constexpr (KIND == 0) {
-      int64_t off;
-      if constexpr (GROUP)
-        off = g.gv.rowoff[row];
-      else
-        off = (g.a.rowmap ? (int64_t)g.a.rowmap[row] : row) * g.a.ldx;
-      a = X0 + off;
-      b = nullptr;
-      t = 0;
-    } else {
-      const int64_t i = row - pt_first;
-      const int64_t ray = i / n_pts;
-      const int jj = (int)(i % n_pts);
-      t = ((TIn)jj + (TIn)0.5) / (TIn)n_pts;
-      a = X0 + roff + ray * d;
-      b = X1 + roff + ray * d;
-    }
-  };
-
-  // fixed rows of this thread
   const int ca = tid % VRA, cb = tid % VRB;
-  const TIn *arow[NA];
-  const TIn *qrow_p[NA];
+
+  // Fixed rows of this thread: the operand offset of its X row (kind 0) or of
+  // its ray's endpoints with the parameter t (kind 1).  Rows past M (A) and d
+  // (B) take the tile's first row: they feed only outputs that are not written.
+  int64_t aoff[NA];
   TIn tpar[NA];
-  bool aok[NA];
 #pragma unroll
   for (int r = 0; r < NA; ++r) {
     const int i = (tid + 256 * r) / VRA;
-    const int64_t row = m0 + i;
-    aok[r] = row < M;
-    arow[r] = nullptr;
-    qrow_p[r] = nullptr;
+    const int64_t row = m0 + i < M ? m0 + i : m0;
     tpar[r] = 0;
-    if (aok[r]) row_src(row, arow[r], qrow_p[r], tpar[r]);
+    if constexpr (KIND == 0) {
+      if constexpr (GROUP)
+        aoff[r] = g.gv.rowoff[row];
+      else
+        aoff[r] = (g.a.rowmap ? (int64_t)g.a.rowmap[row] : row) * g.a.ldx;
+    } else {
+      // t = (j + 1/2) / n_pts
+      const int64_t pt = row - pt_first, ray = pt / n_pts;
+      tpar[r] = ((TIn)(int)(pt - ray * n_pts) + (TIn)0.5) / (TIn)n_pts;
+      aoff[r] = roff + ray * d;
+    }
+    if (ca == 0) {
+      roff_s[i] = aoff[r];
+      if constexpr (KIND == 1) tpar_s[i] = tpar[r];
+    }
+    aoff[r] += ca * NI;
   }
   const TOp *brow[NB];
-  bool bok[NB];
 #pragma unroll
   for (int r = 0; r < NB; ++r) {
-    const int n = (tid + 256 * r) / VRB;
-    bok[r] = (n0 + n) < d;
-    brow[r] = Pk + (size_t)(n0 + n) * d;
+    const int n = n0 + (tid + 256 * r) / VRB;
+    brow[r] = Pk + (size_t)(n < d ? n : n0) * d + cb * CE;
   }
 
   VI ra[NA], rq[NA], rmu;
   VO rb[NB];
-  auto zero_i = []() {
-    VI z;
+  // the part of a chunk below the row's end (n values left), zeros behind it
+  auto part_i = [](const TIn *p, int n) {
+    VI v;
 #pragma unroll
-    for (int e = 0; e < NI; ++e) z[e] = (TIn)0;
-    return z;
+    for (int e = 0; e < NI; ++e) v[e] = e < n ? p[e] : (TIn)0;
+    return v;
   };
-  auto zero_o = []() {
-    VO z;
+  auto part_o = [](const TOp *p, int n) {
+    VO v;
 #pragma unroll
-    for (int e = 0; e < NO; ++e) z[e] = 0;
-    return z;
+    for (int e = 0; e < CE; ++e) v[e] = e < n ? p[e] : (TOp)0;
+    return v;
   };
+#pragma unroll
+  for (int e = 0; e < NI; ++e) rmu[e] = (TIn)0;
   auto load = [&](int k0) {
-    const int ka = k0 + ca * NI;
-    const bool kin = ka < d;
+    if (k0 + BK <= d) {  // (uniform)
 #pragma unroll
-    for (int r = 0; r < NA; ++r) {
-      const bool ok = aok[r] && kin;
-      ra[r] = ok ? *(const VI *)(arow[r] + ka) : zero_i();
-      if constexpr (KIND == 1) rq[r] = ok ? *(const VI *)(qrow_p[r] + ka) : zero_i();
+      for (int r = 0; r < NA; ++r) {
+        ra[r] = *(const VI *)(X0 + aoff[r] + k0);
+        if constexpr (KIND == 1) rq[r] = *(const VI *)(X1 + aoff[r] + k0);
+      }
+      if (mu) rmu = *(const VI *)(mu + k0 + ca * NI);
+#pragma unroll
+      for (int r = 0; r < NB; ++r) rb[r] = *(const VO *)(brow[r] + k0);
+    } else {
+      const int na = d - (k0 + ca * NI), nb = d - (k0 + cb * CE);
+#pragma unroll
+      for (int r = 0; r < NA; ++r) {
+        ra[r] = part_i(X0 + aoff[r] + k0, na);
+        if constexpr (KIND == 1) rq[r] = part_i(X1 + aoff[r] + k0, na);
+      }
+      if (mu) rmu = part_i(mu + k0 + ca * NI, na);
+#pragma unroll
+      for (int r = 0; r < NB; ++r) rb[r] = part_o(brow[r] + k0, nb);
     }
-    rmu = (mu && kin) ? *(const VI *)(mu + ka) : zero_i();
-    const int kb = k0 + cb * NO;
-    const bool kbin = kb < d;
-#pragma unroll
-    for (int r = 0; r < NB; ++r) rb[r] = (bok[r] && kbin) ? *(const VO *)(brow[r] + kb) : zero_o();
   };
   auto store = [&]() {
 #pragma unroll
     for (int r = 0; r < NA; ++r) {
       const int i = (tid + 256 * r) / VRA;
-      TOp *dst = &As[i * LDA + ca * NI];
+      typedef TOp vop __attribute__((ext_vector_type(NI)));
+      vop w;
 #pragma unroll
       for (int e = 0; e < NI; ++e) {
         TIn x;
@@ -433,17 +304,18 @@ __global__ __launch_bounds__(256) void quad_gemm_vec_kernel(GemmParams g) {
 #pragma clang fp contract(off)
           x = ra[r][e] + tpar[r] * (rq[r][e] - ra[r][e]);
         }
-        const TIn v = aok[r] ? x - rmu[e] : (TIn)0;
+        const TIn v = x - rmu[e];  // (k >= d: both zero)
         if constexpr (sizeof(TOp) == 8)
-          dst[e] = v;
+          w[e] = v;
         else
-          dst[e] = to_op<TOp>((float)v);
+          w[e] = to_op<TOp>((float)v);
       }
+      *(vop *)&As[lds(i, ca * NI)] = w;
     }
 #pragma unroll
     for (int r = 0; r < NB; ++r) {
       const int n = (tid + 256 * r) / VRB;
-      *(VO *)&Bs[n * LDA + cb * NO] = rb[r];
+      *(chunk *)&Bs[lds(n, cb * CE)] = rb[r];
     }
   };
 
@@ -452,85 +324,94 @@ __global__ __launch_bounds__(256) void quad_gemm_vec_kernel(GemmParams g) {
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j) acc[i][j] = accv{0, 0, 0, 0};
+  const int lr = lane >> 4, lc = lane & 15;
+  auto mma = [&](int kk) {  // the 4 CE values of k at kk of the k-tile
+    chunk af[TM], bf[TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+      af[i] = *(const chunk *)&As[lds(wm * WM + i * 16 + lc, kk + lr * CE)];
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+      bf[j] = *(const chunk *)&Bs[lds(wn * WN + j * 16 + lc, kk + lr * CE)];
+#pragma unroll
+    for (int q = 0; q < MF::STEPS; ++q)
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = MF::mma(af[i], bf[j], q, acc[i][j]);
+  };
 
   load(0);
   for (int k0 = 0; k0 < d; k0 += BK) {
     store();
     __syncthreads();
     if (k0 + BK < d) load(k0 + BK);
+    if (k0 + BK <= d) {
 #pragma unroll
-    for (int kk = 0; kk < BK; kk += MF::KPI) {
-      const int kl = kk + MF::KPL * (lane >> 4);
-      const TOp *af[TM];
-      const TOp *bfp[TN];
-#pragma unroll
-      for (int i = 0; i < TM; ++i) af[i] = &As[(wm * WM + i * 16 + (lane & 15)) * LDA + kl];
-#pragma unroll
-      for (int j = 0; j < TN; ++j) bfp[j] = &Bs[(wn * WN + j * 16 + (lane & 15)) * LDA + kl];
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = MF::mma(af[i], bfp[j], acc[i][j]);
+      for (int kk = 0; kk < BK; kk += 4 * CE) mma(kk);
+    } else {  // (no products of the zeros behind the rows' end)
+      for (int kk = 0; k0 + kk < d; kk += 4 * CE) mma(kk);
     }
     __syncthreads();
   }
 
-  // Epilogue: store Y, partial q per row for this tile's columns.
-  const int lr = lane >> 4, lc = lane & 15;
-  TAcc qrow[TM][4];
+  // Epilogue: the partial q per row over this tile's columns, then Y.  The
+  // points are read again before any store (vmcnt counts both in order: a load
+  // behind a store would wait for it).
+  const int cbase = n0 + wn * WN + lc;
+  TAcc muv[TN];
 #pragma unroll
-  for (int i = 0; i < TM; ++i)
+  for (int j = 0; j < TN; ++j) {
+    const int n = cbase + j * 16;
+    muv[j] = (mu && n < d) ? (TAcc)mu[n] : (TAcc)0;
+  }
+  if (g.qpart) {
 #pragma unroll
-    for (int v = 0; v < 4; ++v) qrow[i][v] = 0;
-  TAcc *Y = (TAcc *)g.Y;
-  const int64_t ystride = GROUP ? ystr : g.ldy;
+    for (int i = 0; i < TM; ++i) {
+      TIn x[4][TN];
 #pragma unroll
-  for (int i = 0; i < TM; ++i) {
+      for (int v = 0; v < 4; ++v) {
+        const int il = wm * WM + i * 16 + MF::row(lr, v);
+        const int64_t off = roff_s[il];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int il = wm * WM + i * 16 + MF::row(lr, v);
-      const int64_t row = m0 + il;
-      if (row >= M) continue;
-      const TIn *pa, *pb;
-      TIn tt;
-      row_src(row, pa, pb, tt);
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const int n = n0 + wn * WN + j * 16 + lc;
-        if (n >= d) continue;
-        TAcc yv = acc[i][j][v];
-        if (Y) Y[ybase + row * ystride + (int64_t)k * d + n] = g.yneg ? -yv : yv;
-        TIn x;
-        if constexpr (KIND == 0) {
-          x = pa[n];
-        } else {
+        for (int j = 0; j < TN; ++j) {
+          const int n = cbase + j * 16;
+          x[v][j] = n < d ? X0[off + n] : (TIn)0;
+          if constexpr (KIND == 1) {
 #pragma clang fp contract(off)
-          x = pa[n] + tt * (pb[n] - pa[n]);
+            const TIn e = n < d ? X1[off + n] : (TIn)0;
+            x[v][j] = x[v][j] + tpar_s[il] * (e - x[v][j]);
+          }
         }
-        TAcc dl = (TAcc)(mu ? x - mu[n] : x);
-        qrow[i][v] += dl * yv;
+      }
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        TAcc q = 0;
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+          if (cbase + j * 16 < d) q += ((TAcc)x[v][j] - muv[j]) * acc[i][j][v];
+        q = row16_sum(q);
+        if (lc == 0) qs[wn][wm * WM + i * 16 + MF::row(lr, v)] = q;
       }
     }
   }
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      TAcc t = qrow[i][v];
-      t += __shfl_xor(t, 1, 64);
-      t += __shfl_xor(t, 2, 64);
-      t += __shfl_xor(t, 4, 64);
-      t += __shfl_xor(t, 8, 64);
-      qrow[i][v] = t;
-    }
-  if (lc == 0) {
+  if (g.Y) {
+    TAcc *Y = (TAcc *)g.Y;
+    const int64_t ystride = GROUP ? ystr : g.ldy;
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) qs[wn][wm * WM + i * 16 + MF::row(lr, v)] = qrow[i][v];
+      for (int v = 0; v < 4; ++v) {
+        const int64_t row = m0 + wm * WM + i * 16 + MF::row(lr, v);
+        if (row >= M) continue;
+        TAcc *y = Y + ybase + row * ystride + (int64_t)k * d;
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+          if (cbase + j * 16 < d) y[cbase + j * 16] = g.yneg ? -acc[i][j][v] : acc[i][j][v];
+      }
   }
-  __syncthreads();
   if (g.qpart) {
+    __syncthreads();
     TAcc *qp = (TAcc *)g.qpart;
     for (int i = tid; i < BM; i += 256) {
       const int64_t row = m0 + i;
@@ -545,17 +426,19 @@ __global__ __launch_bounds__(256) void quad_gemm_vec_kernel(GemmParams g) {
 
 template <typename TIn, typename TOp, int BM, int BN, int BK>
 static int launch_t(const GemmParams &p, hipStream_t s) {
-  dim3 grid((unsigned)ceil_div(p.M, BM), (unsigned)(p.K * p.ntn));
-  if (grid.x == 0 || grid.y == 0) return SB_OK;
-  // vector path: 16-byte aligned rows of X (or ray endpoints), mu and P
-  const bool vec = (p.d % V16<TIn>::N == 0) && (p.d % V16<TOp>::N == 0) &&
-                   (p.a.kind == 1 || p.a.ldx % V16<TIn>::N == 0);
-  if (vec && p.a.kind == 0)
-    hipLaunchKernelGGL((quad_gemm_vec_kernel<TIn, TOp, BM, BN, BK, 0, false>), grid, dim3(256), 0, s, p);
-  else if (vec)
-    hipLaunchKernelGGL((quad_gemm_vec_kernel<TIn, TOp, BM, BN, BK, 1, false>), grid, dim3(256), 0, s, p);
+  const int64_t tiles = ceil_div(p.M, BM) * p.K * p.ntn;
+  if (tiles <= 0) return SB_OK;
+  if (tiles > 0x7fffffffll) {
+    set_error("contraction too large for one launch (%lld tiles)", (long long)tiles);
+    return SB_E_UNSUPPORTED;
+  }
+  const dim3 grid((unsigned)tiles);
+  if (p.a.kind == 0)
+    hipLaunchKernelGGL((quad_gemm_vec_kernel<TIn, TOp, BM, BN, BK, 0, false>), grid,
+                       dim3(256), 0, s, p);
   else
-    return launch_scalar<TIn, TOp, BM, BN, BK>(p, s);
+    hipLaunchKernelGGL((quad_gemm_vec_kernel<TIn, TOp, BM, BN, BK, 1, false>), grid,
+                       dim3(256), 0, s, p);
   SB_LAUNCH_CHECK();
   return SB_OK;
 }
@@ -1614,9 +1497,11 @@ int launch_quad_gemm_group(int dtype, const BatchDev &b, const GroupView &gv_in,
   p.Y = Y;
   p.qpart = qpart;
   p.gv = gv_in;
-  const int bn = (t.bn == 64) ? 64 : 128;
-  const int bm = (t.bm == 64) ? 64 : 128;
-  dim3 grid((unsigned)n_tiles, (unsigned)(b.K_max * ceil_div(b.dp_max, bn)));
+  if (t.bm != t.bn || (t.bm != 64 && t.bm != 128) || (dtype != DT_BF16 && t.bm != 64)) {
+    set_error("grouped contraction: no %d x %d tile", t.bm, t.bn);
+    return SB_E_INVAL;
+  }
+  dim3 grid((unsigned)n_tiles, (unsigned)(b.K_max * ceil_div(b.dp_max, t.bn)));
   if (dtype == DT_F64) {
     p.gv.mu = b.mu64;
     p.gv.P = b.P64;
@@ -1627,31 +1512,19 @@ int launch_quad_gemm_group(int dtype, const BatchDev &b, const GroupView &gv_in,
     p.gv.mu = b.mu32;
     p.gv.P = b.Pbf;
   }
-#define SB_GG(TI, TO, BMv, BNv, BKv)                                                             \
+#define SB_GG(TI, TO, BMv, BNv)                                                                  \
   do {                                                                                           \
     if (p.a.kind == 0)                                                                           \
-      hipLaunchKernelGGL((quad_gemm_vec_kernel<TI, TO, BMv, BNv, BKv, 0, true>), grid, dim3(256), \
+      hipLaunchKernelGGL((quad_gemm_vec_kernel<TI, TO, BMv, BNv, 32, 0, true>), grid, dim3(256), \
                          0, s, p);                                                               \
     else                                                                                         \
-      hipLaunchKernelGGL((quad_gemm_vec_kernel<TI, TO, BMv, BNv, BKv, 1, true>), grid, dim3(256), \
+      hipLaunchKernelGGL((quad_gemm_vec_kernel<TI, TO, BMv, BNv, 32, 1, true>), grid, dim3(256), \
                          0, s, p);                                                               \
   } while (0)
-  if (dtype == DT_F64) {
-    if (bm == 64 && bn == 64) SB_GG(double, double, 64, 64, 16);
-    else if (bm == 128 && bn == 64) SB_GG(double, double, 128, 64, 16);
-    else if (bm == 64) SB_GG(double, double, 64, 128, 16);
-    else SB_GG(double, double, 128, 128, 16);
-  } else if (dtype == DT_F32) {
-    if (bm == 64 && bn == 64) SB_GG(float, float, 64, 64, 16);
-    else if (bm == 128 && bn == 64) SB_GG(float, float, 128, 64, 16);
-    else if (bm == 64) SB_GG(float, float, 64, 128, 16);
-    else SB_GG(float, float, 128, 128, 16);
-  } else {
-    if (bm == 64 && bn == 64) SB_GG(float, bf16_t, 64, 64, 32);
-    else if (bm == 128 && bn == 64) SB_GG(float, bf16_t, 128, 64, 32);
-    else if (bm == 64) SB_GG(float, bf16_t, 64, 128, 32);
-    else SB_GG(float, bf16_t, 128, 128, 32);
-  }
+  if (dtype == DT_F64) SB_GG(double, double, 64, 64);
+  else if (dtype == DT_F32) SB_GG(float, float, 64, 64);
+  else if (t.bm == 64) SB_GG(float, bf16_t, 64, 64);
+  else SB_GG(float, bf16_t, 128, 128);
 #undef SB_GG
   SB_LAUNCH_CHECK();
   return SB_OK;

@@ -503,16 +503,14 @@ int launch_mgs_chunks(int n_chunks, int d, const int32_t *off, const int32_t *cn
 // Autotuner: tile choice for the quadratic-form GEMM (cached per shape class).
 // Candidates are timed on the caller's own operands and scratch outputs
 // (`probe`: the launch about to be made, whose outputs the real launch then
-// overwrites), so device entry points allocate nothing.  Without a probe the
-// shape is timed on private buffers only when `may_alloc` (host-level
-// entry points), else the heuristic choice is returned uncached.
+// overwrites), so nothing is allocated.  Without a probe the heuristic choice
+// is returned uncached.
 struct TuneProbe {
   ASrc a;
   QuadOut o;
 };
 TileCfg autotune_tiles(int dtype, const Model &m, int64_t M, hipStream_t s,
-                       const TuneProbe *probe = nullptr, bool may_alloc = false,
-                       int kt = 32);
+                       const TuneProbe *probe);
 
 }  // namespace sb
 

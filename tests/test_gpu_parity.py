@@ -810,3 +810,37 @@ def test_logl_grad_largest_supported_dimension(L):
     l, g = L.sb_logl_grad_dev(L.DeviceModel(prob), dev(X))
     assert rel(l.cpu().numpy(), lo) < 1e-10
     assert rel(g.cpu().numpy(), go, axis=1) < 1e-10
+
+
+@pytest.mark.parametrize("tile", ["64x64x32", "64x128x16", "128x128x16", "32x64x32"])
+@pytest.mark.parametrize("d", [1, 3, 16, 17, 33, 63, 65, 127, 130])
+def test_quadform_edges(L, d, tile, monkeypatch):
+    """The FP64 and FP32 matrix-core contraction alone at the edges of its column tiles and
+    k-tiles, rows of any alignment (odd d) and ragged row tiles: Y = P (x - mu) and the row's
+    quadratic form from the same products, against FP64 products of the operands the kernel
+    reads.  d products and their sum round 2 d u at most (the bound is relative to the sum of
+    magnitudes); q adds d more products."""
+    monkeypatch.setenv("SB_TILE", tile)
+    K = 2
+    for dt, u, B in ((torch.float64, 2.0 ** -53, 67), (torch.float32, 2.0 ** -24, 129)):
+        rng = np.random.Generator(np.random.PCG64(500 + d))
+        P = np.stack([synth.random_precision(rng, d, 0.1, 1.0)[0] for _ in range(K)])
+        mu = rng.uniform(-1, 1, (K, d))
+        prob = synth.Problem(0, 0, d, K, np.zeros(K), mu, P, 0.0, 0.0, -np.ones(d), np.ones(d),
+                             np.zeros(K))
+        m = L.DeviceModel(prob, low_precision=True)
+        X = dev(rng.uniform(-2, 2, (B, d))).to(dt)
+        q = L.QuadForm(m, X)
+        q()
+        Pd = (m.prec if dt == torch.float64 else m.prec_f32.double()).cpu()
+        mud = (m.mu if dt == torch.float64 else m.mu_f32).cpu()
+        for k in range(K):
+            delta = (X.cpu() - mud[k]).double()  # (one rounding, as the kernel takes it)
+            Y = delta @ Pd[k].T
+            mag = delta.abs() @ Pd[k].abs().T
+            got = q.Y[:, k * d:(k + 1) * d].cpu().double()
+            assert bool(((got - Y).abs() <= 2 * d * u * mag + 1e-300).all())
+            nt = q.n_tiles.value
+            qk = q.qpart.reshape(-1)[:B * K * nt].reshape(B, K, nt)[:, k].double().sum(1).cpu()
+            qmag = (delta.abs() * mag).sum(1)
+            assert bool(((qk - (delta * Y).sum(1)).abs() <= 4 * (d + 1) * u * qmag).all())
