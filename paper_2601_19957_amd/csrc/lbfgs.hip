@@ -50,70 +50,99 @@ struct LbArgs {
   int32_t *count_reset;     // compaction count, zeroed by this launch (nullable)
 };
 
-// A thread's chunk [i0, i0 + EPT) of a length-d vector (i0 = tid * EPT):
-// one vector access when `vec` (d and the base offset multiples of EPT, so
-// the chunk is aligned) and the chunk is whole, else element by element.
-template <typename T, int EPT>
-__device__ inline void vload(const T *p, int i0, int d, bool vec, T (&v)[EPT]) {
-  if constexpr (EPT > 1) {
-    typedef T vt __attribute__((ext_vector_type(EPT)));
-    if (vec && i0 + EPT <= d) {
-      const vt w = *(const vt *)(p + i0);
+// A thread's chunk [i0, i0 + EPT) of a length-d vector (i0 = tid * EPT), at
+// whatever element the vector starts: a whole chunk is one access of 16-byte
+// pieces (global memory takes them at any alignment); the chunk that crosses
+// the end takes its whole pieces and the values behind them one by one.
+// NT: the streaming form, for the history ring and the direction, which are
+// read and written once per step and not again before the whole batch has moved
+// several times the size of the last-level cache: non-temporal accesses keep
+// them from displacing the points and gradients the contraction reads next.
+template <typename T, int N>
+struct VecU {
+  typedef T v __attribute__((ext_vector_type(N), aligned(sizeof(T))));
+};
+template <typename T, int N, bool NT>
+__device__ inline void piece_load(const T *p, T *v) {
+  if constexpr (N == 1) {
+    v[0] = NT ? __builtin_nontemporal_load(p) : *p;
+  } else {
+    typedef typename VecU<T, N>::v vt;
+    const vt w = NT ? __builtin_nontemporal_load((const vt *)p) : *(const vt *)p;
 #pragma unroll
-      for (int e = 0; e < EPT; ++e) v[e] = w[e];
-      return;
-    }
+    for (int e = 0; e < N; ++e) v[e] = w[e];
   }
+}
+template <typename T, int N, bool NT>
+__device__ inline void piece_store(T *p, const T *v) {
+  if constexpr (N == 1) {
+    if constexpr (NT)
+      __builtin_nontemporal_store(v[0], p);
+    else
+      *p = v[0];
+  } else {
+    typedef typename VecU<T, N>::v vt;
+    vt w;
 #pragma unroll
-  for (int e = 0; e < EPT; ++e) v[e] = (i0 + e < d) ? p[i0 + e] : (T)0;
+    for (int e = 0; e < N; ++e) w[e] = v[e];
+    if constexpr (NT)
+      __builtin_nontemporal_store(w, (vt *)p);
+    else
+      *(vt *)p = w;
+  }
 }
 template <typename T, int EPT>
-__device__ inline void vstore(T *p, int i0, int d, bool vec, const T (&v)[EPT]) {
-  if constexpr (EPT > 1) {
-    typedef T vt __attribute__((ext_vector_type(EPT)));
-    if (vec && i0 + EPT <= d) {
-      vt w;
-#pragma unroll
-      for (int e = 0; e < EPT; ++e) w[e] = v[e];
-      *(vt *)(p + i0) = w;
-      return;
-    }
+constexpr int kPiece = EPT < (int)(16 / sizeof(T)) ? EPT : (int)(16 / sizeof(T));
+template <typename T, int EPT, bool NT>
+__device__ inline void chunk_load(const T *p, int i0, int d, T (&v)[EPT]) {
+  constexpr int N = kPiece<T, EPT>;
+  if (i0 + EPT <= d) {
+    piece_load<T, EPT, NT>(p + i0, v);
+    return;
   }
 #pragma unroll
-  for (int e = 0; e < EPT; ++e)
-    if (i0 + e < d) p[i0 + e] = v[e];
+  for (int q = 0; q < EPT; q += N) {
+    if (i0 + q + N <= d) {
+      piece_load<T, N, NT>(p + i0 + q, &v[q]);
+    } else {
+#pragma unroll
+      for (int e = q; e < q + N; ++e) v[e] = (i0 + e < d) ? p[i0 + e] : (T)0;
+    }
+  }
 }
-
-// Streaming variants for the history ring, read and written once per step and
-// not again before the whole batch has moved several times the size of the
-// last-level cache: non-temporal accesses keep it from displacing the points
-// and gradients the contraction reads next.
-template <typename T, int EPT>
-__device__ inline void vload_nt(const T *p, int i0, int d, bool vec, T (&v)[EPT]) {
-  if constexpr (EPT > 1) {
-    typedef T vt __attribute__((ext_vector_type(EPT)));
-    if (vec && i0 + EPT <= d) {
-      const vt w = __builtin_nontemporal_load((const vt *)(p + i0));
+template <typename T, int EPT, bool NT>
+__device__ inline void chunk_store(T *p, int i0, int d, const T (&v)[EPT]) {
+  constexpr int N = kPiece<T, EPT>;
+  if (i0 + EPT <= d) {
+    piece_store<T, EPT, NT>(p + i0, v);
+    return;
+  }
 #pragma unroll
-      for (int e = 0; e < EPT; ++e) v[e] = w[e];
-      return;
+  for (int q = 0; q < EPT; q += N) {
+    if (i0 + q + N <= d) {
+      piece_store<T, N, NT>(p + i0 + q, &v[q]);
+    } else {
+#pragma unroll
+      for (int e = q; e < q + N; ++e)
+        if (i0 + e < d) p[i0 + e] = v[e];
     }
   }
-  vload<T, EPT>(p, i0, d, vec, v);
 }
 template <typename T, int EPT>
-__device__ inline void vstore_nt(T *p, int i0, int d, bool vec, const T (&v)[EPT]) {
-  if constexpr (EPT > 1) {
-    typedef T vt __attribute__((ext_vector_type(EPT)));
-    if (vec && i0 + EPT <= d) {
-      vt w;
-#pragma unroll
-      for (int e = 0; e < EPT; ++e) w[e] = v[e];
-      __builtin_nontemporal_store(w, (vt *)(p + i0));
-      return;
-    }
-  }
-  vstore<T, EPT>(p, i0, d, vec, v);
+__device__ inline void vload(const T *p, int i0, int d, T (&v)[EPT]) {
+  chunk_load<T, EPT, false>(p, i0, d, v);
+}
+template <typename T, int EPT>
+__device__ inline void vstore(T *p, int i0, int d, const T (&v)[EPT]) {
+  chunk_store<T, EPT, false>(p, i0, d, v);
+}
+template <typename T, int EPT>
+__device__ inline void vload_nt(const T *p, int i0, int d, T (&v)[EPT]) {
+  chunk_load<T, EPT, true>(p, i0, d, v);
+}
+template <typename T, int EPT>
+__device__ inline void vstore_nt(T *p, int i0, int d, const T (&v)[EPT]) {
+  chunk_store<T, EPT, true>(p, i0, d, v);
 }
 
 // The history ring in BF16 (FP32 starts): a thread's EPT values as EPT
@@ -124,32 +153,34 @@ __device__ inline float bf16_round(float v) {
   return (float)h;
 }
 template <int EPT>
-__device__ inline void hload_nt(const uint16_t *p, int i0, int d, bool vec, float (&v)[EPT]) {
-  if constexpr (EPT == 4) {
-    if (vec && i0 + 4 <= d) {
-      typedef uint32_t u2v __attribute__((ext_vector_type(2)));
-      const u2v w = __builtin_nontemporal_load((const u2v *)(p + i0));
-      v[0] = __builtin_bit_cast(float, w[0] << 16);
-      v[1] = __builtin_bit_cast(float, w[0] & 0xffff0000u);
-      v[2] = __builtin_bit_cast(float, w[1] << 16);
-      v[3] = __builtin_bit_cast(float, w[1] & 0xffff0000u);
-      return;
+__device__ inline void hload_nt(const uint16_t *p, int i0, int d, float (&v)[EPT]) {
+  // (chunks that cross the end, and odd chunk sizes: four values at a time)
+#pragma unroll
+  for (int q = 0; q < EPT; q += (EPT % 4 ? 1 : 4)) {
+    if (EPT % 4 == 0 && i0 + q + 4 <= d) {
+      typedef uint32_t u2v __attribute__((ext_vector_type(2), aligned(2)));
+      const u2v w = __builtin_nontemporal_load((const u2v *)(p + i0 + q));
+      v[q] = __builtin_bit_cast(float, w[0] << 16);
+      v[q + 1] = __builtin_bit_cast(float, w[0] & 0xffff0000u);
+      v[q + 2] = __builtin_bit_cast(float, w[1] << 16);
+      v[q + 3] = __builtin_bit_cast(float, w[1] & 0xffff0000u);
+    } else {
+#pragma unroll
+      for (int e = q; e < q + (EPT % 4 ? 1 : 4); ++e)
+        v[e] = (i0 + e < d) ? __builtin_bit_cast(float, (uint32_t)p[i0 + e] << 16) : 0.f;
     }
   }
-#pragma unroll
-  for (int e = 0; e < EPT; ++e)
-    v[e] = (i0 + e < d) ? __builtin_bit_cast(float, (uint32_t)p[i0 + e] << 16) : 0.f;
 }
 template <int EPT>
-__device__ inline void hstore_nt(uint16_t *p, int i0, int d, bool vec, const float (&v)[EPT]) {
+__device__ inline void hstore_nt(uint16_t *p, int i0, int d, const float (&v)[EPT]) {
   // (v already holds BF16 values: the top 16 bits are exact)
   auto pk = [&](int e) {
     return (__builtin_bit_cast(uint32_t, v[e]) >> 16) |
            (__builtin_bit_cast(uint32_t, v[e + 1]) & 0xffff0000u);
   };
   if constexpr (EPT % 8 == 0) {
-    if (vec && i0 + EPT <= d) {
-      typedef uint32_t u4v __attribute__((ext_vector_type(4)));
+    if (i0 + EPT <= d) {
+      typedef uint32_t u4v __attribute__((ext_vector_type(4), aligned(2)));
 #pragma unroll
       for (int q = 0; q < EPT; q += 8) {
         u4v w;
@@ -160,62 +191,52 @@ __device__ inline void hstore_nt(uint16_t *p, int i0, int d, bool vec, const flo
       return;
     }
   }
-  if constexpr (EPT == 4) {
-    if (vec && i0 + 4 <= d) {
-      typedef uint32_t u2v __attribute__((ext_vector_type(2)));
-      u2v w;
-      w[0] = pk(0);
-      w[1] = pk(2);
-      __builtin_nontemporal_store(w, (u2v *)(p + i0));
-      return;
-    }
-  }
 #pragma unroll
-  for (int e = 0; e < EPT; ++e)
-    if (i0 + e < d) p[i0 + e] = (uint16_t)(__builtin_bit_cast(uint32_t, v[e]) >> 16);
+  for (int q = 0; q < EPT; q += (EPT % 4 ? 1 : 4)) {
+    if constexpr (EPT % 4 == 0) {
+      if (i0 + q + 4 <= d) {
+        typedef uint32_t u2v __attribute__((ext_vector_type(2), aligned(2)));
+        u2v w;
+        w[0] = pk(q);
+        w[1] = pk(q + 2);
+        __builtin_nontemporal_store(w, (u2v *)(p + i0 + q));
+        continue;
+      }
+    }
+#pragma unroll
+    for (int e = q; e < q + (EPT % 4 ? 1 : 4); ++e)
+      if (i0 + e < d) p[i0 + e] = (uint16_t)(__builtin_bit_cast(uint32_t, v[e]) >> 16);
+  }
 }
-// The raw words of a thread's EPT BF16 values (EPT even, whole aligned
-// chunk), kept packed in registers: no conversion between the loads, so the
-// loads of a whole history issue back to back.
+// The raw words of a thread's EPT BF16 values (EPT even, whole chunk), kept
+// packed in registers: no conversion between the loads, so the loads of a whole
+// history issue back to back.
 template <int EPT>
 __device__ inline void hload_raw_nt(const uint16_t *p, int i0, uint32_t (&w)[EPT / 2]) {
   static_assert(EPT % 2 == 0, "whole 32-bit words");
-  typedef uint32_t u2v __attribute__((ext_vector_type(2)));
-  typedef uint32_t u4v __attribute__((ext_vector_type(4)));
-  if constexpr (EPT % 8 == 0) {
+  constexpr int N = EPT % 8 == 0 ? 4 : (EPT % 4 == 0 ? 2 : 1);
+  typedef uint32_t uv __attribute__((ext_vector_type(N), aligned(2)));
 #pragma unroll
-    for (int q = 0; q < EPT / 2; q += 4) {
-      const u4v t = __builtin_nontemporal_load((const u4v *)(p + i0 + 2 * q));
+  for (int q = 0; q < EPT / 2; q += N) {
+    const uv t = __builtin_nontemporal_load((const uv *)(p + i0 + 2 * q));
 #pragma unroll
-      for (int e = 0; e < 4; ++e) w[q + e] = t[e];
-    }
-  } else if constexpr (EPT % 4 == 0) {
-#pragma unroll
-    for (int q = 0; q < EPT / 2; q += 2) {
-      const u2v t = __builtin_nontemporal_load((const u2v *)(p + i0 + 2 * q));
-      w[q] = t[0];
-      w[q + 1] = t[1];
-    }
-  } else {
-#pragma unroll
-    for (int q = 0; q < EPT / 2; ++q)
-      w[q] = __builtin_nontemporal_load((const uint32_t *)(p + i0 + 2 * q));
+    for (int e = 0; e < N; ++e) w[q + e] = t[e];
   }
 }
 // Ring access for history type HB (BF16 when true, else T).
 template <typename T, int EPT, bool HB>
-__device__ inline void ring_load(const T *base, size_t off, int i0, int d, bool vec, T (&v)[EPT]) {
+__device__ inline void ring_load(const T *base, size_t off, int i0, int d, T (&v)[EPT]) {
   if constexpr (HB)
-    hload_nt<EPT>((const uint16_t *)base + off, i0, d, vec, v);
+    hload_nt<EPT>((const uint16_t *)base + off, i0, d, v);
   else
-    vload_nt<T, EPT>(base + off, i0, d, vec, v);
+    vload_nt<T, EPT>(base + off, i0, d, v);
 }
 template <typename T, int EPT, bool HB>
-__device__ inline void ring_store(T *base, size_t off, int i0, int d, bool vec, const T (&v)[EPT]) {
+__device__ inline void ring_store(T *base, size_t off, int i0, int d, const T (&v)[EPT]) {
   if constexpr (HB)
-    hstore_nt<EPT>((uint16_t *)base + off, i0, d, vec, v);
+    hstore_nt<EPT>((uint16_t *)base + off, i0, d, v);
   else
-    vstore_nt<T, EPT>(base + off, i0, d, vec, v);
+    vstore_nt<T, EPT>(base + off, i0, d, v);
 }
 
 // A thread's slices of the kMaxHist register-resident history vectors:
@@ -358,7 +379,7 @@ __device__ inline void two_loop(const H &Sr, const H &Yr, const T (&rh)[kMaxHist
 // arithmetic and its order are those of two_loop.
 template <typename T, int TPB, int EPT>
 __device__ __forceinline__ void two_loop_stream(const T *Sb, const T *Yb, const T *rho, int d, int m,
-                                       int head, int cnt, bool vec, bool reg_new,
+                                       int head, int cnt, bool reg_new,
                                        const T (&sn)[EPT], const T (&yn)[EPT], T rn, T gamma,
                                        const T (&g)[EPT], T (&p)[EPT], BlockRed<TPB, T> &red) {
   const int i0 = threadIdx.x * EPT;
@@ -378,11 +399,11 @@ __device__ __forceinline__ void two_loop_stream(const T *Sb, const T *Yb, const 
     }
     const int ph = slot(j);
     if (last) {
-      vload_nt<T, EPT>(Sb + (size_t)ph * d, i0, d, vec, sv);
-      vload_nt<T, EPT>(Yb + (size_t)ph * d, i0, d, vec, yv);
+      vload_nt<T, EPT>(Sb + (size_t)ph * d, i0, d, sv);
+      vload_nt<T, EPT>(Yb + (size_t)ph * d, i0, d, yv);
     } else {
-      vload<T, EPT>(Sb + (size_t)ph * d, i0, d, vec, sv);
-      vload<T, EPT>(Yb + (size_t)ph * d, i0, d, vec, yv);
+      vload<T, EPT>(Sb + (size_t)ph * d, i0, d, sv);
+      vload<T, EPT>(Yb + (size_t)ph * d, i0, d, yv);
     }
     rv = rho[ph];
   };
@@ -470,7 +491,6 @@ __device__ __forceinline__ void lbfgs_step_one(const LbArgs<T> &a, const int64_t
   const int64_t vo = vov;
   const int64_t Lt = a.Ltot;
   const int i0 = tid * EPT;  // this thread's chunk of every vector
-  const bool vec = (d % EPT == 0) && (vo % EPT == 0) && (Lt % EPT == 0);
   T tol = a.tol;
   int max_iter = a.max_iter;
   if (a.sprob) {
@@ -514,11 +534,11 @@ __device__ __forceinline__ void lbfgs_step_one(const LbArgs<T> &a, const int64_t
     T *xt = a.X + (size_t)tr * Lt + vo;
     const T *pd = a.Pd + vo;
     T c[EPT], q[EPT];
-    vload<T, EPT>(xc, i0, d, vec, c);
-    vload<T, EPT>(pd, i0, d, vec, q);
+    vload<T, EPT>(xc, i0, d, c);
+    vload<T, EPT>(pd, i0, d, q);
 #pragma unroll
     for (int e = 0; e < EPT; ++e) c[e] = c[e] + alpha * q[e];
-    vstore<T, EPT>(xt, i0, d, vec, c);
+    vstore<T, EPT>(xt, i0, d, c);
     if (tid == 0) {
       a.alpha[s] = alpha;
       a.ls[s] = lsn;
@@ -537,12 +557,12 @@ __device__ __forceinline__ void lbfgs_step_one(const LbArgs<T> &a, const int64_t
     const T *gn = a.G + (size_t)newcur * Lt + vo;
     const T *xo = a.X + (size_t)cur * Lt + vo;
     const T *go = a.G + (size_t)cur * Lt + vo;
-    vload<T, EPT>(xn, i0, d, vec, x);
-    vload<T, EPT>(gn, i0, d, vec, gl);
+    vload<T, EPT>(xn, i0, d, x);
+    vload<T, EPT>(gn, i0, d, gl);
     if (mode == M_ACCEPT) {
       T xov[EPT], gov[EPT];
-      vload<T, EPT>(xo, i0, d, vec, xov);
-      vload<T, EPT>(go, i0, d, vec, gov);
+      vload<T, EPT>(xo, i0, d, xov);
+      vload<T, EPT>(go, i0, d, gov);
 #pragma unroll
       for (int e = 0; e < EPT; ++e) {
         sv[e] = x[e] - xov[e];
@@ -567,9 +587,9 @@ __device__ __forceinline__ void lbfgs_step_one(const LbArgs<T> &a, const int64_t
   T rh[MH], yyr[MH];
   const bool defer_oldest = (mode == M_ACCEPT && cnt == m);
   if constexpr (HREG) {
-    // packed BF16 history in whole aligned chunks: the raw words go straight
+    // packed BF16 history in whole chunks: the raw words go straight
     // to registers, every load issued before the first use
-    const bool raw = PK && vec && i0 + EPT <= d;
+    const bool raw = PK && i0 + EPT <= d;
 #pragma unroll
     for (int j = 0; j < kMaxHist; ++j) {
       rh[j] = 0;
@@ -585,14 +605,14 @@ __device__ __forceinline__ void lbfgs_step_one(const LbArgs<T> &a, const int64_t
             hload_raw_nt<EPT>((const uint16_t *)a.Yh + off, i0, Yr.w[j]);
           } else {
             T t[EPT];
-            ring_load<T, EPT, HB>(a.S, off, i0, d, vec, t);
+            ring_load<T, EPT, HB>(a.S, off, i0, d, t);
             Sr.set(j, t);
-            ring_load<T, EPT, HB>(a.Yh, off, i0, d, vec, t);
+            ring_load<T, EPT, HB>(a.Yh, off, i0, d, t);
             Yr.set(j, t);
           }
         } else {
-          ring_load<T, EPT, HB>(a.S, off, i0, d, vec, Sr.v[j]);
-          ring_load<T, EPT, HB>(a.Yh, off, i0, d, vec, Yr.v[j]);
+          ring_load<T, EPT, HB>(a.S, off, i0, d, Sr.v[j]);
+          ring_load<T, EPT, HB>(a.Yh, off, i0, d, Yr.v[j]);
         }
         rh[j] = a.rho[(size_t)s * m + ph];
         yyr[j] = a.yy[(size_t)s * m + ph];
@@ -616,8 +636,8 @@ __device__ __forceinline__ void lbfgs_step_one(const LbArgs<T> &a, const int64_t
     ++it;
     if (sy > (T)1e-10 * sqrt(ss) * sqrt(yy)) {
       // store the pair in the ring and append it to the logical history
-      ring_store<T, EPT, HB>(a.S, (size_t)m * vo + (size_t)head * d, i0, d, vec, sv);
-      ring_store<T, EPT, HB>(a.Yh, (size_t)m * vo + (size_t)head * d, i0, d, vec, yv);
+      ring_store<T, EPT, HB>(a.S, (size_t)m * vo + (size_t)head * d, i0, d, sv);
+      ring_store<T, EPT, HB>(a.Yh, (size_t)m * vo + (size_t)head * d, i0, d, yv);
       if (tid == 0) {
         a.rho[(size_t)s * m + head] = (T)1 / sy;
         a.yy[(size_t)s * m + head] = yy;
@@ -654,9 +674,9 @@ __device__ __forceinline__ void lbfgs_step_one(const LbArgs<T> &a, const int64_t
       if constexpr (HREG) {
         // pair kept out: the oldest pair (ring slot head) stays in the history
         T t[EPT];
-        ring_load<T, EPT, HB>(a.S, (size_t)m * vo + (size_t)head * d, i0, d, vec, t);
+        ring_load<T, EPT, HB>(a.S, (size_t)m * vo + (size_t)head * d, i0, d, t);
         Sr.set(0, t);
-        ring_load<T, EPT, HB>(a.Yh, (size_t)m * vo + (size_t)head * d, i0, d, vec, t);
+        ring_load<T, EPT, HB>(a.Yh, (size_t)m * vo + (size_t)head * d, i0, d, t);
         Yr.set(0, t);
         rh[0] = a.rho[(size_t)s * m + head];
         yyr[0] = a.yy[(size_t)s * m + head];
@@ -728,7 +748,7 @@ __device__ __forceinline__ void lbfgs_step_one(const LbArgs<T> &a, const int64_t
       two_loop<T, TPB, EPT>(Sr, Yr, rh, gamma, cnt, g, p, red);
     else
       two_loop_stream<T, TPB, EPT>(a.S + (size_t)m * vo, a.Yh + (size_t)m * vo,
-                                   a.rho + (size_t)s * m, d, m, head, cnt, vec, reg_new, sv, yv,
+                                   a.rho + (size_t)s * m, d, m, head, cnt, reg_new, sv, yv,
                                    r_new, gamma, g, p, red);
     T t = 0;
 #pragma unroll
@@ -756,8 +776,8 @@ __device__ __forceinline__ void lbfgs_step_one(const LbArgs<T> &a, const int64_t
   T xtv[EPT];
 #pragma unroll
   for (int e = 0; e < EPT; ++e) xtv[e] = x[e] + p[e];
-  vstore_nt<T, EPT>(pd, i0, d, vec, p);
-  vstore<T, EPT>(xt, i0, d, vec, xtv);
+  vstore_nt<T, EPT>(pd, i0, d, p);
+  vstore<T, EPT>(xt, i0, d, xtv);
   if (tid == 0) {
     a.alpha[s] = (T)1;
     a.gtp[s] = gtp;
@@ -773,7 +793,9 @@ __device__ __forceinline__ void lbfgs_step_one(const LbArgs<T> &a, const int64_t
   }
 }
 
-// Start s_base + blockIdx.x (one workgroup per start of the launch's range).
+// Start s_base + blockIdx.x: a workgroup each.  (Four one-wave starts per
+// workgroup, for d <= 256, measured the same: handing out workgroups is not what
+// a step with few active starts costs.)
 template <typename T, int TPB, int EPT, bool HREG, bool HB = false>
 __global__ __launch_bounds__(TPB) void lbfgs_step_kernel(LbArgs<T> a) {
   __shared__ T rbuf[2 * BlockRed<TPB, T>::NMAX * (TPB / 64)];
@@ -783,6 +805,40 @@ __global__ __launch_bounds__(TPB) void lbfgs_step_kernel(LbArgs<T> a) {
   if (a.count_reset && blockIdx.x == 0 && threadIdx.x == 0) *a.count_reset = 0;
   if ((int64_t)blockIdx.x < a.s_count)
     lbfgs_step_one<T, TPB, EPT, HREG, HB>(a, a.s_base + blockIdx.x, red);
+}
+
+template <typename T, int TPB, int EPT, bool HREG, bool HB>
+static void step_go(const LbArgs<T> &a, hipStream_t s) {
+  hipLaunchKernelGGL((lbfgs_step_kernel<T, TPB, EPT, HREG, HB>), dim3((unsigned)a.s_count),
+                     dim3(TPB), 0, s, a);
+}
+
+// Workgroup size and elements per thread by d; HR: history in registers.
+template <typename T, bool HR>
+static void step_by_d(const LbArgs<T> &a, int d, hipStream_t s) {
+  if (d <= 64) step_go<T, 64, 1, HR, false>(a, s);
+  else if (d <= 128) step_go<T, 64, 2, HR, false>(a, s);
+  else if (d <= 256) step_go<T, 64, 4, HR, false>(a, s);
+  else if (d <= 512) step_go<T, 128, 4, HR, false>(a, s);
+  else if (d <= 1024) step_go<T, 256, 4, HR, false>(a, s);
+  else if (d <= 2048) step_go<T, 512, 4, HR, false>(a, s);
+  else step_go<T, 1024, 4, HR, false>(a, s);
+}
+// Register-resident history for m <= kMaxHist, streamed beyond.
+template <typename T>
+static void step_launch(const LbArgs<T> &a, int d, hipStream_t s) {
+  if (a.m <= kMaxHist) step_by_d<T, true>(a, d, s);
+  else step_by_d<T, false>(a, d, s);
+}
+// FP32 starts with the BF16 history ring (register-resident, m <= kMaxHist).
+static void step_launch_hb(const LbArgs<float> &a, int d, hipStream_t s) {
+  if (d <= 64) step_go<float, 64, 1, true, true>(a, s);
+  else if (d <= 128) step_go<float, 64, 2, true, true>(a, s);
+  else if (d <= 256) step_go<float, 64, 4, true, true>(a, s);
+  else if (d <= 512) step_go<float, 64, 8, true, true>(a, s);
+  else if (d <= 1024) step_go<float, 128, 8, true, true>(a, s);
+  else if (d <= 2048) step_go<float, 256, 8, true, true>(a, s);
+  else step_go<float, 512, 8, true, true>(a, s);
 }
 
 // Two-loop direction only, for B independent histories given in logical
@@ -800,15 +856,14 @@ __global__ __launch_bounds__(TPB) void two_loop_kernel(int d, int m, const int32
     // recursion (logical order is the slot order: head = cnt mod m)
     __shared__ T rho_s[kMaxMem];
     const int i0 = tid * EPT;
-    const bool vec = (d % EPT == 0);
     T g[EPT], p[EPT], z[EPT], gamma = 1;
 #pragma unroll
     for (int e = 0; e < EPT; ++e) z[e] = 0;
-    vload<T, EPT>(G + (size_t)b * d, i0, d, vec, g);
+    vload<T, EPT>(G + (size_t)b * d, i0, d, g);
     for (int j = 0; j < cnt; ++j) {
       T sv[EPT], yv[EPT];
-      vload<T, EPT>(S + ((size_t)b * m + j) * d, i0, d, vec, sv);
-      vload<T, EPT>(Y + ((size_t)b * m + j) * d, i0, d, vec, yv);
+      vload<T, EPT>(S + ((size_t)b * m + j) * d, i0, d, sv);
+      vload<T, EPT>(Y + ((size_t)b * m + j) * d, i0, d, yv);
       T v2[2] = {0, 0};
 #pragma unroll
       for (int e = 0; e < EPT; ++e) {
@@ -821,22 +876,21 @@ __global__ __launch_bounds__(TPB) void two_loop_kernel(int d, int m, const int32
     }
     __syncthreads();
     two_loop_stream<T, TPB, EPT>(S + (size_t)b * m * d, Y + (size_t)b * m * d, rho_s, d, m,
-                                 cnt % m, cnt, vec, false, z, z, (T)0, gamma, g, p, red);
-    vstore<T, EPT>(P + (size_t)b * d, i0, d, vec, p);
+                                 cnt % m, cnt, false, z, z, (T)0, gamma, g, p, red);
+    vstore<T, EPT>(P + (size_t)b * d, i0, d, p);
     return;
   }
   HistReg<T, EPT, false> Sr, Yr;
   T rh[kMaxHist], g[EPT], p[EPT];
   T gamma = 1;
   const int i0 = tid * EPT;
-  const bool vec = (d % EPT == 0);
-  vload<T, EPT>(G + (size_t)b * d, i0, d, vec, g);
+  vload<T, EPT>(G + (size_t)b * d, i0, d, g);
 #pragma unroll
   for (int j = 0; j < kMaxHist; ++j) {
     rh[j] = 0;
     if (j < cnt) {
-      vload<T, EPT>(S + ((size_t)b * m + j) * d, i0, d, vec, Sr.v[j]);
-      vload<T, EPT>(Y + ((size_t)b * m + j) * d, i0, d, vec, Yr.v[j]);
+      vload<T, EPT>(S + ((size_t)b * m + j) * d, i0, d, Sr.v[j]);
+      vload<T, EPT>(Y + ((size_t)b * m + j) * d, i0, d, Yr.v[j]);
     } else {
       Sr.zero(j);
       Yr.zero(j);
@@ -854,7 +908,7 @@ __global__ __launch_bounds__(TPB) void two_loop_kernel(int d, int m, const int32
     }
   }
   two_loop<T, TPB, EPT>(Sr, Yr, rh, gamma, cnt, g, p, red);
-  vstore<T, EPT>(P + (size_t)b * d, i0, d, vec, p);
+  vstore<T, EPT>(P + (size_t)b * d, i0, d, p);
 }
 
 // ------------------------------------------------------------- dispatch
@@ -884,31 +938,6 @@ __global__ __launch_bounds__(TPB) void two_loop_kernel(int d, int m, const int32
   } else {                                          \
     SB_LB_CASES_H(KERNEL, T, false, __VA_ARGS__)    \
   }
-// FP32 starts with the BF16 history ring (register-resident, m <= kMaxHist).
-#define SB_LB_CASES_HB(KERNEL, ...)                                                            \
-  if (d <= 64) {                                                                               \
-    hipLaunchKernelGGL((KERNEL<float, 64, 1, true, true>), dim3((unsigned)B), dim3(64), 0, s,   \
-                       __VA_ARGS__);                                                           \
-  } else if (d <= 128) {                                                                       \
-    hipLaunchKernelGGL((KERNEL<float, 64, 2, true, true>), dim3((unsigned)B), dim3(64), 0, s,   \
-                       __VA_ARGS__);                                                           \
-  } else if (d <= 256) {                                                                       \
-    hipLaunchKernelGGL((KERNEL<float, 64, 4, true, true>), dim3((unsigned)B), dim3(64), 0, s,   \
-                       __VA_ARGS__);                                                           \
-  } else if (d <= 512) {                                                                       \
-    hipLaunchKernelGGL((KERNEL<float, 64, 8, true, true>), dim3((unsigned)B), dim3(64), 0, s,   \
-                       __VA_ARGS__);                                                           \
-  } else if (d <= 1024) {                                                                      \
-    hipLaunchKernelGGL((KERNEL<float, 128, 8, true, true>), dim3((unsigned)B), dim3(128), 0, s, \
-                       __VA_ARGS__);                                                           \
-  } else if (d <= 2048) {                                                                      \
-    hipLaunchKernelGGL((KERNEL<float, 256, 8, true, true>), dim3((unsigned)B), dim3(256), 0, s, \
-                       __VA_ARGS__);                                                           \
-  } else {                                                                                     \
-    hipLaunchKernelGGL((KERNEL<float, 512, 8, true, true>), dim3((unsigned)B), dim3(512), 0,    \
-                       s, __VA_ARGS__);                                                        \
-  }
-
 static int check_d(int d, int m) {
   if (d < 1 || d > 4096) {
     set_error("L-BFGS supports 1 <= d <= 4096 (got %d)", d);
@@ -968,35 +997,9 @@ static LbArgs<T> make_args(const LbfgsBuffers &b, int max_iter, double tol) {
   return a;
 }
 
-// One workgroup per start of the launch: the dispatcher hands freed slots
-// to the next start, which balances starts of uneven cost (a fixed grid
-// striding over starts measured slower: its last round runs part-empty).
-static int64_t step_grid(int64_t count) { return count; }
-
-int launch_lbfgs_step(const LbfgsBuffers &b, int max_iter, double grad_tol, hipStream_t s) {
-  int st = check_d(b.d, b.m);
-  if (!st) st = check_hist(b);
-  if (st) return st;
-  const int d = b.d;
-  const int64_t B = step_grid(b.B);
-  if (B <= 0) return SB_OK;
-  if (b.dtype == DT_F64) {
-    LbArgs<double> a = make_args<double>(b, max_iter, grad_tol);
-    a.count_reset = b.count;
-    SB_LB_CASES(lbfgs_step_kernel, double, b.m, a);
-  } else if (b.hist_bf16) {
-    LbArgs<float> a = make_args<float>(b, max_iter, grad_tol);
-    a.count_reset = b.count;
-    SB_LB_CASES_HB(lbfgs_step_kernel, a);
-  } else {
-    LbArgs<float> a = make_args<float>(b, max_iter, grad_tol);
-    a.count_reset = b.count;
-    SB_LB_CASES(lbfgs_step_kernel, float, b.m, a);
-  }
-  SB_LAUNCH_CHECK();
-  return SB_OK;
-}
-
+// Every start of the launch has its own workgroup: the dispatcher hands freed
+// slots to the next start, which balances starts of uneven cost (a fixed
+// grid striding over starts measured slower: its last round runs part-empty).
 int launch_lbfgs_step_range(const LbfgsBuffers &b, int64_t s_begin, int64_t count, int d_class,
                             double grad_tol, int max_iter, hipStream_t s) {
   int st = check_d(d_class, b.m);
@@ -1008,26 +1011,25 @@ int launch_lbfgs_step_range(const LbfgsBuffers &b, int64_t s_begin, int64_t coun
               (long long)(s_begin + count), (long long)b.B);
     return SB_E_INVAL;
   }
-  const int d = d_class;
-  const int64_t B = step_grid(count);
-  if (b.dtype == DT_F64) {
-    LbArgs<double> a = make_args<double>(b, max_iter, grad_tol);
+  auto run = [&](auto a, auto launch) {
     a.s_base = s_begin;
     a.s_count = count;
-    SB_LB_CASES(lbfgs_step_kernel, double, b.m, a);
-  } else if (b.hist_bf16) {
-    LbArgs<float> a = make_args<float>(b, max_iter, grad_tol);
-    a.s_base = s_begin;
-    a.s_count = count;
-    SB_LB_CASES_HB(lbfgs_step_kernel, a);
-  } else {
-    LbArgs<float> a = make_args<float>(b, max_iter, grad_tol);
-    a.s_base = s_begin;
-    a.s_count = count;
-    SB_LB_CASES(lbfgs_step_kernel, float, b.m, a);
-  }
+    // (the uniform batch resets its compaction count; the grouped one has its own)
+    if (!b.voff) a.count_reset = b.count;
+    launch(a, d_class, s);
+  };
+  if (b.dtype == DT_F64)
+    run(make_args<double>(b, max_iter, grad_tol), step_launch<double>);
+  else if (b.hist_bf16)
+    run(make_args<float>(b, max_iter, grad_tol), step_launch_hb);
+  else
+    run(make_args<float>(b, max_iter, grad_tol), step_launch<float>);
   SB_LAUNCH_CHECK();
   return SB_OK;
+}
+
+int launch_lbfgs_step(const LbfgsBuffers &b, int max_iter, double grad_tol, hipStream_t s) {
+  return launch_lbfgs_step_range(b, 0, b.B, b.d, grad_tol, max_iter, s);
 }
 
 int launch_two_loop(int64_t B, int d, int m, const int32_t *cnt, const void *S, const void *Y,

@@ -844,3 +844,27 @@ def test_quadform_edges(L, d, tile, monkeypatch):
             qk = q.qpart.reshape(-1)[:B * K * nt].reshape(B, K, nt)[:, k].double().sum(1).cpu()
             qmag = (delta.abs() * mag).sum(1)
             assert bool(((qk - (delta * Y).sum(1)).abs() <= 4 * (d + 1) * u * qmag).all())
+
+
+@pytest.mark.parametrize("d", [3, 67, 129, 255, 509, 1021])
+def test_lbfgs_rows_of_any_alignment(L, d):
+    """L-BFGS from starts whose vectors begin at any element and end inside a thread's chunk
+    (odd d), in FP64, FP32 and FP32 with the BF16 history ring: every start ends at the mode of
+    an anisotropic Gaussian as closely as its gradient test asks (|P^-1 grad| <= |grad| /
+    lambda_min(P), lambda_min(P) >= 1; FP32: the rounding of the point itself, 2^-24 |mu|
+    cond(P) <= 1e-3)."""
+    rng = np.random.Generator(np.random.PCG64(700 + d))
+    P, _ = synth.random_precision(rng, d, 0.1, 1.0)
+    mu = rng.uniform(-2, 2, (1, d))
+    prob = synth.Problem(0, 0, d, 1, np.zeros(1), mu, P[None], 0.0, 0.0, -9 * np.ones(d),
+                         9 * np.ones(d), np.zeros(1))
+    m = L.DeviceModel(prob, low_precision=True)
+    X0 = dev(mu + rng.uniform(-3, 3, (13, d)))
+    r = L.sb_lbfgs_dev(m, X0, m=8, grad_tol=1e-8)
+    assert int(r["status"].max()) == 1
+    assert np.max(np.abs(r["x"].cpu().numpy() - mu)) <= 1e-8 * np.sqrt(d)
+    for hb in (False, True):
+        r = L.sb_lbfgs_dev(m, X0.float(), m=8, grad_tol=2e-4, max_iter=400, hist_bf16=hb)
+        assert np.max(np.abs(r["x"].cpu().numpy() - mu)) <= 1e-3 * np.sqrt(d)
+        # (a ring read or written at wrong elements would not converge superlinearly)
+        assert int(r["iters"].max()) <= 100
