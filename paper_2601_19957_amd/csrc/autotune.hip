@@ -1,12 +1,12 @@
 // Tile-shape autotuner for the quadratic-form GEMM.
 //
 // The first time a shape class (dtype, d, K, M rounded up to a power of two)
-// is seen, each candidate tile (BM x BN x k-tile: five for FP64, four for FP32,
-// seven with their LDS stages for the BF16 and split contractions) is timed
-// with HIP events, one warm-up and five timed launches, and the fastest is
-// cached for the process.  The launches run on the caller's probe (its operands
-// and scratch outputs, which the real launch overwrites).  Timing synchronises
-// the stream, so a stream under graph capture gets the heuristic choice (not
+// is seen, each candidate tile (BM x BN x k-tile: four for FP64 and for FP32,
+// seven with their LDS stages for the BF16 and split contractions) is timed with
+// HIP events, one warm-up and five timed launches, and the fastest is cached
+// for the process.  The launches run on the caller's probe (its operands and
+// scratch outputs, which the real launch overwrites).  Timing synchronises the
+// stream, so a stream under graph capture gets the heuristic choice (not
 // cached).  SB_TILE=BMxBN[xBK[xSTAGES]] forces a shape; SB_AUTOTUNE=0 uses the
 // heuristic without timing.
 #include <algorithm>
@@ -61,15 +61,17 @@ bool time_launches(int dtype, const Model &m, const ASrc &a, QuadOut o, int64_t 
   // FP32 at 16384 x 1024, K = 8: 64 x 128 x 16 2.20 ms, 64 x 128 x 32 2.25, 128 x
   // 64 x 32 2.27, 64 x 64 x 32 2.48; at 8192 x 256: 16.9 us for 64 x 64 x 32, 17.2
   // for 64 x 128 x 32.
-  const int cands[5][4] = {{64, 64, 32, 1}, {64, 128, 16, 1}, {128, 128, 16, 1},
-                           {64, 128, 32, 1}, {32, 64, 32, 1}};
+  const int cands_f64[4][4] = {{32, 64, 32, 1}, {64, 64, 32, 1}, {64, 128, 16, 1},
+                               {128, 128, 16, 1}};
+  const int cands_f32[4][4] = {{64, 64, 32, 1}, {64, 128, 16, 1}, {64, 128, 32, 1},
+                               {128, 128, 16, 1}};
   const int cands_bf[7][4] = {{128, 128, 32, 1}, {128, 128, 64, 1}, {256, 128, 32, 1},
                               {128, 256, 32, 1}, {256, 256, 32, 1}, {128, 128, 32, 2},
                               {256, 256, 32, 2}};
-  const int nc = bf ? 7 : (dtype == DT_F64 ? 5 : 4);
+  const int nc = bf ? 7 : 4;
   for (int c = 0; c < nc && ok; ++c) {
     TileCfg t;
-    const int *cd = bf ? cands_bf[c] : cands[c];
+    const int *cd = bf ? cands_bf[c] : (dtype == DT_F64 ? cands_f64[c] : cands_f32[c]);
     t.bm = cd[0];
     t.bn = cd[1];
     t.bk = cd[2];

@@ -49,7 +49,7 @@ __host__ __device__ inline float bf16_to_f32(bf16_t h) {
 // 99.2 ms, d = 64, K = 4 in FP64 3.91 -> 3.70 ms.
 template <int CTRL>
 __device__ inline int dpp_mov(int v) {
-  return __builtin_amdgcn_update_dpp(v, v, CTRL, 0xf, 0xf, false);
+  return __builtin_amdgcn_mov_dpp(v, CTRL, 0xf, 0xf, true);
 }
 constexpr int kDppRor8 = 0x128, kDppRor4 = 0x124, kDppXor2 = 0x4e, kDppXor1 = 0xb1, kDppHalfMirror = 0x141;
 template <int CTRL>
@@ -178,6 +178,16 @@ __device__ inline T block_max(T v, T *red) {
     for (int i = 1; i < TPB / 64; ++i) t = fmax(t, red[i]);
     return t;
   }
+}
+
+// A value equal in all lanes of the wave, held as such: branches on it and the
+// addresses formed from it are scalar.
+__device__ inline int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ inline bool uniform(bool v) { return __builtin_amdgcn_readfirstlane((int)v) != 0; }
+__device__ inline int64_t uniform(int64_t v) {
+  const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(uint64_t)v);
+  const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)((uint64_t)v >> 32));
+  return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }

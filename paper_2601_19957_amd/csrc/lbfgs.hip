@@ -386,7 +386,8 @@ __device__ __forceinline__ void two_loop_stream(const T *Sb, const T *Yb, const 
   T q[EPT], al[kMaxMem];
 #pragma unroll
   for (int e = 0; e < EPT; ++e) q[e] = g[e];
-  auto slot = [&](int j) { return (head - cnt + j + 2 * m) % m; };
+  const int slot0 = head >= cnt ? head - cnt : head - cnt + m;
+  auto slot = [&](int j) { return slot0 + j < m ? slot0 + j : slot0 + j - m; };
   auto fetch = [&](int j, T (&sv)[EPT], T (&yv)[EPT], T &rv, bool last) {
     if (reg_new && j == cnt - 1) {
 #pragma unroll
@@ -472,16 +473,19 @@ __device__ __forceinline__ void lbfgs_step_one(const LbArgs<T> &a, const int64_t
   const int tid = threadIdx.x;
   const int64_t B = a.B;
   // every per-start scalar is read before the first decision, so the reads
-  // share one memory round trip (all are in bounds for any start)
-  const int status = a.status[s];
-  int cur = a.cur[s];
-  const int phase = a.phase[s];
-  int cnt = a.cnt[s], head = a.head[s], it = a.iters[s];
+  // share one memory round trip (all are in bounds for any start); what steers
+  // the step is then the same in every lane, for the compiler too
+  const int status_v = a.status[s], cur_v = a.cur[s], phase_v = a.phase[s], cnt_v = a.cnt[s],
+            head_v = a.head[s], it_v = a.iters[s];
   const double f0 = a.F[s], f1 = a.F[(size_t)B + s];
   const T alpha_s = a.alpha[s], gtp_s = a.gtp[s];
-  const int ls_s = a.ls[s];
-  const int dv = a.vdim ? a.vdim[s] : a.d;
-  const int64_t vov = a.voff ? a.voff[s] : (int64_t)s * a.d;
+  const int ls_v = a.ls[s];
+  const int dv_v = a.vdim ? a.vdim[s] : a.d;
+  const int64_t vo_v = a.voff ? a.voff[s] : (int64_t)s * a.d;
+  const int status = uniform(status_v), phase = uniform(phase_v), ls_s = uniform(ls_v);
+  int cur = uniform(cur_v), cnt = uniform(cnt_v), head = uniform(head_v), it = uniform(it_v);
+  const int dv = uniform(dv_v);
+  const int64_t vov = uniform(vo_v);
   if (status != ST_ACTIVE) {
     if (tid == 0) a.active[s] = 0;
     return;
@@ -494,9 +498,9 @@ __device__ __forceinline__ void lbfgs_step_one(const LbArgs<T> &a, const int64_t
   T tol = a.tol;
   int max_iter = a.max_iter;
   if (a.sprob) {
-    const int p = a.sprob[s];
+    const int p = uniform(a.sprob[s]);
     tol = (T)a.ptol[p];
-    max_iter = a.pmaxit[p];
+    max_iter = uniform(a.pmaxit[p]);
   }
   const double lcur = cur ? f1 : f0;
 
@@ -510,7 +514,7 @@ __device__ __forceinline__ void lbfgs_step_one(const LbArgs<T> &a, const int64_t
     alpha = alpha_s;
     const double gtp_old = (double)gtp_s;
     const double fc = -lcur, ft = -lt;
-    if (isfinite(ft) && ft <= fc + 1e-4 * (double)alpha * gtp_old) {
+    if (uniform(isfinite(ft) && ft <= fc + 1e-4 * (double)alpha * gtp_old)) {
       mode = M_ACCEPT;
     } else {
       lsn = ls_s + 1;
@@ -586,6 +590,9 @@ __device__ __forceinline__ void lbfgs_step_one(const LbArgs<T> &a, const int64_t
   HistReg<T, EPT, PK> Sr, Yr;
   T rh[MH], yyr[MH];
   const bool defer_oldest = (mode == M_ACCEPT && cnt == m);
+  const int slot0 = head >= cnt ? head - cnt : head - cnt + m;  // ring slot of the oldest pair
+  const size_t hist0 = (size_t)m * vo;
+  const T *rho_s = a.rho + (size_t)s * m, *yy_s = a.yy + (size_t)s * m;
   if constexpr (HREG) {
     // packed BF16 history in whole chunks: the raw words go straight
     // to registers, every load issued before the first use
@@ -597,8 +604,8 @@ __device__ __forceinline__ void lbfgs_step_one(const LbArgs<T> &a, const int64_t
       Sr.zero(j);
       Yr.zero(j);
       if (mode == M_ACCEPT && j < cnt && !(j == 0 && defer_oldest)) {
-        const int ph = (head - cnt + j + 2 * m) % m;
-        const size_t off = (size_t)m * vo + (size_t)ph * d;
+        const int ph = slot0 + j < m ? slot0 + j : slot0 + j - m;
+        const size_t off = hist0 + (uint32_t)(ph * d);  // (m, d <= 32, 4096)
         if constexpr (PK) {
           if (raw) {
             hload_raw_nt<EPT>((const uint16_t *)a.S + off, i0, Sr.w[j]);
@@ -614,8 +621,8 @@ __device__ __forceinline__ void lbfgs_step_one(const LbArgs<T> &a, const int64_t
           ring_load<T, EPT, HB>(a.S, off, i0, d, Sr.v[j]);
           ring_load<T, EPT, HB>(a.Yh, off, i0, d, Yr.v[j]);
         }
-        rh[j] = a.rho[(size_t)s * m + ph];
-        yyr[j] = a.yy[(size_t)s * m + ph];
+        rh[j] = rho_s[ph];
+        yyr[j] = yy_s[ph];
       }
     }
   }
@@ -634,7 +641,7 @@ __device__ __forceinline__ void lbfgs_step_one(const LbArgs<T> &a, const int64_t
     const T sy = v3[0], ss = v3[1], yy = v3[2];
     cur = newcur;
     ++it;
-    if (sy > (T)1e-10 * sqrt(ss) * sqrt(yy)) {
+    if (uniform(sy > (T)1e-10 * sqrt(ss) * sqrt(yy))) {
       // store the pair in the ring and append it to the logical history
       ring_store<T, EPT, HB>(a.S, (size_t)m * vo + (size_t)head * d, i0, d, sv);
       ring_store<T, EPT, HB>(a.Yh, (size_t)m * vo + (size_t)head * d, i0, d, yv);
@@ -668,7 +675,7 @@ __device__ __forceinline__ void lbfgs_step_one(const LbArgs<T> &a, const int64_t
         r_new = (T)1 / sy;
         yy_new = yy;
       }
-      head = (head + 1) % m;
+      head = head + 1 < m ? head + 1 : 0;
       cnt = full ? m : cnt + 1;
     } else if (defer_oldest) {
       if constexpr (HREG) {
@@ -699,9 +706,9 @@ __device__ __forceinline__ void lbfgs_step_one(const LbArgs<T> &a, const int64_t
     if (v2[1] != (T)0) gn = (T)NAN;
   }
   int newst = ST_ACTIVE;
-  if (mode == M_INIT && !(isfinite(lcur) && isfinite(gn)))
+  if (mode == M_INIT && uniform(!(isfinite(lcur) && isfinite(gn))))
     newst = ST_DEAD;
-  else if (gn <= tol)
+  else if (uniform(gn <= tol))
     newst = ST_CONVERGED;
   else if (it >= max_iter)
     newst = ST_MAXITER;
@@ -754,7 +761,7 @@ __device__ __forceinline__ void lbfgs_step_one(const LbArgs<T> &a, const int64_t
 #pragma unroll
     for (int e = 0; e < EPT; ++e) t += g[e] * p[e];
     gtp = red.sum(t);
-    if (!(gtp < (T)0)) {
+    if (uniform(!(gtp < (T)0))) {
       sd = true;
       cnt = 0;
       head = 0;
