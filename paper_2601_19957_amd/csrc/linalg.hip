@@ -3,10 +3,21 @@
 // H = L L^T (the whitening factor of the paper's appendix "Coordinate
 // Whitening"); log det H = 2 sum_i log L_ii.  A failed pivot means H is not
 // positive definite, i.e. the candidate is not a maximum (saddle filter of
-// GreenDragon, generalised).  Blocked right-looking factorisation with 64-wide
-// panels: diagonal block in registers, triangular solve of the panel below
-// it, symmetric rank-64 update of the trailing lower triangle.  One launch
-// per stage covers every matrix of the batch.
+// GreenDragon, generalised).
+//
+// Blocked right-looking factorisation with 64-wide panels, one launch per panel
+// for every matrix of the batch, of one size or of their own.  What bounds a
+// factorisation of few matrices is the chain of its panels, so a launch does all
+// of a panel at once: the workgroup of each trailing tile (I, J) solves the
+// panel rows of I and J itself (L's 64 x 64 block by 16 x 16 blocks, their
+// inverses and the products on the FP64 matrix cores) and subtracts X_I X_J^T;
+// the workgroup of the first trailing tile goes on to factor it, the next
+// panel's diagonal block.  Other workgroups still read the unsolved panel rows,
+// so the solved ones go to the mirrored block of the upper triangle first and
+// are moved by the next launch.  n = 1024, 8 matrices: 0.66 ms (27 us a panel
+// where few tiles are left, of which the pivots take 16); three launches
+// per panel (diagonal block, panel solve, trailing update, each element updated
+// one column at a time) took 1.08 ms.
 #include <algorithm>
 
 #include "internal.h"
@@ -15,297 +26,378 @@ namespace sb {
 
 constexpr int NB = 64;
 
-// The 64 x 64 blocks below are held as a 16 x 16 grid of 4 x 4 register
-// tiles, thread t owning tile (t / 16, t % 16), and processed four columns
-// (one tile column) at a time.  Every element receives the subtractions of
-// the columns before it one at a time in column order and is scaled by the
-// reciprocal of its pivot last (one division per pivot instead of one per
-// element: the serial pivot chain is the kernels' critical path).
+namespace {
 
-// Factor the diagonal block [j0, j0+nb)^2 of every matrix.  Step s: the
-// owner of diagonal tile s factors it (left-looking within the tile), the
-// tiles below it solve against it, and the trailing tiles take the rank-4
-// update.  Rows and columns past nb are padded with the identity.
-__global__ __launch_bounds__(256) void chol_diag_kernel(int n, int j0, double *L,
-                                                        int32_t *info) {
-  const int c = blockIdx.x;
-  if (info[c] != 0) return;
-  double *A = L + (size_t)c * n * n;
-  const int nb = min(NB, n - j0);
-  const int tid = threadIdx.x, ti = tid >> 4, tk = tid & 15;
-  const bool low = ti >= tk;
-  __shared__ double Dg[2][4][4];   // factor of the step's diagonal tile
-  __shared__ double Dr[2][4];      // reciprocals of its diagonal
-  __shared__ double Pn[2][NB][4];  // the step's solved tile column
-  __shared__ int fail;
-  double a[4][4];
-#pragma unroll
-  for (int u = 0; u < 4; ++u)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int i = 4 * ti + u, k = 4 * tk + v;
-      a[u][v] = (i < nb && k < nb) ? (k <= i ? A[(size_t)(j0 + i) * n + j0 + k] : 0.0)
-                                   : (i == k ? 1.0 : 0.0);
-    }
-  if (tid == 0) fail = 0;
-  __syncthreads();
-  for (int s = 0; s < NB / 4; ++s) {
-    const int b = s & 1;
-    if (ti == s && tk == s) {
-      int f = 0;
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        double p = a[v][v];
-#pragma unroll
-        for (int w = 0; w < v; ++w) p -= a[v][w] * a[v][w];
-        if (!(p > 0.0) && f == 0) f = 4 * s + v + 1;
-        const double d = sqrt(p), r = 1.0 / d;
-        a[v][v] = d;
-        Dr[b][v] = r;
-#pragma unroll
-        for (int u = v + 1; u < 4; ++u) {
-          double t = a[u][v];
-#pragma unroll
-          for (int w = 0; w < v; ++w) t -= a[u][w] * a[v][w];
-          a[u][v] = t * r;
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) Dg[b][u][v] = (v <= u) ? a[u][v] : 0.0;
-      if (f) fail = f;
-    }
-    __syncthreads();
-    if (fail) break;
-    if (tk == s && ti > s) {
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          double t = a[u][v];
-#pragma unroll
-          for (int w = 0; w < v; ++w) t -= a[u][w] * Dg[b][v][w];
-          a[u][v] = t * Dr[b][v];
-          Pn[b][4 * ti + u][v] = a[u][v];
-        }
-    }
-    __syncthreads();
-    // Pn[b] and Dg[b] are next written at step s + 2, after every thread
-    // has passed the first barrier of step s + 1
-    if (low && tk > s) {
-      double pi[4][4], pk[4][4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int w = 0; w < 4; ++w) {
-          pi[u][w] = Pn[b][4 * ti + u][w];
-          pk[u][w] = Pn[b][4 * tk + u][w];
-        }
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
-#pragma unroll
-          for (int w = 0; w < 4; ++w) a[u][v] -= pi[u][w] * pk[v][w];
-    }
+typedef double d4v __attribute__((ext_vector_type(4)));
+
+// The matrices of a batch: all n x n, one after another, or (nv) of size nv[c]
+// at offset off[c], row-major with their size as leading dimension.
+struct CholBatch {
+  int n;
+  const int32_t *nv;
+  const int64_t *off;
+  const double *A;  // first launch: the input (may be L)
+  double *L;
+  int32_t *info;
+};
+__device__ inline int chol_n(const CholBatch &b, int c) { return b.nv ? b.nv[c] : b.n; }
+__device__ inline size_t chol_off(const CholBatch &b, int c) {
+  return b.nv ? (size_t)b.off[c] : (size_t)c * b.n * b.n;
+}
+
+// 64 x 64 tiles in LDS: rows of 68 values, so that the 16 rows x 4 columns of
+// an MFMA operand touch every bank evenly.
+constexpr int LD = 68;
+constexpr int LDD = 20;  // 16 x 16 inverses
+
+__device__ inline d4v mfma(double a, double b, d4v c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+// LDS written by other lanes of this wave is visible after this
+__device__ inline void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+__device__ inline double lane_value(double v, int l) {  // lane l's value (l uniform)
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
+                          __builtin_amdgcn_readlane(__double2loint(v), l));
+}
+
+// Column j of sub-block b by LDS and the library's root and division, a row per
+// lane: for pivots that are not positive or near the ends of the exponent range.
+__device__ __noinline__ int factor_columns_lds(double *T, int b) {
+  const int lane = threadIdx.x;
+  for (int j = 16 * b; j < 16 * b + 16; ++j) {
+    const double p = T[j * LD + j];
+    if (!uniform(p > 0.0)) return j + 1;
+    const double d = sqrt(p), r = 1.0 / d;
+    wave_lds_sync();
+    if (lane >= j) T[lane * LD + j] = lane == j ? d : T[lane * LD + j] * r;
+    wave_lds_sync();
+    const double l = T[lane * LD + j];
+    for (int k = j + 1; k < 16 * b + 16; ++k)
+      if (lane >= k) T[lane * LD + k] -= l * T[k * LD + j];
+    wave_lds_sync();
   }
-  if (fail) {
-    if (tid == 0) info[c] = j0 + fail;
+  return 0;
+}
+
+// Factors the 64 x 64 block in T (lower triangle, rows from nb on the identity)
+// in place, all four waves; returns 0 or the 1-based column of the first pivot
+// that is not positive (the same in every thread).  Sixteen columns at a time:
+// their update from the columns before on the matrix cores, then one wave with a
+// row per lane and the 16 values in registers, so that the chain of pivots, which
+// is what bounds a factorisation, needs no barrier.  A pivot's root comes from
+// v_rsq_f64 and two Newton steps: r += r (1 - p r^2) / 2, then d = p r corrected by
+// (p - d^2) r / 2.
+__device__ int factor_block(double *T, int nb, int *fail_s) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int lr = lane >> 4, lc = lane & 15;
+  if (tid == 0) *fail_s = 0;
+  for (int b = 0; 16 * b < nb; ++b) {
+    if (b > 0 && wave >= b) {
+      d4v acc = {0.0, 0.0, 0.0, 0.0};
+      for (int kk = 0; kk < 16 * b; kk += 4)
+        acc = mfma(T[(16 * wave + lc) * LD + kk + lr], T[(16 * b + lc) * LD + kk + lr], acc);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) T[(16 * wave + lr + 4 * v) * LD + 16 * b + lc] -= acc[v];
+    }
+    __syncthreads();
+    if (wave == 0) {
+      double a[16];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) a[k] = T[lane * LD + 16 * b + k];
+      bool odd = false;
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        const double p = lane_value(a[j], 16 * b + j);
+        odd |= !(p > 0x1p-900 && p < 0x1p900);
+        double r = __builtin_amdgcn_rsq(p);
+        r = fma(0.5 * r, fma(-p * r, r, 1.0), r);
+        r = fma(0.5 * r, fma(-p * r, r, 1.0), r);
+        const double l = a[j] * r;
+#pragma unroll
+        for (int k = j + 1; k < 16; ++k) a[k] = fma(-l, lane_value(l, 16 * b + k), a[k]);
+        const double d = p * r;
+        a[j] = lane == 16 * b + j ? fma(0.5 * r, fma(-d, d, p), d) : l;
+      }
+      int f = 0;
+      if (uniform(odd)) {
+        f = factor_columns_lds(T, b);
+      } else if (lane >= 16 * b) {
+#pragma unroll
+        for (int k = 0; k < 16; ++k) T[lane * LD + 16 * b + k] = a[k];
+      }
+      if (f && lane == 0) *fail_s = f;
+    }
+    __syncthreads();
+    if (*fail_s) break;
+  }
+  return *fail_s;
+}
+
+// Factor in T (its first nb rows) to the matrix, zeros above the diagonal.
+__device__ void put_block(const double *T, double *A, int n, int j0, int nb) {
+  for (int e = threadIdx.x; e < NB * NB; e += 256) {
+    const int i = e >> 6, k = e & 63;
+    if (i < nb && k < nb) A[(size_t)(j0 + i) * n + j0 + k] = k <= i ? T[i * LD + k] : 0.0;
+  }
+}
+
+// First launch: workgroup 0 of a matrix factors its first diagonal block, the
+// others bring the rest of the lower triangle over and clear the upper one.
+__global__ __launch_bounds__(256) void chol_first_kernel(CholBatch g) {
+  __shared__ __attribute__((aligned(16))) double T[NB * LD];
+  __shared__ int fail_s;
+  const int c = blockIdx.x, n = chol_n(g, c);
+  const size_t base = chol_off(g, c);
+  const double *A = g.A + base;
+  double *L = g.L + base;
+  if (blockIdx.y > 0) {
+    const int64_t total = (int64_t)n * n;
+    for (int64_t e = (int64_t)(blockIdx.y - 1) * 256 + threadIdx.x; e < total;
+         e += (int64_t)(gridDim.y - 1) * 256) {
+      const int i = (int)(e / n), k = (int)(e - (int64_t)i * n);
+      if (i < NB && k < NB) continue;
+      if (k > i)
+        L[e] = 0.0;
+      else if (A != L)
+        L[e] = A[e];
+    }
     return;
   }
-#pragma unroll
-  for (int u = 0; u < 4; ++u)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int i = 4 * ti + u, k = 4 * tk + v;
-      if (i < nb && k < nb) A[(size_t)(j0 + i) * n + j0 + k] = (k <= i) ? a[u][v] : 0.0;
-    }
-}
-
-// Rows i >= j0+nb: L[i][j0:j0+nb] = A[i][j0:j0+nb] L_jj^{-T}, 64 rows per
-// workgroup.  Step s: the threads of tile column s finish their tiles by
-// substitution against diagonal tile s, then the tiles to the right
-// subtract their products with L_jj's tile row.
-__global__ __launch_bounds__(256) void chol_trsm_kernel(int n, int j0, double *L,
-                                                        const int32_t *info) {
-  const int c = blockIdx.y;
-  if (info[c] != 0) return;
-  double *A = L + (size_t)c * n * n;
-  const int nb = min(NB, n - j0);
-  const int rb = j0 + nb + blockIdx.x * 64;
-  const int tid = threadIdx.x, ti = tid >> 4, tk = tid & 15;
-  __shared__ double D[NB][NB + 1];  // L_jj, identity-padded past nb
-  __shared__ double Rd[NB];         // reciprocals of its diagonal
-  __shared__ double Xc[2][64][4];   // the step's solved tile column
-  {
-    // every load issued before the first LDS store
-    const int k = tid & 63;
-    double dv[16];
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      const int i = (tid >> 6) + 4 * q;
-      dv[q] = (i < nb && k < nb) ? (k <= i ? A[(size_t)(j0 + i) * n + j0 + k] : 0.0)
-                                 : (i == k ? 1.0 : 0.0);
-    }
-#pragma unroll
-    for (int q = 0; q < 16; ++q) D[(tid >> 6) + 4 * q][k] = dv[q];
+  const int nb = min(NB, n);
+  for (int e = threadIdx.x; e < NB * NB; e += 256) {
+    const int i = e >> 6, k = e & 63;
+    T[i * LD + k] = (i < nb && k < nb) ? (k <= i ? A[(size_t)i * n + k] : 0.0)
+                                       : (i == k ? 1.0 : 0.0);
   }
-  if (tid < NB) Rd[tid] = tid < nb ? 1.0 / A[(size_t)(j0 + tid) * n + j0 + tid] : 1.0;
-  double a[4][4];
-#pragma unroll
-  for (int u = 0; u < 4; ++u)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int i = rb + 4 * ti + u, k = 4 * tk + v;
-      a[u][v] = (i < n && k < nb) ? A[(size_t)i * n + j0 + k] : 0.0;
-    }
   __syncthreads();
-  for (int s = 0; s < NB / 4; ++s) {
-    const int b = s & 1;
-    if (tk == s) {
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          double t = a[u][v];
-#pragma unroll
-          for (int w = 0; w < v; ++w) t -= a[u][w] * D[4 * s + v][4 * s + w];
-          a[u][v] = t * Rd[4 * s + v];
-          Xc[b][4 * ti + u][v] = a[u][v];
-        }
+  const int f = factor_block(T, nb, &fail_s);
+  if (threadIdx.x == 0) g.info[c] = f;
+  if (f)
+    for (int e = threadIdx.x; e < NB * NB; e += 256) {  // (not factored: the input's triangle)
+      const int i = e >> 6, k = e & 63;
+      if (i < nb && k < nb) L[(size_t)i * n + k] = k <= i ? A[(size_t)i * n + k] : 0.0;
     }
-    __syncthreads();
-    // Xc[b] is next written at step s + 2, after this step's readers have
-    // passed the barrier of step s + 1
-    if (tk > s) {
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
-#pragma unroll
-          for (int w = 0; w < 4; ++w) a[u][v] -= Xc[b][4 * ti + u][w] * D[4 * tk + v][4 * s + w];
-    }
-  }
-#pragma unroll
-  for (int u = 0; u < 4; ++u)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int i = rb + 4 * ti + u, k = 4 * tk + v;
-      if (i < n && k < nb) A[(size_t)i * n + j0 + k] = a[u][v];
-    }
+  else
+    put_block(T, L, n, 0, nb);
 }
 
-// Trailing update A[i][k] -= sum_c L[i][j0+c] L[k][j0+c] for r0 <= k <= i < n,
-// 64x64 tiles of the lower triangle, 4x4 outputs per thread.
-__global__ __launch_bounds__(256) void chol_syrk_kernel(int n, int j0, double *L,
-                                                        const int32_t *info) {
-  const int c = blockIdx.y;
-  if (info[c] != 0) return;
-  double *A = L + (size_t)c * n * n;
-  const int nb = min(NB, n - j0);
-  const int r0 = j0 + nb;
+// Panel p.  Workgroups below `gt` (the tile count of the largest matrix) take a
+// trailing tile each, the others move the solved rows of panel p - 1 into place.
+__global__ __launch_bounds__(256, 1) void chol_panel_kernel(CholBatch g, int p, int gt) {
+  __shared__ __attribute__((aligned(16))) double Ls[NB * LD], XI[NB * LD], XJ[NB * LD];
+  __shared__ double Di[4 * 16 * LDD];  // inverses of L_jj's diagonal 16 x 16 blocks
+  __shared__ int fail_s;
+  const int c = blockIdx.y, n = chol_n(g, c), nblk = (n + NB - 1) / NB;
+  double *A = g.L + chol_off(g, c);
+  // A failed pivot stops its matrix at block q: panels before q are solved.
+  // (Formed so that a failure noted while this launch runs, in block p + 1,
+  // stops none of its workgroups.)
+  const int inf = g.info[c], q = inf ? (inf - 1) / NB : nblk;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if ((int)blockIdx.x >= gt) {
+    const int I = p + (int)blockIdx.x - gt, pp = p - 1;
+    if (pp < 0 || I >= nblk || pp >= q) return;
+    const int i0 = I * NB, j0 = pp * NB, nr = min(NB, n - i0);
+    // block (pp, I) of the upper triangle holds X_I transposed
+    double v[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      const int r = wave + 4 * u;
+      v[u] = lane < nr ? A[(size_t)(j0 + r) * n + i0 + lane] : 0.0;
+    }
+#pragma unroll
+    for (int u = 0; u < 16; ++u) XI[lane * LD + wave + 4 * u] = v[u];
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      const int r = wave + 4 * u;
+      if (r < nr) A[(size_t)(i0 + r) * n + j0 + lane] = XI[r * LD + lane];
+      if (lane < nr) A[(size_t)(j0 + r) * n + i0 + lane] = 0.0;
+    }
+    return;
+  }
+  const int T = nblk - 1 - p, t = blockIdx.x;
+  if (T <= 0 || t >= T * (T + 1) / 2 || p >= q) return;
   // tile index -> (I, J) with I >= J
-  const int t = blockIdx.x;
-  int I = (int)((sqrt(8.0 * t + 1.0) - 1.0) * 0.5);
+  int I = (int)((sqrtf(8.0f * (float)t + 1.0f) - 1.0f) * 0.5f);
   while ((I + 1) * (I + 2) / 2 <= t) ++I;
   while (I * (I + 1) / 2 > t) --I;
   const int J = t - I * (I + 1) / 2;
-  const int i0 = r0 + I * 64, k0 = r0 + J * 64;
-  __shared__ double LI[64][NB + 1];
-  __shared__ double LJ[64][NB + 1];
-  const int tid = threadIdx.x;
-  const int ti = (tid >> 4) * 4, tk = (tid & 15) * 4;
-  // this thread's outputs, fetched with the panels (their loads overlap)
-  double old[4][4];
+  const int j0 = p * NB, i0 = j0 + NB + I * NB, k0 = j0 + NB + J * NB;
+  const int lr = lane >> 4, lc = lane & 15;
+  const int wm = wave >> 1, wn = wave & 1;
+
+  // Sums of products are formed from zero and subtracted once: rounded at their
+  // own size and not at that of what they leave.  Every load first: L_jj's block, this wave's 16 panel rows of I and J and its
+  // 32 x 32 quadrant of the tile (accumulator item v: row lr + 4 v, column lc)
+  double lv[16];
 #pragma unroll
-  for (int u = 0; u < 4; ++u)
+  for (int u = 0; u < 16; ++u) {
+    const int r = wave + 4 * u;
+    lv[u] = lane <= r ? A[(size_t)(j0 + r) * n + j0 + lane] : 0.0;
+  }
+  d4v pi[4], pj[4], old[2][2], acc[2][2];
+#pragma unroll
+  for (int b = 0; b < 4; ++b)
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-      const int i = i0 + ti + u, k = k0 + tk + v;
-      old[u][v] = (i < n && k < n && k <= i) ? A[(size_t)i * n + k] : 0.0;
-    }
-  if (nb == NB) {
-    // a whole panel: every load issued before the first LDS store
-    const int cc = tid & 63;
-    double vi[16], vj[16];
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      const int r = (tid >> 6) + 4 * q;
-      vi[q] = (i0 + r < n) ? A[(size_t)(i0 + r) * n + j0 + cc] : 0.0;
-      vj[q] = (k0 + r < n) ? A[(size_t)(k0 + r) * n + j0 + cc] : 0.0;
+      const int r = 16 * wave + lr + 4 * v;
+      pi[b][v] = i0 + r < n ? A[(size_t)(i0 + r) * n + j0 + 16 * b + lc] : 0.0;
+      pj[b][v] = (I != J && k0 + r < n) ? A[(size_t)(k0 + r) * n + j0 + 16 * b + lc] : 0.0;
     }
 #pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      const int r = (tid >> 6) + 4 * q;
-      LI[r][cc] = vi[q];
-      LJ[r][cc] = vj[q];
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int r = i0 + 32 * wm + 16 * i + lr + 4 * v, k = k0 + 32 * wn + 16 * j + lc;
+        old[i][j][v] = (r < n && k <= r) ? A[(size_t)r * n + k] : 0.0;
+        acc[i][j][v] = 0.0;
+      }
+#pragma unroll
+  for (int u = 0; u < 16; ++u) Ls[(wave + 4 * u) * LD + lane] = lv[u];
+  __syncthreads();
+  // inverse of diagonal 16 x 16 block `wave`, column lc per lane: as each x_k is
+  // known, its products leave the entries below
+  {
+    const double *D = Ls + (16 * wave) * LD + 16 * wave;
+    const double rp = 1.0 / D[lc * LD + lc];
+    double x[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) x[k] = k == lc ? 1.0 : 0.0;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      x[k] *= lane_value(rp, k);
+#pragma unroll
+      for (int m = k + 1; m < 16; ++m) x[m] = fma(-D[m * LD + k], x[k], x[m]);
     }
-  } else {
-    for (int e = tid; e < 64 * nb; e += 256) {
-      int r = e / nb, cc = e % nb;
-      LI[r][cc] = (i0 + r < n) ? A[(size_t)(i0 + r) * n + j0 + cc] : 0.0;
-      LJ[r][cc] = (k0 + r < n) ? A[(size_t)(k0 + r) * n + j0 + cc] : 0.0;
-    }
+    if (lr == 0)
+#pragma unroll
+      for (int k = 0; k < 16; ++k) Di[(16 * wave + k) * LDD + lc] = x[k];
   }
   __syncthreads();
-  double acc[4][4] = {};
-  for (int cc = 0; cc < nb; ++cc) {
-    double a[4], b[4];
+  // X = A L_jj^-T for 16 rows of I and of J per wave, 16 columns at a time
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      a[u] = LI[ti + u][cc];
-      b[u] = LJ[tk + u][cc];
+  for (int b = 0; b < 4; ++b) {
+    const int row = 16 * wave + lc;
+    d4v si = {0.0, 0.0, 0.0, 0.0}, sj = si;
+#pragma unroll
+    for (int kk = 0; kk < 16 * b; kk += 4) {
+      const double l = Ls[(16 * b + lc) * LD + kk + lr];
+      si = mfma(XI[row * LD + kk + lr], l, si);
+      if (I != J) sj = mfma(XJ[row * LD + kk + lr], l, sj);
     }
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) acc[u][v] += a[u] * b[v];
-  }
-#pragma unroll
-  for (int u = 0; u < 4; ++u)
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-      int i = i0 + ti + u, k = k0 + tk + v;
-      if (i < n && k < n && k <= i) A[(size_t)i * n + k] = old[u][v] - acc[u][v];
+      XI[(16 * wave + lr + 4 * v) * LD + 16 * b + lc] = pi[b][v] - si[v];
+      if (I != J) XJ[(16 * wave + lr + 4 * v) * LD + 16 * b + lc] = pj[b][v] - sj[v];
     }
+    wave_lds_sync();
+    d4v xi = {0.0, 0.0, 0.0, 0.0}, xj = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int kk = 0; kk < 16; kk += 4) {
+      const double w = Di[(16 * b + lc) * LDD + kk + lr];
+      xi = mfma(XI[row * LD + 16 * b + kk + lr], w, xi);
+      if (I != J) xj = mfma(XJ[row * LD + 16 * b + kk + lr], w, xj);
+    }
+    wave_lds_sync();
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      XI[(16 * wave + lr + 4 * v) * LD + 16 * b + lc] = xi[v];
+      if (I != J) XJ[(16 * wave + lr + 4 * v) * LD + 16 * b + lc] = xj[v];
+    }
+    wave_lds_sync();
+  }
+  __syncthreads();
+  const double *B = I != J ? XJ : XI;
+  if (I != J || wm >= wn) {  // (a diagonal tile's upper quadrant is not kept)
+#pragma unroll 4
+    for (int kk = 0; kk < NB; kk += 4) {
+      double af[2], bf[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        af[i] = XI[(32 * wm + 16 * i + lc) * LD + kk + lr];
+        bf[i] = B[(32 * wn + 16 * i + lc) * LD + kk + lr];
+      }
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = mfma(af[i], bf[j], acc[i][j]);
+    }
+  }
+  if (I == J)  // the solved rows, transposed into block (p, I) of the upper triangle
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      const int r = wave + 4 * u;
+      if (i0 + lane < n) A[(size_t)(j0 + r) * n + i0 + lane] = XI[lane * LD + r];
+    }
+  if (t > 0) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int r = i0 + 32 * wm + 16 * i + lr + 4 * v, k = k0 + 32 * wn + 16 * j + lc;
+          if (r < n && k <= r) A[(size_t)r * n + k] = old[i][j][v] - acc[i][j][v];
+        }
+    return;
+  }
+  // the next diagonal block (Ls is free: every wave has passed its products)
+  const int nb = min(NB, n - i0);
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int r = 32 * wm + 16 * i + lr + 4 * v, k = 32 * wn + 16 * j + lc;
+        Ls[r * LD + k] = (r < nb && k < nb) ? old[i][j][v] - acc[i][j][v] : (r == k ? 1.0 : 0.0);
+      }
+  __syncthreads();
+  const int f = factor_block(Ls, nb, &fail_s);
+  if (f) {
+    if (tid == 0) g.info[c] = i0 + f;
+    return;
+  }
+  put_block(Ls, A, n, i0, nb);
 }
 
-__global__ void copy_lower_kernel(int C, int n, const double *A, double *L) {
-  int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  int64_t total = (int64_t)C * n * n;
-  for (; e < total; e += (int64_t)gridDim.x * blockDim.x) {
-    int64_t r = e % ((int64_t)n * n);
-    int i = (int)(r / n), k = (int)(r % n);
-    L[e] = (k <= i) ? A[e] : 0.0;
-  }
-}
-
-int chol_batched(int C, int n, const double *A, double *L, int32_t *info, hipStream_t s) {
-  if (C <= 0 || n <= 0) return SB_OK;
-  int st = launch_fill_i32(C, 0, info, s);
-  if (st) return st;
-  {
-    int64_t total = (int64_t)C * n * n;
-    unsigned blocks = (unsigned)std::min<int64_t>(8192, ceil_div(total, 256));
-    hipLaunchKernelGGL(copy_lower_kernel, dim3(blocks), dim3(256), 0, s, C, n, A, L);
-    SB_LAUNCH_CHECK();
-  }
-  for (int j0 = 0; j0 < n; j0 += NB) {
-    const int nb = std::min(NB, n - j0);
-    hipLaunchKernelGGL(chol_diag_kernel, dim3(C), dim3(256), 0, s, n, j0, L, info);
-    SB_LAUNCH_CHECK();
-    const int rest = n - j0 - nb;
-    if (rest <= 0) break;
-    hipLaunchKernelGGL(chol_trsm_kernel, dim3((unsigned)ceil_div(rest, 64), C), dim3(256), 0, s, n,
-                       j0, L, info);
-    SB_LAUNCH_CHECK();
-    const int T = (int)ceil_div(rest, 64);
-    hipLaunchKernelGGL(chol_syrk_kernel, dim3((unsigned)(T * (T + 1) / 2), C), dim3(256), 0, s, n,
-                       j0, L, info);
+int chol_run(int C, int n_max, const CholBatch &g, hipStream_t s) {
+  const int64_t total = (int64_t)n_max * n_max;
+  const unsigned copies =
+      n_max > NB ? (unsigned)std::min<int64_t>(512, ceil_div(total, 2048)) : 0u;
+  hipLaunchKernelGGL(chol_first_kernel, dim3(C, 1 + copies), dim3(256), 0, s, g);
+  SB_LAUNCH_CHECK();
+  const int nblk = (int)ceil_div(n_max, NB);
+  if (nblk < 2) return SB_OK;
+  for (int p = 0; p < nblk; ++p) {
+    const int T = nblk - 1 - p, gt = T * (T + 1) / 2;
+    const int moves = p > 0 ? nblk - p : 0;  // rows of blocks p .. of panel p - 1
+    hipLaunchKernelGGL(chol_panel_kernel, dim3((unsigned)(gt + moves), C), dim3(256), 0, s, g, p,
+                       gt);
     SB_LAUNCH_CHECK();
   }
   return SB_OK;
+}
+
+}  // namespace
+
+int chol_batched(int C, int n, const double *A, double *L, int32_t *info, hipStream_t s) {
+  if (C <= 0 || n <= 0) return SB_OK;
+  return chol_run(C, n, CholBatch{n, nullptr, nullptr, A, L, info}, s);
+}
+
+// In-place factorisation of C matrices of sizes nv[c] at offsets off[c].
+int chol_batched_u(int C, const int32_t *nv, const int64_t *off, int n_max, double *L,
+                   int32_t *info, hipStream_t s) {
+  if (C <= 0 || n_max <= 0) return SB_OK;
+  return chol_run(C, n_max, CholBatch{0, nv, off, L, L, info}, s);
 }
 
 // log det = 2 sum_i log L_ii from the factor (fixed-order reduction), NaN if it failed.
@@ -471,181 +563,8 @@ int launch_chol_solve(int C, int n, const double *L, const double *b, double *x,
 
 // ====================================================================
 // Uneven batches: matrix c has size n[c] and starts at off[c] (row-major,
-// leading dimension n[c]); vectors of matrix c start at voff[c].  The panel
-// loop runs to max n; a matrix whose size is reached skips the stage.
+// leading dimension n[c]); vectors of matrix c start at voff[c].
 namespace sb {
-
-__global__ __launch_bounds__(256) void chol_diag_u_kernel(int j0, const int32_t *nv,
-                                                          const int64_t *off, double *L,
-                                                          int32_t *info) {
-  const int c = blockIdx.x;
-  const int n = nv[c];
-  if (j0 >= n || info[c] != 0) return;
-  double *A = L + off[c];
-  const int nb = min(NB, n - j0);
-  const int tid = threadIdx.x;
-  __shared__ double T[NB][NB + 1];
-  __shared__ int fail;
-  for (int e = tid; e < nb * nb; e += 256) {
-    int i = e / nb, k = e % nb;
-    T[i][k] = (k <= i) ? A[(size_t)(j0 + i) * n + j0 + k] : 0.0;
-  }
-  if (tid == 0) fail = 0;
-  __syncthreads();
-  for (int col = 0; col < nb; ++col) {
-    if (tid == 0) {
-      double p = T[col][col];
-      if (!(p > 0.0))
-        fail = col + 1;
-      else
-        T[col][col] = sqrt(p);
-    }
-    __syncthreads();
-    if (fail) break;
-    const double ljj = T[col][col];
-    for (int i = col + 1 + tid; i < nb; i += 256) T[i][col] /= ljj;
-    __syncthreads();
-    const int rem = nb - col - 1;
-    for (int e = tid; e < rem * rem; e += 256) {
-      int i = col + 1 + e / rem, k = col + 1 + e % rem;
-      if (k <= i) T[i][k] -= T[i][col] * T[k][col];
-    }
-    __syncthreads();
-  }
-  if (fail) {
-    if (tid == 0) info[c] = j0 + fail;
-    return;
-  }
-  for (int e = tid; e < nb * nb; e += 256) {
-    int i = e / nb, k = e % nb;
-    A[(size_t)(j0 + i) * n + j0 + k] = (k <= i) ? T[i][k] : 0.0;
-  }
-}
-
-__global__ __launch_bounds__(64) void chol_trsm_u_kernel(int j0, const int32_t *nv,
-                                                         const int64_t *off, double *L,
-                                                         const int32_t *info) {
-  const int c = blockIdx.y;
-  const int n = nv[c];
-  if (j0 >= n || info[c] != 0) return;
-  double *A = L + off[c];
-  const int nb = min(NB, n - j0);
-  const int r0 = j0 + nb;
-  if (r0 + (int)blockIdx.x * 64 >= n) return;
-  __shared__ double D[NB][NB + 1];
-  for (int e = threadIdx.x; e < nb * nb; e += 64) {
-    int i = e / nb, k = e % nb;
-    D[i][k] = A[(size_t)(j0 + i) * n + j0 + k];
-  }
-  __syncthreads();
-  const int i = r0 + blockIdx.x * 64 + threadIdx.x;
-  if (i >= n) return;
-  double *row = A + (size_t)i * n + j0;
-  double x[NB];
-#pragma unroll
-  for (int cc = 0; cc < NB; ++cc) x[cc] = (cc < nb) ? row[cc] : 0.0;
-#pragma unroll
-  for (int cc = 0; cc < NB; ++cc) {
-    if (cc < nb) {
-      double s = x[cc];
-#pragma unroll
-      for (int t = 0; t < cc; ++t) s -= x[t] * D[cc][t];
-      x[cc] = s / D[cc][cc];
-    }
-  }
-#pragma unroll
-  for (int cc = 0; cc < NB; ++cc)
-    if (cc < nb) row[cc] = x[cc];
-}
-
-__global__ __launch_bounds__(256) void chol_syrk_u_kernel(int j0, const int32_t *nv,
-                                                          const int64_t *off, double *L,
-                                                          const int32_t *info) {
-  const int c = blockIdx.y;
-  const int n = nv[c];
-  if (j0 >= n || info[c] != 0) return;
-  double *A = L + off[c];
-  const int nb = min(NB, n - j0);
-  const int r0 = j0 + nb;
-  const int rest = n - r0;
-  if (rest <= 0) return;
-  const int Tn = (rest + 63) / 64;
-  const int t = blockIdx.x;
-  if (t >= Tn * (Tn + 1) / 2) return;
-  int I = (int)((sqrt(8.0 * t + 1.0) - 1.0) * 0.5);
-  while ((I + 1) * (I + 2) / 2 <= t) ++I;
-  while (I * (I + 1) / 2 > t) --I;
-  const int J = t - I * (I + 1) / 2;
-  const int i0 = r0 + I * 64, k0 = r0 + J * 64;
-  __shared__ double LI[64][NB + 1];
-  __shared__ double LJ[64][NB + 1];
-  const int tid = threadIdx.x;
-  for (int e = tid; e < 64 * nb; e += 256) {
-    int r = e / nb, cc = e % nb;
-    LI[r][cc] = (i0 + r < n) ? A[(size_t)(i0 + r) * n + j0 + cc] : 0.0;
-    LJ[r][cc] = (k0 + r < n) ? A[(size_t)(k0 + r) * n + j0 + cc] : 0.0;
-  }
-  __syncthreads();
-  const int ti = (tid >> 4) * 4, tk = (tid & 15) * 4;
-  double acc[4][4] = {};
-  for (int cc = 0; cc < nb; ++cc) {
-    double a[4], bv[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      a[u] = LI[ti + u][cc];
-      bv[u] = LJ[tk + u][cc];
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) acc[u][v] += a[u] * bv[v];
-  }
-#pragma unroll
-  for (int u = 0; u < 4; ++u)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      int i = i0 + ti + u, k = k0 + tk + v;
-      if (i < n && k < n && k <= i) A[(size_t)i * n + k] -= acc[u][v];
-    }
-}
-
-__global__ void zero_upper_u_kernel(int C, const int32_t *nv, const int64_t *off, double *L) {
-  const int c = blockIdx.y;
-  if (c >= C) return;
-  const int n = nv[c];
-  const int64_t tot = (int64_t)n * n;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < tot;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    const int i = (int)(e / n), k = (int)(e % n);
-    if (k > i) L[off[c] + e] = 0.0;
-  }
-}
-
-// In-place factorisation of C matrices of sizes nv[c] at offsets off[c].
-int chol_batched_u(int C, const int32_t *nv, const int64_t *off, int n_max, double *L,
-                   int32_t *info, hipStream_t s) {
-  if (C <= 0 || n_max <= 0) return SB_OK;
-  int st = launch_fill_i32(C, 0, info, s);
-  if (st) return st;
-  hipLaunchKernelGGL(zero_upper_u_kernel, dim3((unsigned)std::min<int64_t>(64, ceil_div((int64_t)n_max * n_max, 256)), C),
-                     dim3(256), 0, s, C, nv, off, L);
-  SB_LAUNCH_CHECK();
-  for (int j0 = 0; j0 < n_max; j0 += NB) {
-    hipLaunchKernelGGL(chol_diag_u_kernel, dim3(C), dim3(256), 0, s, j0, nv, off, L, info);
-    const int rest = n_max - j0 - std::min(NB, n_max - j0);
-    if (rest <= 0) {
-      SB_LAUNCH_CHECK();
-      break;
-    }
-    hipLaunchKernelGGL(chol_trsm_u_kernel, dim3((unsigned)ceil_div(rest, 64), C), dim3(64), 0, s,
-                       j0, nv, off, L, info);
-    const int T = (int)ceil_div(rest, 64);
-    hipLaunchKernelGGL(chol_syrk_u_kernel, dim3((unsigned)(T * (T + 1) / 2), C), dim3(256), 0, s,
-                       j0, nv, off, L, info);
-    SB_LAUNCH_CHECK();
-  }
-  return SB_OK;
-}
 
 __global__ __launch_bounds__(256) void logdet_u_kernel(const int32_t *nv, const int64_t *off,
                                                        const double *L, const int32_t *info,

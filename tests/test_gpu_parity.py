@@ -868,3 +868,23 @@ def test_lbfgs_rows_of_any_alignment(L, d):
         assert np.max(np.abs(r["x"].cpu().numpy() - mu)) <= 1e-3 * np.sqrt(d)
         # (a ring read or written at wrong elements would not converge superlinearly)
         assert int(r["iters"].max()) <= 100
+
+
+@pytest.mark.parametrize("n", [2, 16, 63, 127, 128, 129, 193, 320])
+def test_cholesky_blocks(L, n):
+    """Factors at the edges of the 16- and 64-wide blocks and panels against LAPACK
+    (numpy, FP64), zeros above the diagonal, and matrices of the batch whose pivot fails in the
+    first, a middle or the last column (info is that column, the others are unaffected).
+    |L - L_ref| <= n cond eps |L| with cond 1e3 (backward error n eps, first-order sensitivity)."""
+    A = synth.random_spd(n, 900 + n, cond=1e3, batch=4)
+    fails = {1: 0, 2: n // 2, 3: n - 1}
+    B = A.copy()
+    for c, k in fails.items():
+        B[c, k, k] = -1.0
+    Lf, ld, info = (t.cpu().numpy() for t in L.sb_cholesky_logdet_dev(dev(B)))
+    ref = np.linalg.cholesky(A[0])
+    assert np.max(np.abs(Lf[0] - ref)) <= n * 1e3 * 2.0 ** -52 * np.max(np.abs(ref))
+    assert np.all(np.triu(Lf[0], 1) == 0.0)
+    assert abs(ld[0] - np.linalg.slogdet(A[0])[1]) <= n * 1e3 * 2.0 ** -52 * n
+    assert info[0] == 0 and [int(info[c]) for c in fails] == [k + 1 for k in fails.values()]
+    assert np.all(np.isnan(ld[1:]))
