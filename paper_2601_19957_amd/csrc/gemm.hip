@@ -1309,43 +1309,100 @@ int launch_hvp_finish(const Model &m, const HvpArgs &h, hipStream_t s) {
 // H = -nabla^2 l = sum_k r_k (P_k - u_k u_k^T) + g g^T (mixture) or
 // ((nu+d)/(nu+q)) P - (2 (nu+d)/(nu+q)^2) u u^T (Student-t), u_k = Y_k;
 // symmetrised as (H + H^T)/2.  This is the HVP epilogue with V = I.
-__device__ inline double hess_entry(const Model &m, int c, int i, int j, const double *Y,
-                                    int64_t ldy, const double *aux, const double *grad) {
-  const int d = m.d, K = m.K;
-  const double *y = Y + (size_t)c * ldy;
-  if (m.family == SB_FAMILY_STUDENT_T) {
-    double q = aux[(size_t)c * K];
-    double nd = m.nu + d, den = m.nu + q;
-    return (nd / den) * m.P64[(size_t)i * d + j] - (2.0 * nd / (den * den)) * y[i] * y[j];
+//
+// Bound by memory: d^2 of P per component with weight and of H per point.  A
+// workgroup takes the 32 x 32 tiles (I, J) and (J, I) together, so that both
+// halves of every entry are read along rows and meet in LDS; a component whose
+// responsibility is zero adds nothing and its P is not read (as in the row
+// epilogue).  d = 1024, K = 8, 8 points at the modes: 31 us (each entry with
+// its mirror image read down a column, and every component: 272 us).
+struct HessSrc {
+  int d, ld, K, family;  // ld: row stride of P and of each component's u
+  double nu;
+  const double *P, *u, *g, *aux;  // P [K][ld][ld], u [K][ld], g [d], r [K] (or q)
+  double *H;                      // [d][d]
+};
+
+__device__ inline void hess_tiles(const HessSrc &h, int t, double (&S)[2][32][33]) {
+  int I = (int)((sqrtf(8.0f * (float)t + 1.0f) - 1.0f) * 0.5f);
+  while ((I + 1) * (I + 2) / 2 <= t) ++I;
+  while (I * (I + 1) / 2 > t) --I;
+  const int J = t - I * (I + 1) / 2, d = h.d;
+  if (32 * I >= d) return;
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+  // entries (r0 + ty + 8 q, c0 + tx) of tile 0 = (I, J) and 1 = (J, I)
+  const int r0[2] = {32 * I, 32 * J}, nt = I == J ? 1 : 2;
+  double e[2][4];
+  for (int w = 0; w < nt; ++w) {
+    const int j = r0[1 - w] + tx;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int i = r0[w] + ty + 8 * q;
+      e[w][q] = (h.family != SB_FAMILY_STUDENT_T && i < d && j < d) ? h.g[i] * h.g[j] : 0.0;
+    }
   }
-  const double *g = grad + (size_t)c * d;
-  double s = g[i] * g[j];
-  for (int k = 0; k < K; ++k) {
-    double rk = aux[(size_t)c * K + k];
-    const double *u = y + (size_t)k * d;
-    s += rk * (m.P64[(size_t)k * d * d + (size_t)i * d + j] - u[i] * u[j]);
+  if (h.family == SB_FAMILY_STUDENT_T) {
+    const double qv = h.aux[0], nd = h.nu + h.d, den = h.nu + qv;
+    for (int w = 0; w < nt; ++w) {
+      const int j = r0[1 - w] + tx;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int i = r0[w] + ty + 8 * q;
+        if (i < d && j < d)
+          e[w][q] = (nd / den) * h.P[(size_t)i * h.ld + j] -
+                    (2.0 * nd / (den * den)) * h.u[i] * h.u[j];
+      }
+    }
+  } else {
+    for (int k = 0; k < h.K; ++k) {
+      const double rk = h.aux[k];
+      if (rk == 0.0) continue;
+      const double *P = h.P + (size_t)k * h.ld * h.ld, *u = h.u + (size_t)k * h.ld;
+      for (int w = 0; w < nt; ++w) {
+        const int j = r0[1 - w] + tx;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int i = r0[w] + ty + 8 * q;
+          if (i < d && j < d) e[w][q] += rk * (P[(size_t)i * h.ld + j] - u[i] * u[j]);
+        }
+      }
+    }
   }
-  return s;
+  for (int w = 0; w < nt; ++w)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) S[w][ty + 8 * q][tx] = e[w][q];
+  __syncthreads();
+  for (int w = 0; w < nt; ++w) {
+    const int j = r0[1 - w] + tx;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int i = r0[w] + ty + 8 * q;
+      if (i < d && j < d)
+        h.H[(size_t)i * d + j] = 0.5 * (e[w][q] + S[nt - 1 - w][tx][ty + 8 * q]);
+    }
+  }
 }
 
-__global__ __launch_bounds__(256) void hessian_kernel(Model m, int C, const double *Y, int64_t ldy,
+__global__ __launch_bounds__(256) void hessian_kernel(Model m, const double *Y, int64_t ldy,
                                                       const double *aux, const double *grad,
                                                       double *H) {
-  const int c = blockIdx.z;
-  const int i = blockIdx.y * 16 + (threadIdx.x >> 4);
-  const int j = blockIdx.x * 16 + (threadIdx.x & 15);
-  const int d = m.d;
-  if (c >= C || i >= d || j >= d) return;
-  double hij = hess_entry(m, c, i, j, Y, ldy, aux, grad);
-  double hji = hess_entry(m, c, j, i, Y, ldy, aux, grad);
-  H[(size_t)c * d * d + (size_t)i * d + j] = 0.5 * (hij + hji);
+  __shared__ double S[2][32][33];
+  const int c = blockIdx.y, d = m.d;
+  hess_tiles(HessSrc{d, d, m.K, m.family, m.nu, m.P64, Y + (size_t)c * ldy,
+                     grad + (size_t)c * d, aux + (size_t)c * m.K, H + (size_t)c * d * d},
+             blockIdx.x, S);
+}
+
+static unsigned hess_grid(int d) {
+  const int64_t T = ceil_div(d, 32);
+  return (unsigned)(T * (T + 1) / 2);
 }
 
 int launch_hessian_assemble(const Model &m, int C, const double *Y, int64_t ldy,
                             const double *aux, const double *grad, double *H, hipStream_t s) {
   if (C <= 0) return SB_OK;
-  dim3 grid((unsigned)ceil_div(m.d, 16), (unsigned)ceil_div(m.d, 16), (unsigned)C);
-  hipLaunchKernelGGL(hessian_kernel, grid, dim3(256), 0, s, m, C, Y, ldy, aux, grad, H);
+  hipLaunchKernelGGL(hessian_kernel, dim3(hess_grid(m.d), (unsigned)C), dim3(256), 0, s, m, Y, ldy,
+                     aux, grad, H);
   SB_LAUNCH_CHECK();
   return SB_OK;
 }
@@ -1667,45 +1724,26 @@ int launch_finish_group(int dtype, const BatchDev &b, const FinishGroupArgs &f, 
 // d_p, leading dimension d_p, at H + hoff[c]; Y rows packed by segment,
 // aux rows of stride auxs, gradient rows of stride gs.  Symmetrised.
 __global__ __launch_bounds__(256) void hessian_group_kernel(BatchDev b, const GSeg *segs,
-                                                             int nseg, int C, const double *Y,
+                                                             int nseg, const double *Y,
                                                              const double *aux, int64_t auxs,
                                                              const double *grad, int64_t gs,
                                                              const int64_t *hoff, double *H) {
-  const int c = blockIdx.z;
-  if (c >= C) return;
+  __shared__ double S[2][32][33];
+  const int c = blockIdx.y;
   const GSeg sg = segs[find_seg(segs, nseg, c)];
   const BatchProb pr = b.probs[sg.prob];
-  const int d = pr.d, dp = pr.dp;
-  const int i = blockIdx.y * 16 + (threadIdx.x >> 4);
-  const int j = blockIdx.x * 16 + (threadIdx.x & 15);
-  if (i >= d || j >= d) return;
-  const double *y = Y + sg.yoff + (int64_t)(c - sg.row0) * pr.K * dp;
-  const double *P = b.P64 + pr.P_off;
-  auto entry = [&](int a, int bb) -> double {
-    if (pr.family == SB_FAMILY_STUDENT_T) {
-      const double q = aux[(size_t)c * auxs];
-      const double nd = pr.nu + pr.d, den = pr.nu + q;
-      return (nd / den) * P[(size_t)a * dp + bb] - (2.0 * nd / (den * den)) * y[a] * y[bb];
-    }
-    const double *g = grad + (size_t)c * gs;
-    double s = g[a] * g[bb];
-    for (int k = 0; k < pr.K; ++k) {
-      const double rk = aux[(size_t)c * auxs + k];
-      const double *u = y + (size_t)k * dp;
-      s += rk * (P[(size_t)k * dp * dp + (size_t)a * dp + bb] - u[a] * u[bb]);
-    }
-    return s;
-  };
-  H[hoff[c] + (size_t)i * d + j] = 0.5 * (entry(i, j) + entry(j, i));
+  hess_tiles(HessSrc{pr.d, pr.dp, pr.K, pr.family, pr.nu, b.P64 + pr.P_off,
+                     Y + sg.yoff + (int64_t)(c - sg.row0) * pr.K * pr.dp, grad + (size_t)c * gs,
+                     aux + (size_t)c * auxs, H + hoff[c]},
+             blockIdx.x, S);
 }
 
 int launch_hessian_group(const BatchDev &b, const GSeg *segs, int nseg, int C, const double *Y,
                          const double *aux, int64_t auxs, const double *grad, int64_t gs,
                          const int64_t *hoff, double *H, int d_max, hipStream_t s) {
   if (C <= 0) return SB_OK;
-  dim3 grid((unsigned)ceil_div(d_max, 16), (unsigned)ceil_div(d_max, 16), (unsigned)C);
-  hipLaunchKernelGGL(hessian_group_kernel, grid, dim3(256), 0, s, b, segs, nseg, C, Y, aux, auxs,
-                     grad, gs, hoff, H);
+  hipLaunchKernelGGL(hessian_group_kernel, dim3(hess_grid(d_max), (unsigned)C), dim3(256), 0, s, b,
+                     segs, nseg, Y, aux, auxs, grad, gs, hoff, H);
   SB_LAUNCH_CHECK();
   return SB_OK;
 }
