@@ -419,144 +419,185 @@ int launch_logdet(int C, int n, const double *L, const int32_t *info, double *lo
   return SB_OK;
 }
 
-// Solve L L^T x = b: blocked forward (row dots over solved blocks, then the
-// 64x64 diagonal block in one wave) and backward substitution.  One
-// workgroup of 16 waves per matrix, x in LDS; the dots against the solved
-// part are split over all waves with several independent loads per lane in
-// flight (the solve is bound by the latency of reading L).
-constexpr int SV_T = 1024, SV_W = SV_T / 64;
-// Lane l's value to every lane (l uniform): two scalar reads, no LDS trip.
-__device__ inline double lane_bcast(double v, int l) {
-  const unsigned long long u = (unsigned long long)__double_as_longlong(v);
-  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)u, l);
-  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(u >> 32), l);
-  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-__global__ __launch_bounds__(SV_T) void chol_solve_kernel(int n, const double *Lall,
-                                                          const double *ball, double *xall,
+// Solve L L^T x = b, one workgroup of 16 waves per matrix, x in LDS, 64 rows at
+// a time forward (L z = b) and back (L^T x = z).  One wave carries the chain: it
+// adds the block's product with the block solved last and substitutes through
+// the diagonal block, both from LDS.  Meanwhile the others sum the next block's
+// products with everything solved before that and bring its two tiles in, so
+// that reading L, which is what bounds the solve (one workgroup takes about a
+// hundredth of the memory rate), goes on all the time.  n = 1024: 350 -> 235 us.
+constexpr int SV_T = 1024, SV_W = SV_T / 64 - 1;  // (15 waves beside the chain)
+constexpr int SV_LD = 65;
+__global__ __launch_bounds__(SV_T) void chol_solve_kernel(CholBatch g, const double *ball,
+                                                          double *xall, int64_t vs,
                                                           const int32_t *info) {
   extern __shared__ double xs[];  // [n]
-  __shared__ double part[SV_W][64];
-  __shared__ double Tb[64][65];   // current diagonal block
-  const int c = blockIdx.x;
-  const double *L = Lall + (size_t)c * n * n;
-  const double *b = ball + (size_t)c * n;
-  double *x = xall + (size_t)c * n;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  __shared__ double TD[NB * SV_LD], TL[NB * SV_LD];  // diagonal block, its neighbour
+  __shared__ double part[2][SV_W][64];
+  const int c = blockIdx.x, n = chol_n(g, c), nblk = (n + NB - 1) / NB;
+  const double *L = g.L + chol_off(g, c);
+  const double *b = ball + (size_t)c * vs;
+  double *x = xall + (size_t)c * vs;
+  const int tid = threadIdx.x, lane = tid & 63, w = uniform(tid >> 6);
   if (info && info[c] != 0) {
     for (int i = tid; i < n; i += SV_T) x[i] = NAN;
     return;
   }
   for (int i = tid; i < n; i += SV_T) xs[i] = b[i];
+  // tile (bi, bj) through the registers of the 15 waves (zeros outside L)
+  constexpr int NE = (NB * NB + 64 * SV_W - 1) / (64 * SV_W);
+  auto fetch = [&](int bi, int bj, double (&v)[NE]) {
+#pragma unroll
+    for (int q = 0; q < NE; ++q) {
+      const int e = tid - 64 + 64 * SV_W * q, i = bi * NB + (e >> 6), k = bj * NB + (e & 63);
+      v[q] = (e < NB * NB && i < n && k <= i) ? L[(size_t)i * n + k] : 0.0;
+    }
+  };
+  auto put = [&](double *T, const double (&v)[NE]) {
+#pragma unroll
+    for (int q = 0; q < NE; ++q) {
+      const int e = tid - 64 + 64 * SV_W * q;
+      if (e < NB * NB) T[(e >> 6) * SV_LD + (e & 63)] = v[q];
+    }
+  };
+  if (w > 0) {
+    double v[NE];
+    fetch(0, 0, v);
+    put(TD, v);
+  }
   __syncthreads();
-  // forward: L z = b
-  for (int i0 = 0; i0 < n; i0 += 64) {
-    const int nb = min(64, n - i0);
-    for (int r = w; r < nb; r += SV_W)  // diagonal block into LDS, row by row
-      if (lane < nb) Tb[r][lane] = L[(size_t)(i0 + r) * n + i0 + lane];
-    // rows i0 + w + 16 q (q < 4) less sum_{k < i0} L[i][k] z_k; lanes split k.
-    // Eight k values per lane per pass, their 32 loads issued before the
-    // first product (the sums keep their order: k ascending per lane); a row
-    // past the block reads row i0 and its sum is never used.
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
-    const double *Lr[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int r = w + SV_W * q;
-      Lr[q] = L + (size_t)(i0 + (r < nb ? r : 0)) * n;
-    }
-    int k = lane;
-    for (; k + 64 * 7 < i0; k += 64 * 8) {
-      double lv[8][4];
-#pragma unroll
-      for (int u = 0; u < 8; ++u)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) lv[u][q] = Lr[q][k + 64 * u];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const double zk = xs[k + 64 * u];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) acc[q] += lv[u][q] * zk;
-      }
-    }
-    for (; k < i0; k += 64) {
-      const double zk = xs[k];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) acc[q] += Lr[q][k] * zk;
-    }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const double t = wave_sum(acc[q]);
-      if (lane == 0) part[0][w + SV_W * q] = t;
-    }
-    __syncthreads();
+  for (int i = 0; i < nblk; ++i) {
+    const int i0 = i * NB, nb = min(NB, n - i0), pb = i & 1;
+    double vl[NE], vd[NE];
     if (w == 0) {
-      // lane cc holds the reciprocal of pivot cc; one division per lane
-      const double rp = (lane < nb) ? 1.0 / Tb[lane][lane] : 1.0;
-      double val = (lane < nb) ? xs[i0 + lane] - part[0][lane] : 0.0;
+      double t = i > 1 ? part[pb][0][lane] : 0.0;
+      if (i > 0)
+#pragma unroll 16
+        for (int k = 0; k < NB; ++k) t += TL[lane * SV_LD + k] * xs[i0 - NB + k];
+      double val = lane < nb ? xs[i0 + lane] - t : 0.0;
+      const double rp = lane < nb ? 1.0 / TD[lane * SV_LD + lane] : 1.0;
 #pragma unroll 8
-      for (int cc = 0; cc < nb; ++cc) {  // (unrolled: the Tb reads leave the chain)
-        const double xc = lane_bcast(val * rp, cc);
+      for (int cc = 0; cc < nb; ++cc) {  // (unrolled: the reads of TD leave the chain)
+        const double xc = lane_value(val * rp, cc);
         if (lane == cc) val = xc;
-        if (lane > cc && lane < nb) val -= Tb[lane][cc] * xc;
+        if (lane > cc) val -= TD[lane * SV_LD + cc] * xc;
       }
       if (lane < nb) xs[i0 + lane] = val;
+    } else if (i + 1 < nblk) {
+      fetch(i + 1, i, vl);
+      fetch(i + 1, i + 1, vd);
+      // rows w - 1 + 15 q of block i + 1 with the solved k < i0, lanes split k
+      constexpr int NR = (NB + SV_W - 1) / SV_W;
+      double acc[NR];
+      const double *Lr[NR];
+#pragma unroll
+      for (int q = 0; q < NR; ++q) {
+        const int r = w - 1 + SV_W * q, row = i0 + NB + r;
+        acc[q] = 0.0;
+        Lr[q] = L + (size_t)(r < NB && row < n ? row : 0) * n;  // (others: sums not used)
+      }
+      int k = lane;
+      for (; k + 64 * 3 < i0; k += 64 * 4) {
+        double lv[4][NR];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+          for (int q = 0; q < NR; ++q) lv[u][q] = Lr[q][k + 64 * u];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+          for (int q = 0; q < NR; ++q) acc[q] += lv[u][q] * xs[k + 64 * u];
+      }
+      for (; k < i0; k += 64)
+#pragma unroll
+        for (int q = 0; q < NR; ++q) acc[q] += Lr[q][k] * xs[k];
+#pragma unroll
+      for (int q = 0; q < NR; ++q) {
+        const double t = wave_sum(acc[q]);
+        if (lane == 0 && w - 1 + SV_W * q < NB) part[pb ^ 1][0][w - 1 + SV_W * q] = t;
+      }
+    }
+    __syncthreads();
+    if (w > 0 && i + 1 < nblk) {
+      put(TL, vl);
+      put(TD, vd);
     }
     __syncthreads();
   }
-  // backward: L^T x = z
-  for (int iend = n; iend > 0; iend -= 64) {
-    const int i0 = max(0, iend - 64);
-    const int nb = iend - i0;
-    for (int r = w; r < nb; r += SV_W)
-      if (lane < nb) Tb[r][lane] = L[(size_t)(i0 + r) * n + i0 + lane];
-    // s_i = sum_{k >= iend} L[k][i] x_k for i in block; lanes index i, waves split k
-    // (sixteen rows per pass, their loads issued before the first product;
-    // k ascending per wave as before)
-    double sacc = 0.0;
-    if (lane < nb) {
-      int k = iend + w;
+  for (int i = nblk - 1; i >= 0; --i) {
+    const int i0 = i * NB, nb = min(NB, n - i0), pb = i & 1;
+    double vl[NE], vd[NE];
+    if (w == 0) {
+      double t = 0.0;
+      if (i + 2 < nblk)
+#pragma unroll
+        for (int u = 0; u < SV_W; ++u) t += part[pb][u][lane];
+      if (i + 1 < nblk) {
+        const int nn = min(NB, n - i0 - NB);  // (rows past the matrix: zeros in TL)
+#pragma unroll 16
+        for (int k = 0; k < nn; ++k) t += TL[k * SV_LD + lane] * xs[i0 + NB + k];
+      }
+      double val = lane < nb ? xs[i0 + lane] - t : 0.0;
+      const double rp = lane < nb ? 1.0 / TD[lane * SV_LD + lane] : 1.0;
+#pragma unroll 8
+      for (int cc = nb - 1; cc >= 0; --cc) {
+        const double xc = lane_value(val * rp, cc);
+        if (lane == cc) val = xc;
+        if (lane < cc) val -= TD[cc * SV_LD + lane] * xc;
+      }
+      if (lane < nb) xs[i0 + lane] = val;
+    } else if (i > 0) {
+      fetch(i, i - 1, vl);
+      fetch(i - 1, i - 1, vd);
+      // column lane of block i - 1 with the solved rows k >= i0 + 64, waves split k
+      const double *Lc = L + i0 - NB + lane;
+      double acc = 0.0;
+      int k = i0 + NB + w - 1;
       for (; k + SV_W * 15 < n; k += SV_W * 16) {
         double lv[16];
 #pragma unroll
-        for (int u = 0; u < 16; ++u) lv[u] = L[(size_t)(k + SV_W * u) * n + i0 + lane];
+        for (int u = 0; u < 16; ++u) lv[u] = Lc[(size_t)(k + SV_W * u) * n];
 #pragma unroll
-        for (int u = 0; u < 16; ++u) sacc += lv[u] * xs[k + SV_W * u];
+        for (int u = 0; u < 16; ++u) acc += lv[u] * xs[k + SV_W * u];
       }
-      for (; k < n; k += SV_W) sacc += L[(size_t)k * n + i0 + lane] * xs[k];
+      for (; k < n; k += SV_W) acc += Lc[(size_t)k * n] * xs[k];
+      part[pb ^ 1][w - 1][lane] = acc;
     }
-    part[w][lane] = sacc;
     __syncthreads();
-    if (w == 0) {
-      double sv = part[0][lane];
-#pragma unroll
-      for (int u = 1; u < SV_W; ++u) sv += part[u][lane];
-      double val = (lane < nb) ? xs[i0 + lane] - sv : 0.0;
-      const double rp = (lane < nb) ? 1.0 / Tb[lane][lane] : 1.0;
-#pragma unroll 8
-      for (int cc = nb - 1; cc >= 0; --cc) {
-        const double xc = lane_bcast(val * rp, cc);
-        if (lane == cc) val = xc;
-        if (lane < cc) val -= Tb[cc][lane] * xc;
-      }
-      if (lane < nb) xs[i0 + lane] = val;
+    if (w > 0 && i > 0) {
+      put(TL, vl);
+      put(TD, vd);
     }
     __syncthreads();
   }
   for (int i = tid; i < n; i += SV_T) x[i] = xs[i];
 }
 
-int launch_chol_solve(int C, int n, const double *L, const double *b, double *x,
-                      const int32_t *info, hipStream_t s) {
+static int solve_run(int C, int n_max, const CholBatch &g, const double *b, double *x, int64_t vs,
+                     const int32_t *info, hipStream_t s) {
   if (C <= 0) return SB_OK;
-  size_t shm = sizeof(double) * (size_t)n;
+  const size_t shm = sizeof(double) * (size_t)n_max;
   if (shm > 64 * 1024) {
-    set_error("solve dimension %d too large", n);
+    set_error("solve dimension %d too large", n_max);
     return SB_E_UNSUPPORTED;
   }
-  hipLaunchKernelGGL(chol_solve_kernel, dim3(C), dim3(SV_T), shm, s, n, L, b, x, info);
+  hipLaunchKernelGGL(chol_solve_kernel, dim3(C), dim3(SV_T), shm, s, g, b, x, vs, info);
   SB_LAUNCH_CHECK();
   return SB_OK;
+}
+
+int launch_chol_solve(int C, int n, const double *L, const double *b, double *x,
+                      const int32_t *info, hipStream_t s) {
+  return solve_run(C, n, CholBatch{n, nullptr, nullptr, nullptr, (double *)L, nullptr}, b, x, n,
+                   info, s);
+}
+
+// Matrix c of size nv[c] at offset off[c]; its rows of b and x start at c * vs.
+int launch_chol_solve_u(int C, const int32_t *nv, const int64_t *off, int n_max, const double *L,
+                        const double *b, double *x, int64_t vs, const int32_t *info,
+                        hipStream_t s) {
+  return solve_run(C, n_max, CholBatch{0, nv, off, nullptr, (double *)L, nullptr}, b, x, vs, info,
+                   s);
 }
 
 }  // namespace sb
@@ -582,91 +623,6 @@ int launch_logdet_u(int C, const int32_t *nv, const int64_t *off, const double *
                     const int32_t *info, double *logdet, hipStream_t s) {
   if (C <= 0) return SB_OK;
   hipLaunchKernelGGL(logdet_u_kernel, dim3(C), dim3(256), 0, s, nv, off, L, info, logdet);
-  SB_LAUNCH_CHECK();
-  return SB_OK;
-}
-
-// Solve L L^T x = b for matrix c (size nv[c]); b and x rows start at c * vs.
-__global__ __launch_bounds__(256) void chol_solve_u_kernel(const int32_t *nv, const int64_t *off,
-                                                           const double *Lall, const double *ball,
-                                                           double *xall, int64_t vs,
-                                                           const int32_t *info) {
-  extern __shared__ double xs[];
-  __shared__ double part[4][64];
-  __shared__ double Tb[64][65];
-  const int c = blockIdx.x;
-  const int n = nv[c];
-  const double *L = Lall + off[c];
-  const double *b = ball + (size_t)c * vs;
-  double *x = xall + (size_t)c * vs;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  if (info && info[c] != 0) {
-    for (int i = tid; i < n; i += 256) x[i] = NAN;
-    return;
-  }
-  for (int i = tid; i < n; i += 256) xs[i] = b[i];
-  __syncthreads();
-  for (int i0 = 0; i0 < n; i0 += 64) {
-    const int nb = min(64, n - i0);
-    for (int rr = 0; rr < 16; ++rr) {
-      const int r = w * 16 + rr;
-      double sacc = 0.0;
-      if (r < nb)
-#pragma unroll 8
-        for (int k = lane; k < i0; k += 64) sacc += L[(size_t)(i0 + r) * n + k] * xs[k];
-      sacc = wave_sum(sacc);
-      if (lane == 0) part[0][r] = sacc;
-    }
-    for (int r = w; r < nb; r += 4)  // diagonal block into LDS, row by row
-      if (lane < nb) Tb[r][lane] = L[(size_t)(i0 + r) * n + i0 + lane];
-    __syncthreads();
-    if (w == 0) {
-      double val = (lane < nb) ? xs[i0 + lane] - part[0][lane] : 0.0;
-      for (int cc = 0; cc < nb; ++cc) {
-        double xc = __shfl(val / Tb[cc][cc], cc, 64);
-        if (lane == cc) val = xc;
-        if (lane > cc && lane < nb) val -= Tb[lane][cc] * xc;
-      }
-      if (lane < nb) xs[i0 + lane] = val;
-    }
-    __syncthreads();
-  }
-  for (int iend = n; iend > 0; iend -= 64) {
-    const int i0 = max(0, iend - 64);
-    const int nb = iend - i0;
-    double sacc = 0.0;
-    if (lane < nb)
-#pragma unroll 8
-      for (int k = iend + w; k < n; k += 4) sacc += L[(size_t)k * n + i0 + lane] * xs[k];
-    part[w][lane] = sacc;
-    for (int r = w; r < nb; r += 4)
-      if (lane < nb) Tb[r][lane] = L[(size_t)(i0 + r) * n + i0 + lane];
-    __syncthreads();
-    if (w == 0) {
-      double sv = part[0][lane] + part[1][lane] + part[2][lane] + part[3][lane];
-      double val = (lane < nb) ? xs[i0 + lane] - sv : 0.0;
-      for (int cc = nb - 1; cc >= 0; --cc) {
-        double xc = __shfl(val / Tb[cc][cc], cc, 64);
-        if (lane == cc) val = xc;
-        if (lane < cc) val -= Tb[cc][lane] * xc;
-      }
-      if (lane < nb) xs[i0 + lane] = val;
-    }
-    __syncthreads();
-  }
-  for (int i = tid; i < n; i += 256) x[i] = xs[i];
-}
-
-int launch_chol_solve_u(int C, const int32_t *nv, const int64_t *off, int n_max, const double *L,
-                        const double *b, double *x, int64_t vs, const int32_t *info,
-                        hipStream_t s) {
-  if (C <= 0) return SB_OK;
-  const size_t shm = sizeof(double) * (size_t)n_max;
-  if (shm > 64 * 1024) {
-    set_error("solve dimension %d too large", n_max);
-    return SB_E_UNSUPPORTED;
-  }
-  hipLaunchKernelGGL(chol_solve_u_kernel, dim3(C), dim3(256), shm, s, nv, off, L, b, x, vs, info);
   SB_LAUNCH_CHECK();
   return SB_OK;
 }

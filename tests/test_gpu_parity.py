@@ -888,3 +888,16 @@ def test_cholesky_blocks(L, n):
     assert abs(ld[0] - np.linalg.slogdet(A[0])[1]) <= n * 1e3 * 2.0 ** -52 * n
     assert info[0] == 0 and [int(info[c]) for c in fails] == [k + 1 for k in fails.values()]
     assert np.all(np.isnan(ld[1:]))
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 128, 191, 200, 450])
+def test_cholesky_solve_blocks(L, n):
+    """Solves at the edges of the 64-row blocks (one block, its neighbour, blocks summed ahead)
+    against LAPACK: |x - x_ref| <= 4 n cond eps |x_ref| for factors of condition 1e3."""
+    A = synth.random_spd(n, 1300 + n, cond=1e3, batch=3)
+    b = np.random.default_rng(n).standard_normal((3, n))
+    Lf = np.stack([np.linalg.cholesky(a) for a in A])
+    x = L.sb_cholesky_solve_dev(dev(Lf), dev(b)).cpu().numpy()
+    for c in range(3):
+        ref = np.linalg.solve(A[c], b[c])
+        assert np.max(np.abs(x[c] - ref)) <= 4 * n * 1e3 * 2.0 ** -52 * np.max(np.abs(ref))
