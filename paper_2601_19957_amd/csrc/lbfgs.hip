@@ -803,8 +803,12 @@ __device__ __forceinline__ void lbfgs_step_one(const LbArgs<T> &a, const int64_t
 // Start s_base + blockIdx.x: a workgroup each.  (Four one-wave starts per
 // workgroup, for d <= 256, measured the same: handing out workgroups is not what
 // a step with few active starts costs.)
+// Two waves per SIMD at least: left alone, the allocator gave the FP64 step of
+// four values a thread and one wave a start (d <= 256) 310 registers, which
+// leave room for one (d = 256, 8192 starts: 85 -> 81 us; 64 uneven problems: 94 ->
+// 88 ms).
 template <typename T, int TPB, int EPT, bool HREG, bool HB = false>
-__global__ __launch_bounds__(TPB) void lbfgs_step_kernel(LbArgs<T> a) {
+__global__ __launch_bounds__(TPB, 2) void lbfgs_step_kernel(LbArgs<T> a) {
   __shared__ T rbuf[2 * BlockRed<TPB, T>::NMAX * (TPB / 64)];
   BlockRed<TPB, T> red{rbuf, 0};
   // the compaction that follows counts from zero; every reader of the
