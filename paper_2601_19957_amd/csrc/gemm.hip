@@ -523,13 +523,14 @@ int launch_quad_gemm(int dtype, const Model &m, const ASrc &a, int64_t M, const 
 // One wave per row: q_k from the tile partials, the family's l, and (if
 // requested) the gradient -sum_k r_k Y_k (mixture) or -((nu+d)/(nu+q)) Y.
 // The scalar part (q_k sums, beta_k - q_k/2, logsumexp, responsibilities)
-// runs in FP64 for every operand type: l carries constants of size
-// ~(d/2) log 2 pi and (1/2) log det P, and the line search compares l values
-// whose difference is far below the FP32 spacing at that magnitude.
+// runs in FP64 for every operand type, component k in lane k: l carries
+// constants of size ~(d/2) log 2 pi and (1/2) log det P, and the line search
+// compares l values whose difference is far below the FP32 spacing at that
+// magnitude.
 template <typename T>
 __global__ __launch_bounds__(256) void finish_kernel(Model m, FinishArgs f) {
   const int64_t M = f.count ? (int64_t)(*f.count) : f.M;
-  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int64_t row = (int64_t)blockIdx.x * 4 + uniform((int)(threadIdx.x >> 6));
   const int lane = threadIdx.x & 63;
   if (row >= M) return;
   const int d = m.d, K = m.K;
@@ -568,13 +569,12 @@ __global__ __launch_bounds__(256) void finish_kernel(Model m, FinishArgs f) {
   }
   // (its gradient written by the contraction: one listed component, r = 1)
   if (f.resp && f.skip1 && __popc(f.skip1[row]) == 1) return;
-  T r[kMaxK];
+  T rl;  // r of component `lane`
   if (f.resp) {  // l and the responsibilities came from the mixture-rows pass
-#pragma unroll
-    for (int k = 0; k < kMaxK; ++k) r[k] = (k < K) ? (T)((const float *)f.resp)[row * K + k] : (T)0;
+    rl = lane < K ? (T)((const float *)f.resp)[row * K + lane] : (T)0;
   } else {
     double lse;
-    mixture_resp<T>(m, qp, f.ntn, lse, r);
+    mixture_resp_wave<T>(K, m.beta, qp, f.ntn, lane, lse, rl);
     if (lane == 0) {
       if (f.logl_f64)
         ((double *)f.logl)[orow] = m.c + lse;
@@ -582,44 +582,82 @@ __global__ __launch_bounds__(256) void finish_kernel(Model m, FinishArgs f) {
         ((T *)f.logl)[orow] = (T)(m.c + lse);
     }
   }
-  if (f.aux && lane < K) {
+  if (f.aux && lane < K) ((T *)f.aux)[row * K + lane] = rl;
+  if (!gout) return;
+  T r[kMaxK];
 #pragma unroll
-    for (int k = 0; k < kMaxK; ++k)
-      if (k == lane) ((T *)f.aux)[row * K + k] = r[k];
-  }
-  if (gout) {
-    // components whose responsibility rounds to zero in T add nothing: their
-    // Y rows are not read (separated mixtures touch one row of K).  16-byte
-    // accesses where the rows allow them (same sums, element by element).
-    constexpr int V = 16 / sizeof(T);
-    typedef T vt __attribute__((ext_vector_type(V)));
-    const bool vec = d % V == 0 && ((uintptr_t)Y % 16) == 0 && ((uintptr_t)gout % 16) == 0;
-    if (vec) {
-      for (int n = lane * V; n < d; n += 64 * V) {
-        vt s;
+  for (int k = 0; k < kMaxK; ++k) r[k] = k < K ? wave_value(rl, k) : (T)0;
+  // components whose responsibility rounds to zero in T add nothing: their
+  // Y rows are not read (separated mixtures touch one row of K).  16-byte
+  // accesses where the rows allow them (same sums, element by element).
+  constexpr int V = 16 / sizeof(T);
+  typedef T vt __attribute__((ext_vector_type(V)));
+  const bool vec = d % V == 0 && ((uintptr_t)Y % 16) == 0 && ((uintptr_t)gout % 16) == 0;
+  if (vec) {
+    for (int n = lane * V; n < d; n += 64 * V) {
+      vt s;
 #pragma unroll
-        for (int e = 0; e < V; ++e) s[e] = 0;
+      for (int e = 0; e < V; ++e) s[e] = 0;
 #pragma unroll
-        for (int k = 0; k < kMaxK; ++k)
-          if (k < K && r[k] != (T)0) {
-            const vt y = *(const vt *)&Y[(size_t)k * d + n];
+      for (int k = 0; k < kMaxK; ++k)
+        if (k < K && r[k] != (T)0) {
+          const vt y = *(const vt *)&Y[(size_t)k * d + n];
 #pragma unroll
-            for (int e = 0; e < V; ++e) s[e] += r[k] * y[e];
-          }
+          for (int e = 0; e < V; ++e) s[e] += r[k] * y[e];
+        }
 #pragma unroll
-        for (int e = 0; e < V; ++e) s[e] = -s[e];
-        *(vt *)&gout[n] = s;
-      }
-    } else {
-      for (int n = lane; n < d; n += 64) {
-        T s = 0;
+      for (int e = 0; e < V; ++e) s[e] = -s[e];
+      *(vt *)&gout[n] = s;
+    }
+  } else {
+    for (int n = lane; n < d; n += 64) {
+      T s = 0;
 #pragma unroll
-        for (int k = 0; k < kMaxK; ++k)
-          if (k < K && r[k] != (T)0) s += r[k] * Y[(size_t)k * d + n];
-        gout[n] = -s;
-      }
+      for (int k = 0; k < kMaxK; ++k)
+        if (k < K && r[k] != (T)0) s += r[k] * Y[(size_t)k * d + n];
+      gout[n] = -s;
     }
   }
+}
+
+// l alone (ray samples), KP lanes per row: no Y is read and no gradient
+// formed, so a wave scores 64 / KP rows at once.  With one wave per row (each
+// exp repeated in all 64 lanes) the vector units bound it: 3.4 -> 0.08 ms for
+// the ray samples of 64 problems (d 8 to 512, K up to 4) in FP64, 110 -> 5 us
+// for those of one d = 64, K = 4 problem.  The bound is now the q read.
+template <typename T, int KP>
+__global__ __launch_bounds__(64) void score_kernel(Model m, FinishArgs f) {
+  const int64_t M = f.count ? (int64_t)(*f.count) : f.M;
+  const int64_t row = ((int64_t)blockIdx.x * 64 + threadIdx.x) / KP;
+  if (row >= M) return;  // (whole groups: the shuffles below stay in the group)
+  const T *qp = (const T *)f.qpart + (size_t)row * m.K * f.ntn;
+  double l;
+  if (m.family == SB_FAMILY_STUDENT_T) {
+    double q = 0;
+    for (int t = 0; t < f.ntn; ++t) q += (double)qp[t];
+    l = m.c + m.beta[0] - 0.5 * (m.nu + (double)m.d) * log1p(q / m.nu);
+  } else {
+    l = m.c + mixture_lse_group<KP>(m.K, m.beta, qp, f.ntn);
+  }
+  if (threadIdx.x % KP != 0) return;
+  const int64_t orow = f.outmap ? (int64_t)f.outmap[row] : row;
+  if (f.logl_f64)
+    ((double *)f.logl)[orow] = l;
+  else
+    ((T *)f.logl)[orow] = (T)l;
+}
+
+template <typename T>
+static void launch_score(const Model &m, const FinishArgs &f, hipStream_t s) {
+#define SB_SCORE(KP)                                                                          \
+  hipLaunchKernelGGL((score_kernel<T, KP>), dim3((unsigned)ceil_div(f.M, 64 / KP)), dim3(64), 0, s, \
+                     m, f)
+  if (m.K == 1) SB_SCORE(1);
+  else if (m.K == 2) SB_SCORE(2);
+  else if (m.K <= 4) SB_SCORE(4);
+  else if (m.K <= 8) SB_SCORE(8);
+  else SB_SCORE(16);
+#undef SB_SCORE
 }
 
 // Mixture rows (FP32 operands), one thread per row: l = c + logsumexp_k
@@ -757,8 +795,7 @@ __global__ __launch_bounds__(256) void mixture_screen_kernel(Model m, ScreenArgs
       }
     }
     // (the butterfly leaves the same sum in every lane: the decision is uniform)
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) dd += __shfl_xor(dd, o, 64);
+    dd = wave_sum(dd);
     const double D = sqrt((double)dd * (1.0 + screen_rq(d))) * (1.0 + 0x1p-40);
     double Lk = 0.0, Uk = 0.0, hi = -INFINITY;
     if (act) {
@@ -769,9 +806,7 @@ __global__ __launch_bounds__(256) void mixture_screen_kernel(Model m, ScreenArgs
     }
     // largest upper end over the components (fmax drops a NaN: the maximum of
     // the others, as a running fmax over k would give)
-    double mx = hi;
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o, 64));
+    const double mx = wave_max(hi);
     const bool kb = act && !(m.beta[lane] - 0.5 * Lk * Lk < mx - kScreenGap);
     keep = (uint32_t)__ballot(kb);
     // dropped: the widened bounds now hold at x
@@ -806,9 +841,7 @@ __global__ __launch_bounds__(256) void mixture_screen_kernel(Model m, ScreenArgs
   }
 #pragma unroll
   for (int k = 0; k < kMaxK; ++k)
-    if (k < K && ((keep >> k) & 1u))
-#pragma unroll
-      for (int o = 32; o >= 1; o >>= 1) nrm[k] += __shfl_xor(nrm[k], o, 64);
+    if (k < K && ((keep >> k) & 1u)) nrm[k] = wave_sum(nrm[k]);
 #pragma unroll
   for (int k = 0; k < kMaxK; ++k)
     if (k == lane && k < K) a.nrm[row * K + k] = nrm[k];
@@ -1211,7 +1244,12 @@ int launch_finish(int dtype, const Model &m, const FinishArgs &f, hipStream_t s)
   }
   dim3 grid((unsigned)ceil_div(f.M, 4));
   if (grid.x == 0) return SB_OK;
-  if (dtype == DT_F64)
+  if (!f.grad && !f.aux && !f.resp) {
+    if (dtype == DT_F64)
+      launch_score<double>(m, f, s);
+    else
+      launch_score<float>(m, f, s);
+  } else if (dtype == DT_F64)
     hipLaunchKernelGGL(finish_kernel<double>, grid, dim3(256), 0, s, m, f);
   else
     hipLaunchKernelGGL(finish_kernel<float>, grid, dim3(256), 0, s, m, f);
@@ -1605,7 +1643,7 @@ __device__ inline int find_seg(const GSeg *segs, int n, int64_t r) {
 // gradient -> grad + goff[r] (or r * ldg); aux -> aux + r * auxs.
 template <typename T>
 __global__ __launch_bounds__(256) void finish_group_kernel(BatchDev b, FinishGroupArgs f) {
-  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int64_t row = (int64_t)blockIdx.x * 4 + uniform((int)(threadIdx.x >> 6));
   const int lane = threadIdx.x & 63;
   if (row >= f.nrows) return;
   const int sgi = f.rowseg ? f.rowseg[row] : find_seg(f.segs, f.nseg, row);
@@ -1640,69 +1678,88 @@ __global__ __launch_bounds__(256) void finish_group_kernel(BatchDev b, FinishGro
     }
     return;
   }
-  double a[kMaxK];
-  double mx = -INFINITY;
-#pragma unroll
-  for (int k = 0; k < kMaxK; ++k) {
-    if (k < K) {
-      double q = 0;
-      for (int t = 0; t < ntn; ++t) q += (double)qp[k * ntn + t];
-      a[k] = beta[k] - 0.5 * q;
-      mx = fmax(mx, a[k]);
-    }
-  }
   double lse;
-  if (K == 1) {
-    lse = a[0];
-  } else {
-    double ssum = 0;
-#pragma unroll
-    for (int k = 0; k < kMaxK; ++k)
-      if (k < K) ssum += exp(a[k] - mx);
-    lse = mx + log(ssum);
-  }
+  T resp;  // r of component `lane`
+  mixture_resp_wave<T>(K, beta, qp, ntn, lane, lse, resp);
   put_l(pr.c + lse);
+  if (f.aux && lane < K) ((T *)f.aux)[row * f.auxs + lane] = resp;
+  if (!gout) return;
   T r[kMaxK];
 #pragma unroll
-  for (int k = 0; k < kMaxK; ++k) r[k] = (k < K) ? (K == 1 ? (T)1 : (T)exp(a[k] - lse)) : (T)0;
-  if (f.aux && lane < K) {
+  for (int k = 0; k < kMaxK; ++k) r[k] = k < K ? wave_value(resp, k) : (T)0;
+  // components whose responsibility rounds to zero in T add nothing: their
+  // Y rows are not read (separated mixtures touch one row of K).  16-byte
+  // accesses where the rows allow them (same sums, element by element).
+  constexpr int V = 16 / sizeof(T);
+  typedef T vt __attribute__((ext_vector_type(V)));
+  const bool vec = d % V == 0 && ((uintptr_t)Y % 16) == 0 && ((uintptr_t)gout % 16) == 0;
+  if (vec) {
+    for (int n = lane * V; n < d; n += 64 * V) {
+      vt s;
 #pragma unroll
-    for (int k = 0; k < kMaxK; ++k)
-      if (k == lane) ((T *)f.aux)[row * f.auxs + k] = r[k];
-  }
-  if (gout) {
-    // components whose responsibility rounds to zero in T add nothing: their
-    // Y rows are not read (separated mixtures touch one row of K).  16-byte
-    // accesses where the rows allow them (same sums, element by element).
-    constexpr int V = 16 / sizeof(T);
-    typedef T vt __attribute__((ext_vector_type(V)));
-    const bool vec = d % V == 0 && ((uintptr_t)Y % 16) == 0 && ((uintptr_t)gout % 16) == 0;
-    if (vec) {
-      for (int n = lane * V; n < d; n += 64 * V) {
-        vt s;
+      for (int e = 0; e < V; ++e) s[e] = 0;
 #pragma unroll
-        for (int e = 0; e < V; ++e) s[e] = 0;
+      for (int k = 0; k < kMaxK; ++k)
+        if (k < K && r[k] != (T)0) {
+          const vt y = *(const vt *)&Y[(size_t)k * d + n];
 #pragma unroll
-        for (int k = 0; k < kMaxK; ++k)
-          if (k < K && r[k] != (T)0) {
-            const vt y = *(const vt *)&Y[(size_t)k * d + n];
+          for (int e = 0; e < V; ++e) s[e] += r[k] * y[e];
+        }
 #pragma unroll
-            for (int e = 0; e < V; ++e) s[e] += r[k] * y[e];
-          }
+      for (int e = 0; e < V; ++e) s[e] = -s[e];
+      *(vt *)&gout[n] = s;
+    }
+  } else {
+    for (int n = lane; n < d; n += 64) {
+      T s = 0;
 #pragma unroll
-        for (int e = 0; e < V; ++e) s[e] = -s[e];
-        *(vt *)&gout[n] = s;
-      }
-    } else {
-      for (int n = lane; n < d; n += 64) {
-        T s = 0;
-#pragma unroll
-        for (int k = 0; k < kMaxK; ++k)
-          if (k < K && r[k] != (T)0) s += r[k] * Y[(size_t)k * d + n];
-        gout[n] = -s;
-      }
+      for (int k = 0; k < kMaxK; ++k)
+        if (k < K && r[k] != (T)0) s += r[k] * Y[(size_t)k * d + n];
+      gout[n] = -s;
     }
   }
+}
+
+// score_kernel for a batch: a problem's K fills part of the KP lanes.
+template <typename T, int KP>
+__global__ __launch_bounds__(64) void score_group_kernel(BatchDev b, FinishGroupArgs f) {
+  const int64_t row = ((int64_t)blockIdx.x * 64 + threadIdx.x) / KP;
+  if (row >= f.nrows) return;
+  const int sgi = f.rowseg ? f.rowseg[row] : find_seg(f.segs, f.nseg, row);
+  const GSeg sg = f.segs[sgi];
+  const int64_t rows = f.counts ? (int64_t)f.counts[sgi] : (int64_t)sg.rows;
+  if (row - sg.row0 >= rows) return;
+  const BatchProb &pr = b.probs[sg.prob];
+  const int K = pr.K, ntn = (pr.dp + f.bn - 1) / f.bn;
+  const T *qp = (const T *)f.qpart + sg.qoff + (row - sg.row0) * (int64_t)K * ntn;
+  const double *beta = b.beta + pr.beta_off;
+  double l;
+  if (pr.family == SB_FAMILY_STUDENT_T) {
+    double q = 0;
+    for (int t = 0; t < ntn; ++t) q += (double)qp[t];
+    const double nd = pr.nu + (double)pr.d;
+    l = pr.c + beta[0] - 0.5 * nd * log1p(q / pr.nu);
+  } else {
+    l = pr.c + mixture_lse_group<KP>(K, beta, qp, ntn);
+  }
+  if (threadIdx.x % KP != 0) return;
+  if (f.F)
+    f.F[f.fidx ? (int64_t)f.fidx[row] : row] = l;
+  else
+    ((T *)f.lout)[row] = (T)l;
+}
+
+template <typename T>
+static void launch_score_group(const BatchDev &b, const FinishGroupArgs &f, hipStream_t s) {
+#define SB_SCORE(KP)                                                                       \
+  hipLaunchKernelGGL((score_group_kernel<T, KP>), dim3((unsigned)ceil_div(f.nrows, 64 / KP)), \
+                     dim3(64), 0, s, b, f)
+  if (b.K_max <= 1) SB_SCORE(1);
+  else if (b.K_max == 2) SB_SCORE(2);
+  else if (b.K_max <= 4) SB_SCORE(4);
+  else if (b.K_max <= 8) SB_SCORE(8);
+  else SB_SCORE(16);
+#undef SB_SCORE
 }
 
 int launch_finish_group(int dtype, const BatchDev &b, const FinishGroupArgs &f, hipStream_t s) {
@@ -1712,7 +1769,12 @@ int launch_finish_group(int dtype, const BatchDev &b, const FinishGroupArgs &f, 
   }
   if (f.nrows <= 0 || f.nseg <= 0) return SB_OK;
   dim3 grid((unsigned)ceil_div(f.nrows, 4));
-  if (dtype == DT_F64)
+  if (!f.grad && !f.aux) {
+    if (dtype == DT_F64)
+      launch_score_group<double>(b, f, s);
+    else
+      launch_score_group<float>(b, f, s);
+  } else if (dtype == DT_F64)
     hipLaunchKernelGGL(finish_group_kernel<double>, grid, dim3(256), 0, s, b, f);
   else
     hipLaunchKernelGGL(finish_group_kernel<float>, grid, dim3(256), 0, s, b, f);

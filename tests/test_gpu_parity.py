@@ -846,6 +846,25 @@ def test_quadform_edges(L, d, tile, monkeypatch):
             assert bool(((qk - (delta * Y).sum(1)).abs() <= 4 * (d + 1) * u * qmag).all())
 
 
+@pytest.mark.parametrize("B", [1, 31, 65, 130])
+@pytest.mark.parametrize("K", [1, 2, 3, 5, 9, 16])
+def test_scores_alone(L, K, B):
+    """l without the gradient (K lanes rounded up to a power of two per row, 64 / K rows per
+    wave) is the l that comes with it (one wave per row): the same terms in the same order, so
+    the same bits; and it is the log-sum-exp of the exact quadratic forms."""
+    d = 130
+    rng = np.random.Generator(np.random.PCG64(900 + K))
+    prob = synth.gaussian_mixture(rng, d, K, -2.0, 2.0, 0.1, 1.0, 0.0, box_half=12.0)
+    m = L.DeviceModel(prob, low_precision=True)
+    X = dev(prob.mu[rng.integers(K, size=B)] + 0.3 * rng.standard_normal((B, d)))
+    lo, _ = O.logl(prob, X.cpu().numpy())
+    assert rel(L.sb_logl_grad_dev(m, X, grad=False).cpu().numpy(), lo) < 1e-10
+    for dt in (torch.float64, torch.float32):
+        alone = L.sb_logl_grad_dev(m, X.to(dt), grad=False)
+        both, _ = L.sb_logl_grad_dev(m, X.to(dt))
+        assert torch.equal(alone, both)
+
+
 @pytest.mark.parametrize("d", [3, 67, 129, 255, 509, 1021])
 def test_lbfgs_rows_of_any_alignment(L, d):
     """L-BFGS from starts whose vectors begin at any element and end inside a thread's chunk
