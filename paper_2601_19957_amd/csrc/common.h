@@ -51,7 +51,7 @@ template <int CTRL>
 __device__ inline int dpp_mov(int v) {
   return __builtin_amdgcn_mov_dpp(v, CTRL, 0xf, 0xf, true);
 }
-constexpr int kDppRor8 = 0x128, kDppRor4 = 0x124, kDppXor2 = 0x4e, kDppXor1 = 0xb1, kDppHalfMirror = 0x141;
+constexpr int kDppRor8 = 0x128, kDppRor4 = 0x124, kDppXor2 = 0x4e, kDppXor1 = 0xb1, kDppHalfMirror = 0x141, kDppShl1 = 0x101;
 template <int CTRL>
 __device__ inline float dpp_val(float v) {
   return __int_as_float(dpp_mov<CTRL>(__float_as_int(v)));
@@ -188,6 +188,15 @@ __device__ inline int64_t uniform(int64_t v) {
   const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(uint64_t)v);
   const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)((uint64_t)v >> 32));
   return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+
+// Lane k's value (k uniform), in scalar registers.
+__device__ inline float wave_value(float v, int k) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), k));
+}
+__device__ inline double wave_value(double v, int k) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), k),
+                          __builtin_amdgcn_readlane(__double2loint(v), k));
 }
 
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }

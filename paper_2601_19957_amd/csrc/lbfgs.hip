@@ -252,10 +252,6 @@ struct HistReg {
 #pragma unroll
     for (int e = 0; e < EPT; ++e) v[j][e] = x[e];
   }
-  __device__ void zero(int j) {
-#pragma unroll
-    for (int e = 0; e < EPT; ++e) v[j][e] = 0;
-  }
   __device__ void move(int j, int k) {
 #pragma unroll
     for (int e = 0; e < EPT; ++e) v[j][e] = v[k][e];
@@ -274,10 +270,6 @@ struct HistReg<float, EPT, true> {
     for (int q = 0; q < EPT / 2; ++q)
       w[j][q] = (__builtin_bit_cast(uint32_t, x[2 * q]) >> 16) |
                 (__builtin_bit_cast(uint32_t, x[2 * q + 1]) & 0xffff0000u);
-  }
-  __device__ void zero(int j) {
-#pragma unroll
-    for (int q = 0; q < EPT / 2; ++q) w[j][q] = 0;
   }
   __device__ void move(int j, int k) {
 #pragma unroll
@@ -325,43 +317,51 @@ struct BlockRed {
   }
 };
 
-// Two-loop recursion on register-resident history (logical order, oldest
-// first).  q <- g; backward: alpha_j = rho_j s_j^T q, q -= alpha_j y_j;
-// r = gamma q, gamma = s^T y / y^T y of the newest pair; forward:
-// beta = rho_j y_j^T r, r += (alpha_j - beta) s_j; returns p = -r.
+// Two-loop recursion on register-resident history.  Sets 1 to n hold pairs
+// from newer to older, set 0 one more: the newest of all, or (old0) the
+// oldest, or (cnt == n) nothing; rho of set j is in lane j.  q <- g; backward:
+// alpha_j = rho_j s_j^T q, q -= alpha_j y_j; r = gamma q, gamma = s^T y / y^T y
+// of the newest pair; forward: beta = rho_j y_j^T r, r += (alpha_j - beta) s_j;
+// returns p = -r.
 template <typename T, int TPB, int EPT, class H>
-__device__ inline void two_loop(const H &Sr, const H &Yr, const T (&rh)[kMaxHist], T gamma,
-                                int cnt, const T (&g)[EPT], T (&p)[EPT], BlockRed<TPB, T> &red) {
+__device__ inline void two_loop(const H &Sr, const H &Yr, T rh, T gamma, int cnt, int n, bool old0,
+                                const T (&g)[EPT], T (&p)[EPT], BlockRed<TPB, T> &red) {
   T q[EPT], al[kMaxHist];
 #pragma unroll
   for (int e = 0; e < EPT; ++e) q[e] = g[e];
+  auto back = [&](int j) {
+    T dd = 0;
 #pragma unroll
-  for (int j = kMaxHist - 1; j >= 0; --j) {
-    if (j < cnt) {
-      T dd = 0;
+    for (int e = 0; e < EPT; ++e) dd += Sr.get(j, e) * q[e];
+    dd = red.sum(dd);
+    al[j] = wave_value(rh, j) * dd;
 #pragma unroll
-      for (int e = 0; e < EPT; ++e) dd += Sr.get(j, e) * q[e];
-      dd = red.sum(dd);
-      al[j] = rh[j] * dd;
+    for (int e = 0; e < EPT; ++e) q[e] -= al[j] * Yr.get(j, e);
+  };
+  auto fwd = [&](int j) {
+    T bb = 0;
 #pragma unroll
-      for (int e = 0; e < EPT; ++e) q[e] -= al[j] * Yr.get(j, e);
-    } else {
+    for (int e = 0; e < EPT; ++e) bb += Yr.get(j, e) * q[e];
+    bb = wave_value(rh, j) * red.sum(bb);
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) q[e] += (al[j] - bb) * Sr.get(j, e);
+  };
+  al[0] = 0;
+  if (cnt > n && !old0) back(0);
+#pragma unroll
+  for (int j = 1; j < kMaxHist; ++j)
+    if (j <= n)
+      back(j);
+    else
       al[j] = 0;
-    }
-  }
+  if (cnt > n && old0) back(0);
 #pragma unroll
   for (int e = 0; e < EPT; ++e) q[e] *= gamma;
+  if (cnt > n && old0) fwd(0);
 #pragma unroll
-  for (int j = 0; j < kMaxHist; ++j) {
-    if (j < cnt) {
-      T bb = 0;
-#pragma unroll
-      for (int e = 0; e < EPT; ++e) bb += Yr.get(j, e) * q[e];
-      bb = rh[j] * red.sum(bb);
-#pragma unroll
-      for (int e = 0; e < EPT; ++e) q[e] += (al[j] - bb) * Sr.get(j, e);
-    }
-  }
+  for (int j = kMaxHist - 1; j >= 1; --j)
+    if (j <= n) fwd(j);
+  if (cnt > n && !old0) fwd(0);
 #pragma unroll
   for (int e = 0; e < EPT; ++e) p[e] = -q[e];
 }
@@ -482,6 +482,7 @@ __device__ __forceinline__ void lbfgs_step_one(const LbArgs<T> &a, const int64_t
   const int ls_v = a.ls[s];
   const int dv_v = a.vdim ? a.vdim[s] : a.d;
   const int64_t vo_v = a.voff ? a.voff[s] : (int64_t)s * a.d;
+  const int sp_v = a.sprob ? a.sprob[s] : 0;
   const int status = uniform(status_v), phase = uniform(phase_v), ls_s = uniform(ls_v);
   int cur = uniform(cur_v), cnt = uniform(cnt_v), head = uniform(head_v), it = uniform(it_v);
   const int dv = uniform(dv_v);
@@ -498,9 +499,10 @@ __device__ __forceinline__ void lbfgs_step_one(const LbArgs<T> &a, const int64_t
   T tol = a.tol;
   int max_iter = a.max_iter;
   if (a.sprob) {
-    const int p = uniform(a.sprob[s]);
+    // (read with the vectors below: the first use is the convergence test)
+    const int p = uniform(sp_v);
     tol = (T)a.ptol[p];
-    max_iter = uniform(a.pmaxit[p]);
+    max_iter = a.pmaxit[p];
   }
   const double lcur = cur ? f1 : f0;
 
@@ -582,30 +584,32 @@ __device__ __forceinline__ void lbfgs_step_one(const LbArgs<T> &a, const int64_t
     cnt = 0;
     head = 0;
   }
-  // history in logical order (loads issued before the reductions below).
-  // With the ring full, the oldest pair is evicted when the curvature test
-  // passes, so its load waits for that test and happens only when it fails.
-  constexpr int MH = HREG ? kMaxHist : 1;
+  // History by age (loads issued before the reductions below): pair j, j = 0
+  // the newest, sits in register set j + 1, where it belongs once this step's
+  // pair is in set 0; the pair that this evicts (the ring full) is not read.
+  // rho of set j is in lane j, for the recursion to take, and of y^T y only the
+  // newest pair's is needed: as sixteen values equal in every lane the two held
+  // 32 registers in FP64, and a set chosen at run time for the new pair, with
+  // the sets moved down for it, 40 to 80 more.  Should the curvature test refuse the pair, set 0
+  // takes the oldest pair where the ring is full, and is left out otherwise.
   constexpr bool PK = HB && EPT % 2 == 0;
   HistReg<T, EPT, PK> Sr, Yr;
-  T rh[MH], yyr[MH];
-  const bool defer_oldest = (mode == M_ACCEPT && cnt == m);
-  const int slot0 = head >= cnt ? head - cnt : head - cnt + m;  // ring slot of the oldest pair
+  T rh = 0, yynew = 0;
+  const int lane = tid & 63;
+  int nset = 0;
+  bool old0 = false;
   const size_t hist0 = (size_t)m * vo;
   const T *rho_s = a.rho + (size_t)s * m, *yy_s = a.yy + (size_t)s * m;
+  auto slot = [&](int age) { return head - 1 - age >= 0 ? head - 1 - age : head - 1 - age + m; };
   if constexpr (HREG) {
     // packed BF16 history in whole chunks: the raw words go straight
     // to registers, every load issued before the first use
     const bool raw = PK && i0 + EPT <= d;
+    if (mode == M_ACCEPT) nset = cnt < m ? cnt : m - 1;
 #pragma unroll
-    for (int j = 0; j < kMaxHist; ++j) {
-      rh[j] = 0;
-      yyr[j] = 0;
-      Sr.zero(j);
-      Yr.zero(j);
-      if (mode == M_ACCEPT && j < cnt && !(j == 0 && defer_oldest)) {
-        const int ph = slot0 + j < m ? slot0 + j : slot0 + j - m;
-        const size_t off = hist0 + (uint32_t)(ph * d);  // (m, d <= 32, 4096)
+    for (int j = 1; j < kMaxHist; ++j) {
+      if (j <= nset) {
+        const size_t off = hist0 + (uint32_t)(slot(j - 1) * d);  // (m, d <= 32, 4096)
         if constexpr (PK) {
           if (raw) {
             hload_raw_nt<EPT>((const uint16_t *)a.S + off, i0, Sr.w[j]);
@@ -621,9 +625,11 @@ __device__ __forceinline__ void lbfgs_step_one(const LbArgs<T> &a, const int64_t
           ring_load<T, EPT, HB>(a.S, off, i0, d, Sr.v[j]);
           ring_load<T, EPT, HB>(a.Yh, off, i0, d, Yr.v[j]);
         }
-        rh[j] = rho_s[ph];
-        yyr[j] = yy_s[ph];
       }
+    }
+    if (mode == M_ACCEPT && cnt > 0) {
+      if (lane >= 1 && lane <= nset) rh = rho_s[slot(lane - 1)];
+      yynew = yy_s[slot(0)];
     }
   }
   // streamed history: the pair pushed in this step stays in registers
@@ -642,51 +648,37 @@ __device__ __forceinline__ void lbfgs_step_one(const LbArgs<T> &a, const int64_t
     cur = newcur;
     ++it;
     if (uniform(sy > (T)1e-10 * sqrt(ss) * sqrt(yy))) {
+      const T rnew = (T)1 / sy;
       // store the pair in the ring and append it to the logical history
       ring_store<T, EPT, HB>(a.S, (size_t)m * vo + (size_t)head * d, i0, d, sv);
       ring_store<T, EPT, HB>(a.Yh, (size_t)m * vo + (size_t)head * d, i0, d, yv);
       if (tid == 0) {
-        a.rho[(size_t)s * m + head] = (T)1 / sy;
+        a.rho[(size_t)s * m + head] = rnew;
         a.yy[(size_t)s * m + head] = yy;
       }
       const bool full = (cnt == m);
       if constexpr (HREG) {
-        if (full) {
-#pragma unroll
-          for (int j = 0; j < kMaxHist - 1; ++j) {
-            Sr.move(j, j + 1);
-            Yr.move(j, j + 1);
-            rh[j] = rh[j + 1];
-            yyr[j] = yyr[j + 1];
-          }
-        }
-        const int pos = full ? m - 1 : cnt;
-#pragma unroll
-        for (int j = 0; j < kMaxHist; ++j) {
-          if (j == pos) {
-            Sr.set(j, sv);
-            Yr.set(j, yv);
-            rh[j] = (T)1 / sy;
-            yyr[j] = yy;
-          }
-        }
+        Sr.set(0, sv);
+        Yr.set(0, yv);
+        if (lane == 0) rh = rnew;
+        yynew = yy;
       } else {
         reg_new = true;
-        r_new = (T)1 / sy;
+        r_new = rnew;
         yy_new = yy;
       }
       head = head + 1 < m ? head + 1 : 0;
       cnt = full ? m : cnt + 1;
-    } else if (defer_oldest) {
+    } else if (cnt == m) {
       if constexpr (HREG) {
-        // pair kept out: the oldest pair (ring slot head) stays in the history
+        // (its slot is the one that the refused pair would have taken)
+        old0 = true;
         T t[EPT];
-        ring_load<T, EPT, HB>(a.S, (size_t)m * vo + (size_t)head * d, i0, d, t);
+        ring_load<T, EPT, HB>(a.S, hist0 + (size_t)head * d, i0, d, t);
         Sr.set(0, t);
-        ring_load<T, EPT, HB>(a.Yh, (size_t)m * vo + (size_t)head * d, i0, d, t);
+        ring_load<T, EPT, HB>(a.Yh, hist0 + (size_t)head * d, i0, d, t);
         Yr.set(0, t);
-        rh[0] = a.rho[(size_t)s * m + head];
-        yyr[0] = a.yy[(size_t)s * m + head];
+        if (lane == 0) rh = rho_s[head];
       }
     }
   }
@@ -710,7 +702,7 @@ __device__ __forceinline__ void lbfgs_step_one(const LbArgs<T> &a, const int64_t
     newst = ST_DEAD;
   else if (uniform(gn <= tol))
     newst = ST_CONVERGED;
-  else if (it >= max_iter)
+  else if (it >= uniform(max_iter))
     newst = ST_MAXITER;
   if (newst != ST_ACTIVE) {
     if (tid == 0) {
@@ -732,14 +724,9 @@ __device__ __forceinline__ void lbfgs_step_one(const LbArgs<T> &a, const int64_t
   bool sd = (cnt == 0);
   if (!sd) {
     // gamma = s^T y / y^T y of the newest pair (logical index cnt - 1)
-    T rnew = 0, yynew = 1;
+    T rnew;
     if constexpr (HREG) {
-#pragma unroll
-      for (int j = 0; j < kMaxHist; ++j)
-        if (j == cnt - 1) {
-          rnew = rh[j];
-          yynew = yyr[j];
-        }
+      rnew = wave_value(rh, nset > 0 && (old0 || cnt == nset) ? 1 : 0);
     } else {
       if (reg_new) {
         rnew = r_new;
@@ -752,7 +739,7 @@ __device__ __forceinline__ void lbfgs_step_one(const LbArgs<T> &a, const int64_t
     }
     const T gamma = ((T)1 / rnew) / yynew;
     if constexpr (HREG)
-      two_loop<T, TPB, EPT>(Sr, Yr, rh, gamma, cnt, g, p, red);
+      two_loop<T, TPB, EPT>(Sr, Yr, rh, gamma, cnt, nset, old0, g, p, red);
     else
       two_loop_stream<T, TPB, EPT>(a.S + (size_t)m * vo, a.Yh + (size_t)m * vo,
                                    a.rho + (size_t)s * m, d, m, head, cnt, reg_new, sv, yv,
@@ -803,10 +790,10 @@ __device__ __forceinline__ void lbfgs_step_one(const LbArgs<T> &a, const int64_t
 // Start s_base + blockIdx.x: a workgroup each.  (Four one-wave starts per
 // workgroup, for d <= 256, measured the same: handing out workgroups is not what
 // a step with few active starts costs.)
-// Two waves per SIMD at least: left alone, the allocator gave the FP64 step of
-// four values a thread and one wave a start (d <= 256) 310 registers, which
-// leave room for one (d = 256, 8192 starts: 85 -> 81 us; 64 uneven problems: 94 ->
-// 88 ms).
+// Two waves per SIMD at least, which the FP64 step of up to 4 values a thread
+// has without spilling (190 registers; with the history in logical order 310,
+// or 256 and spilled).  FP64, m = 8: d = 256, 8192 starts 81 -> 73 us (21
+// vectors moved: 69 us at the copy rate); d = 30, 32768 starts 97 -> 59 us.
 template <typename T, int TPB, int EPT, bool HREG, bool HB = false>
 __global__ __launch_bounds__(TPB, 2) void lbfgs_step_kernel(LbArgs<T> a) {
   __shared__ T rbuf[2 * BlockRed<TPB, T>::NMAX * (TPB / 64)];
@@ -892,21 +879,15 @@ __global__ __launch_bounds__(TPB) void two_loop_kernel(int d, int m, const int32
     return;
   }
   HistReg<T, EPT, false> Sr, Yr;
-  T rh[kMaxHist], g[EPT], p[EPT];
+  T rh = 0, g[EPT], p[EPT];
   T gamma = 1;
   const int i0 = tid * EPT;
   vload<T, EPT>(G + (size_t)b * d, i0, d, g);
 #pragma unroll
   for (int j = 0; j < kMaxHist; ++j) {
-    rh[j] = 0;
     if (j < cnt) {
-      vload<T, EPT>(S + ((size_t)b * m + j) * d, i0, d, Sr.v[j]);
-      vload<T, EPT>(Y + ((size_t)b * m + j) * d, i0, d, Yr.v[j]);
-    } else {
-      Sr.zero(j);
-      Yr.zero(j);
-    }
-    if (j < cnt) {
+      vload<T, EPT>(S + ((size_t)b * m + (cnt - 1 - j)) * d, i0, d, Sr.v[j]);
+      vload<T, EPT>(Y + ((size_t)b * m + (cnt - 1 - j)) * d, i0, d, Yr.v[j]);
       T v2[2] = {0, 0};
 #pragma unroll
       for (int e = 0; e < EPT; ++e) {
@@ -914,11 +895,11 @@ __global__ __launch_bounds__(TPB) void two_loop_kernel(int d, int m, const int32
         v2[1] += Yr.v[j][e] * Yr.v[j][e];
       }
       red.template reduce<2, false>(v2);
-      rh[j] = (T)1 / v2[0];
-      if (j == cnt - 1) gamma = v2[0] / v2[1];
+      if ((tid & 63) == j) rh = (T)1 / v2[0];
+      if (j == 0) gamma = v2[0] / v2[1];
     }
   }
-  two_loop<T, TPB, EPT>(Sr, Yr, rh, gamma, cnt, g, p, red);
+  two_loop<T, TPB, EPT>(Sr, Yr, rh, gamma, cnt, cnt > 0 ? cnt - 1 : 0, false, g, p, red);
   vstore<T, EPT>(P + (size_t)b * d, i0, d, p);
 }
 

@@ -46,14 +46,6 @@ __device__ inline void mixture_resp(const Model &m, const T *qp, int ntn, double
 // mixture_resp.  lane_resp: lane k's r_k (zero past K).  With one component
 // per lane the row waits for ntn loads and two exps instead of K ntn and 2 K.
 template <typename T>
-__device__ inline T wave_value(T v, int k) {  // lane k's value, in scalar registers
-  if constexpr (sizeof(T) == 8)
-    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), k),
-                            __builtin_amdgcn_readlane(__double2loint(v), k));
-  else
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), k));
-}
-template <typename T>
 __device__ inline void mixture_resp_wave(int K, const double *beta, const T *qp, int ntn, int lane,
                                          double &lse, T &lane_resp) {
   const bool act = lane < K;

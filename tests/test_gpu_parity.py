@@ -846,6 +846,22 @@ def test_quadform_edges(L, d, tile, monkeypatch):
             assert bool(((qk - (delta * Y).sum(1)).abs() <= 4 * (d + 1) * u * qmag).all())
 
 
+@pytest.mark.parametrize("m", [2, 3, 5])
+def test_lbfgs_refused_pairs(L, m):
+    """FP64, short memories on the heavy-tailed t: the curvature test refuses pairs while the
+    ring fills and (m = 2) with it full, where the oldest pair stays in the history beside
+    newer ones.  The points after 20 accepted steps are the oracle's up to rounding order (its
+    own paths move by at most 1.3e-11 relative under 1e-15 perturbations of the starts)."""
+    prob = PROBLEMS["t_d70"]()
+    X0 = synth.points_near_modes(prob, 16, 91, scale=2.0)
+    x = L.sb_lbfgs_dev(L.DeviceModel(prob), dev(X0), m=m, max_iter=20,
+                       grad_tol=1e-14)["x"].cpu().numpy()
+    op = O.OracleProblem(prob)
+    for s in range(16):
+        r = O.lbfgs(prob, X0[s], m=m, max_iter=20, grad_tol=1e-14, op=op)
+        assert absmax(x[s] - r["x"]) / max(1.0, absmax(r["x"])) < 1e-8, s
+
+
 @pytest.mark.parametrize("B", [1, 31, 65, 130])
 @pytest.mark.parametrize("K", [1, 2, 3, 5, 9, 16])
 def test_scores_alone(L, K, B):
