@@ -405,6 +405,14 @@ int launch_lbfgs_step(const LbfgsBuffers &b, int max_iter, double grad_tol, hipS
 // length at most d_class (batches sorted by dimension launch once per class).
 int launch_lbfgs_step_range(const LbfgsBuffers &b, int64_t s_begin, int64_t count, int d_class,
                             double grad_tol, int max_iter, hipStream_t s);
+// Small FP64 problems: up to n_steps iterations of every start (step and
+// evaluation), continued by the next launch up to max_steps in all.  After
+// launch_lbfgs_init and the first evaluation; count then holds the largest
+// number of steps any start needs as far as known (more than the steps issued
+// while one is active), evals the evaluations.
+bool lbfgs_bulk_ok(const LbfgsBuffers &b, const Model &m);
+int launch_lbfgs_bulk(const LbfgsBuffers &b, const Model &m, int max_iter, double grad_tol,
+                      int n_steps, int max_steps, hipStream_t s);
 int launch_compact(const LbfgsBuffers &b, hipStream_t s);
 int launch_lbfgs_gather(const LbfgsBuffers &b, void *X, void *logl, bool logl_f64, void *grad,
                         int32_t *status, int32_t *iters, hipStream_t s);
@@ -441,7 +449,8 @@ struct BlockKey {
   DevProblem P;
   sb_config cfg;
   double tol;
-  int32_t max_iter, blk, dtype, gemm_dtype, two_stage, screen, grad_direct, hist_bf16;
+  int32_t max_iter, blk, dtype, gemm_dtype, two_stage, screen, grad_direct, hist_bf16,
+      one_launch;
   TileCfg tile, tile1, tile2;
 };
 

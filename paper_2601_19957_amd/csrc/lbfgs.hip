@@ -20,6 +20,7 @@
 // the recursion with workgroup reductions for the dot products.
 #include <algorithm>
 
+#include "fused_tile.h"
 #include "internal.h"
 
 namespace sb {
@@ -462,15 +463,16 @@ __device__ __forceinline__ void two_loop_stream(const T *Sb, const T *Yb, const 
   for (int e = 0; e < EPT; ++e) p[e] = -q[e];
 }
 
-// One step of start s (the whole workgroup; every branch is uniform in s).
-// HREG: the history is held in registers (m <= kMaxHist); otherwise it stays
-// in memory and two_loop_stream reads it (m <= kMaxMem).  HB (FP32, HREG):
-// the ring holds BF16 pairs (s and y rounded to BF16 when formed).
+// One step of start s by its TPB threads, tid the thread's index among them
+// (every branch is uniform in s).  Returns the row of the trial point to be
+// evaluated, or -1 when the start has stopped.  HREG: the history is held in
+// registers (m <= kMaxHist); otherwise it stays in memory and two_loop_stream
+// reads it (m <= kMaxMem).  HB (FP32, HREG): the ring holds BF16 pairs (s and y
+// rounded to BF16 when formed).
 template <typename T, int TPB, int EPT, bool HREG, bool HB = false>
-__device__ __forceinline__ void lbfgs_step_one(const LbArgs<T> &a, const int64_t s,
-                                               BlockRed<TPB, T> &red) {
+__device__ __forceinline__ int32_t lbfgs_step_one(const LbArgs<T> &a, const int64_t s,
+                                                  const int tid, BlockRed<TPB, T> &red) {
   static_assert(!HB || (HREG && sizeof(T) == 4), "BF16 history: FP32, register-resident");
-  const int tid = threadIdx.x;
   const int64_t B = a.B;
   // every per-start scalar is read before the first decision, so the reads
   // share one memory round trip (all are in bounds for any start); what steers
@@ -489,7 +491,7 @@ __device__ __forceinline__ void lbfgs_step_one(const LbArgs<T> &a, const int64_t
   const int64_t vov = uniform(vo_v);
   if (status != ST_ACTIVE) {
     if (tid == 0) a.active[s] = 0;
-    return;
+    return -1;
   }
   const int m = a.m;
   const int d = dv;
@@ -532,7 +534,7 @@ __device__ __forceinline__ void lbfgs_step_one(const LbArgs<T> &a, const int64_t
       a.status[s] = ST_STALLED;
       a.active[s] = 0;
     }
-    return;
+    return -1;
   }
   if (mode == M_BACKTRACK) {
     const int tr = 1 - cur;
@@ -552,7 +554,7 @@ __device__ __forceinline__ void lbfgs_step_one(const LbArgs<T> &a, const int64_t
       a.rowid[s] = (int32_t)((size_t)tr * B + s);
       if (a.rowoff) a.rowoff[s] = (int64_t)tr * Lt + vo;
     }
-    return;
+    return (int32_t)((size_t)tr * B + s);
   }
 
   // ---- load the point whose direction we now compute (and, on accept, the old one)
@@ -713,7 +715,7 @@ __device__ __forceinline__ void lbfgs_step_one(const LbArgs<T> &a, const int64_t
       a.head[s] = head;
       a.iters[s] = it;
     }
-    return;
+    return -1;
   }
 
   // ---- next direction
@@ -785,6 +787,7 @@ __device__ __forceinline__ void lbfgs_step_one(const LbArgs<T> &a, const int64_t
     a.rowid[s] = (int32_t)((size_t)tr * B + s);
     if (a.rowoff) a.rowoff[s] = (int64_t)tr * Lt + vo;
   }
+  return (int32_t)((size_t)tr * B + s);
 }
 
 // Start s_base + blockIdx.x: a workgroup each.  (Four one-wave starts per
@@ -802,7 +805,7 @@ __global__ __launch_bounds__(TPB, 2) void lbfgs_step_kernel(LbArgs<T> a) {
   // previous count ran before this launch
   if (a.count_reset && blockIdx.x == 0 && threadIdx.x == 0) *a.count_reset = 0;
   if ((int64_t)blockIdx.x < a.s_count)
-    lbfgs_step_one<T, TPB, EPT, HREG, HB>(a, a.s_base + blockIdx.x, red);
+    lbfgs_step_one<T, TPB, EPT, HREG, HB>(a, a.s_base + blockIdx.x, threadIdx.x, red);
 }
 
 template <typename T, int TPB, int EPT, bool HREG, bool HB>
@@ -1024,6 +1027,147 @@ int launch_lbfgs_step(const LbfgsBuffers &b, int max_iter, double grad_tol, hipS
   return launch_lbfgs_step_range(b, 0, b.B, b.d, grad_tol, max_iter, s);
 }
 
+// ---------------------------------------------------- small FP64 problems
+//
+// The whole iteration of 16 starts by one workgroup: a wave per start for the
+// step, then the 16 trial points together on the matrix cores, until every
+// start has stopped or n_steps are done.  The starts of different workgroups
+// have nothing to exchange, so neither the launches of a step (step,
+// compaction, evaluation) nor the readback of the active count lie between one
+// step and the next; the arithmetic is theirs, in their order.  A step is
+// bound by its latency: scalars, vectors, the recursion's chain of wave sums,
+// the tile's loads, products and row sums.
+// Bulk phase of 80 steps before and after (us): d = 4, K = 1, 64 starts 351 ->
+// 238 (24 steps); d = 64, K = 4, 4096 starts 2440 -> 1310; d = 128, K = 3,
+// 2048 starts 3072 -> 1925.
+// prog[w]: steps workgroup w has done, or ~steps once all of its starts have
+// stopped (zero before the first launch); tmax: the largest number of steps
+// that any workgroup needs as far as known (one more than it has done while a
+// start is active); evals: the evaluations are added.
+// Starts (waves) per workgroup: 16 fill the tile; the step of two values a
+// lane needs more than the 128 registers that 16 waves leave (80 of them
+// spilled: 14 against 11 us a step at d = 128), so it takes 8.
+template <int EPT>
+constexpr int kBulkWaves = EPT == 1 ? fused::kRows : fused::kRows / 2;
+struct BulkArgs {
+  LbArgs<double> lb;
+  Model m;
+  int dp, n_steps, max_steps;
+  int32_t *prog, *tmax;
+  int64_t *evals;
+};
+struct SlotRows {  // tile row i: the row in LDS
+  const int32_t *slot;
+  template <int N>
+  __device__ __forceinline__ void src(const int (&i)[N], int64_t (&row)[N]) const {
+#pragma unroll
+    for (int u = 0; u < N; ++u) row[u] = slot[i[u] < fused::kRows ? i[u] : 0];
+  }
+  __device__ __forceinline__ int64_t dst(int i) const { return slot[i]; }
+  __device__ __forceinline__ int64_t aux(int i) const { return i; }
+};
+template <int EPT, int NS, bool FAST>
+__global__ __launch_bounds__(64 * kBulkWaves<EPT>) void lbfgs_bulk_kernel(BulkArgs b) {
+  constexpr int W = kBulkWaves<EPT>;
+  extern __shared__ __attribute__((aligned(16))) double lds[];
+  __shared__ int32_t slot[fused::kRows];
+  __shared__ int32_t nev_s[W];
+  const int t0 = uniform(b.prog[blockIdx.x]);
+  if (t0 < 0) return;
+  const int lane = threadIdx.x & 63, wave = uniform((int)(threadIdx.x >> 6));
+  const int64_t s = (int64_t)blockIdx.x * W + wave;
+  if (threadIdx.x < fused::kRows) slot[threadIdx.x] = -1;  // (rows past the waves: none)
+  __syncthreads();
+  BlockRed<64, double> red{nullptr, 0};  // (sums within a wave: no LDS)
+  const int tend = min(t0 + b.n_steps, b.max_steps);
+  int t = t0, nev = 0;
+  bool done = false;
+  while (t < tend) {
+    // (the thread's index opaque in each iteration: what follows from it, which
+    // the step and the tile form anew, else fills the registers of both)
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    int32_t row = -1;
+    if (s < b.lb.B) row = lbfgs_step_one<double, 64, EPT, true, false>(b.lb, s, tid & 63, red);
+    asm volatile("" : "+v"(tid));
+    if (lane == 0) slot[wave] = row;
+    nev += row >= 0;
+    ++t;
+    __syncthreads();  // the rows and the trial points are there
+    if (!__any(slot[lane & (fused::kRows - 1)] >= 0)) {
+      done = true;
+      break;
+    }
+    fused::tile<64 * W, NS, FAST>(b.m, b.dp, b.lb.X, b.lb.d, SlotRows{slot}, b.lb.F, b.lb.G,
+                                        b.lb.d, nullptr, lds, t == t0 + 1, tid);
+    __syncthreads();  // l and the gradients are there, the rows read
+  }
+  if (lane == 0) nev_s[wave] = nev;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    unsigned long long n = 0;
+    for (int w = 0; w < W; ++w) n += (unsigned)nev_s[w];
+    if (n) atomicAdd((unsigned long long *)b.evals, n);
+    b.prog[blockIdx.x] = done ? ~t : t;
+    atomicMax(b.tmax, done ? t : t + 1);
+  }
+}
+
+template <int EPT, int NS>
+static void bulk_go(const BulkArgs &a, bool fast, hipStream_t s) {
+  const dim3 grid((unsigned)ceil_div(a.lb.B, kBulkWaves<EPT>)), block(64 * kBulkWaves<EPT>);
+  const size_t lds = fused::lds_bytes(a.m.K, a.dp);
+  if (fast)
+    hipLaunchKernelGGL((lbfgs_bulk_kernel<EPT, NS, true>), grid, block, lds, s, a);
+  else
+    hipLaunchKernelGGL((lbfgs_bulk_kernel<EPT, NS, false>), grid, block, lds, s, a);
+}
+
+// Where all workgroups run at once, or nearly: there is one per CU of 256 (16
+// waves at 128 registers, 8 at 170), so d <= 64 has 4096 starts in one round
+// and d <= 128 2048.  Past that the launches a step that compact the starts win
+// back what the last rounds, with few starts left, lose: whole calls (us, step
+// launches against one launch) d = 64, K = 4 4420 : 3608 at 8192 starts, d = 16,
+// K = 4 2808 : 2574 at 8192 and 3998 : 4296 at 16384; d = 128, K = 3 4156 : 3036
+// at 2048, 5004 : 4992 at 4096 and 7155 : 8900 at 8192.
+bool lbfgs_bulk_ok(const LbfgsBuffers &b, const Model &m) {
+  ASrc a;
+  a.X = b.X;
+  a.ldx = b.d;
+  return b.dtype == DT_F64 && !b.hist_bf16 && !b.voff && b.m <= kMaxHist && b.d == m.d &&
+         b.B <= (m.d <= 64 ? 8192 : 2048) && fused_logl_grad_ok(m, a);
+}
+
+int launch_lbfgs_bulk(const LbfgsBuffers &b, const Model &m, int max_iter, double grad_tol,
+                      int n_steps, int max_steps, hipStream_t s) {
+  if (!lbfgs_bulk_ok(b, m) || m.d > 128) {
+    set_error("L-BFGS in one launch: unsupported model or buffers");
+    return SB_E_UNSUPPORTED;
+  }
+  if (b.B <= 0) return SB_OK;
+  BulkArgs a;
+  a.lb = make_args<double>(b, max_iter, grad_tol);
+  a.m = m;
+  a.dp = (m.d + 31) / 32 * 32;
+  a.n_steps = n_steps;
+  a.max_steps = max_steps;
+  a.prog = b.idx;
+  a.tmax = b.count;
+  a.evals = b.evals;
+  const bool fast = m.d % 8 == 0 && ((uintptr_t)m.P64 & 15) == 0;
+  const int nb = m.K * (a.dp / 16);  // 16-column blocks: up to 24, over the waves
+  if (m.d <= 64) {
+    if (nb <= 16) bulk_go<1, 1>(a, fast, s);
+    else bulk_go<1, 2>(a, fast, s);
+  } else {
+    if (nb <= 8) bulk_go<2, 1>(a, fast, s);
+    else if (nb <= 16) bulk_go<2, 2>(a, fast, s);
+    else bulk_go<2, 3>(a, fast, s);
+  }
+  SB_LAUNCH_CHECK();
+  return SB_OK;
+}
+
 int launch_two_loop(int64_t B, int d, int m, const int32_t *cnt, const void *S, const void *Y,
                     const void *G, void *P, int dtype, hipStream_t s) {
   int st = check_d(d, m);
@@ -1085,8 +1229,8 @@ int lbfgs_carve(Arena &ar, LbfgsBuffers &b) {
 template <typename T>
 __global__ void lbfgs_init_kernel(int64_t B, int d, const T *X0, T *X, int32_t *cur,
                                   int32_t *head, int32_t *cnt, int32_t *iters, int32_t *ls,
-                                  int32_t *status, int32_t *phase, int32_t *count,
-                                  int64_t *evals) {
+                                  int32_t *status, int32_t *phase, int32_t *idx,
+                                  int32_t *count, int64_t *evals) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t n = B * d;
   for (int64_t e = i; e < n; e += (int64_t)gridDim.x * blockDim.x) X[e] = X0[e];
@@ -1098,9 +1242,10 @@ __global__ void lbfgs_init_kernel(int64_t B, int d, const T *X0, T *X, int32_t *
     ls[e] = 0;
     status[e] = ST_ACTIVE;
     phase[e] = PH_INIT;
+    idx[e] = 0;
   }
   if (i == 0) {
-    count[0] = (int32_t)B;
+    count[0] = 0;
     evals[0] = B;
   }
 }
@@ -1110,11 +1255,11 @@ int launch_lbfgs_init(const LbfgsBuffers &b, const void *X0, hipStream_t s) {
   if (b.dtype == DT_F64)
     hipLaunchKernelGGL(lbfgs_init_kernel<double>, dim3(blocks), dim3(256), 0, s, b.B, b.d,
                        (const double *)X0, (double *)b.X, b.cur, b.head, b.cnt, b.iters, b.ls,
-                       b.status, b.phase, b.count, b.evals);
+                       b.status, b.phase, b.idx, b.count, b.evals);
   else
     hipLaunchKernelGGL(lbfgs_init_kernel<float>, dim3(blocks), dim3(256), 0, s, b.B, b.d,
                        (const float *)X0, (float *)b.X, b.cur, b.head, b.cnt, b.iters, b.ls,
-                       b.status, b.phase, b.count, b.evals);
+                       b.status, b.phase, b.idx, b.count, b.evals);
   SB_LAUNCH_CHECK();
   return SB_OK;
 }

@@ -750,6 +750,13 @@ static hipGraphExec_t block_graph(ExecCtx *ex, const BlockKey &key, hipStream_t 
   return victim->exec;
 }
 
+// Small FP64 problems: the iterations of a block in one launch, which stops
+// where its starts do (the compaction and its count are not needed).
+static bool bulk_one_launch(const Layout &L) {
+  const Evaluator &ev = L.bulk;
+  return ev.gemm_dtype < 0 && !ev.two_stage && !ev.grad_direct && lbfgs_bulk_ok(L.lb, ev.m);
+}
+
 // Bulk L-BFGS over all starts in dtype of lb; X0 in that dtype.  With an
 // execution context (and a stream that can be captured) the iteration blocks
 // run as its graph for `key`; without one they are launched directly.
@@ -779,6 +786,10 @@ static int run_bulk(Layout &L, const RunCfg &rc, double tol, hipStream_t s,
   at.ldx = d;
   at.rowmap = lb.idx;
   at.rows = 2 * lb.B;  // both slots
+  const int max_steps = 42 * rc.max_iter + 64;
+  const int step_cap = (int)ceil_div(max_steps, rc.blk) * rc.blk;
+  const bool bulk = bulk_one_launch(L);
+  constexpr int kBulkSteps = 256;
   auto one_step = [&]() -> int {
     int r = launch_lbfgs_step(lb, rc.max_iter, tol, s);
     if (r) return r;
@@ -793,17 +804,18 @@ static int run_bulk(Layout &L, const RunCfg &rc, double tol, hipStream_t s,
   const bool graphs = ex && rc.use_graph && s != nullptr;
   hipGraphExec_t exec = nullptr;
   int steps = 0;
-  const int max_steps = 42 * rc.max_iter + 64;
   int rc_st = SB_OK;
+  auto block = [&]() -> int {
+    if (bulk) return launch_lbfgs_bulk(lb, ev.m, rc.max_iter, tol, kBulkSteps, step_cap, s);
+    int q = SB_OK;
+    for (int k = 0; k < rc.blk && q == SB_OK; ++k) q = one_step();
+    return q;
+  };
   while (steps < max_steps) {
     if (graphs) {
       if (!exec) {
         int r = SB_OK;
-        exec = block_graph(ex, key, s, [&]() -> int {
-          int q = SB_OK;
-          for (int k = 0; k < rc.blk && q == SB_OK; ++k) q = one_step();
-          return q;
-        }, &r);
+        exec = block_graph(ex, key, s, block, &r);
         if (!exec) {
           rc_st = r ? r : SB_E_DEVICE;
           break;
@@ -816,19 +828,24 @@ static int run_bulk(Layout &L, const RunCfg &rc, double tol, hipStream_t s,
       }
       ++ex->n_launch;
     } else {
-      int r = SB_OK;
-      for (int k = 0; k < rc.blk && r == SB_OK; ++k) r = one_step();
+      const int r = block();
       if (r) {
         rc_st = r;
         break;
       }
     }
-    steps += rc.blk;
+    steps = bulk ? std::min(steps + kBulkSteps, step_cap) : steps + rc.blk;
     if (hipMemcpyAsync(hcount, lb.count, sizeof(int32_t), hipMemcpyDeviceToHost, s) !=
             hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess) {
       set_error("count readback failed: %s", hipGetErrorString(hipGetLastError()));
       rc_st = SB_E_DEVICE;
+      break;
+    }
+    if (bulk) {
+      // the steps the slowest start took, in whole blocks as elsewhere
+      if (hcount[0] > steps) continue;
+      steps = (int)ceil_div(std::max(hcount[0], 1), rc.blk) * rc.blk;
       break;
     }
     if (hcount[0] == 0) break;
@@ -1329,6 +1346,7 @@ int run_evidence(const DevProblem &P, const sb_config *cfg, sb_result *res, void
     key.screen = L.bulk.screen;
     key.grad_direct = L.bulk.grad_direct;
     key.hist_bf16 = L.lb.hist_bf16;
+    key.one_launch = bulk_one_launch(L);
     key.tile = L.bulk.tile;
     key.tile1 = L.bulk.tile1;
     key.tile2 = L.bulk.tile2;

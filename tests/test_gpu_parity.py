@@ -846,6 +846,49 @@ def test_quadform_edges(L, d, tile, monkeypatch):
             assert bool(((qk - (delta * Y).sum(1)).abs() <= 4 * (d + 1) * u * qmag).all())
 
 
+@pytest.mark.parametrize("d,K,B", [(1, 1, 1), (4, 2, 15), (31, 12, 17), (33, 3, 16), (64, 6, 33),
+                                   (65, 1, 9), (96, 4, 8), (128, 3, 17), (64, 0, 20),
+                                   (120, 0, 7)])
+def test_evidence_bulk_in_one_launch(L, d, K, B, monkeypatch):
+    """The small FP64 problems' iterations in one launch (16 or 8 starts a workgroup, ragged
+    starts and column blocks; K = 0: Student-t) against the launch per step with the contraction
+    and epilogue of their own: the same modes, and log Z to 1e-10 (both
+    polish to the same stationary points, where l and log det H carry a few ulps of their sums)."""
+    rng = np.random.Generator(np.random.PCG64(1100 + d))
+    if K:
+        prob = synth.gaussian_mixture(rng, d, K, -6.0, 6.0, 0.1, 1.0, 0.0, box_half=9.0,
+                                      linf_min=1.0)
+    else:
+        prob = synth.student_t(rng, d, 5.0, -3.0, 3.0, 0.1, 1.0, 9.0)
+    cfg = synth.RunConfig(n_rays=max(64, 2 * B), n_points=16, n_starts=B, seed=5, precision=0)
+    a = L.EvidenceRunner(prob, cfg).run()
+    monkeypatch.setenv("SB_FUSED", "0")
+    b = L.EvidenceRunner(prob, cfg).run()
+    assert a.status == b.status == 0
+    assert a.n_modes == b.n_modes >= 1
+    assert abs(a.log_z - b.log_z) <= 1e-10 * max(1.0, abs(b.log_z))
+    assert a.iterations % 8 == 0
+
+
+def test_evidence_bulk_continues(L):
+    """More steps than one launch of the small FP64 problems' iterations takes (256): the next
+    launch goes on where each workgroup stopped, as eager launches and as the context's graph."""
+    rng = np.random.Generator(np.random.PCG64(7))
+    P, _ = synth.random_precision(rng, 64, 1e-7, 1.0)
+    prob = synth.Problem(0, 0, 64, 1, np.zeros(1), rng.uniform(-1, 1, (1, 64)), P[None], 0.0, 0.0,
+                         -9 * np.ones(64), 9 * np.ones(64), np.zeros(1))
+    cfg = synth.RunConfig(n_rays=64, n_points=16, n_starts=40, seed=5, precision=0)
+    a = L.EvidenceRunner(prob, cfg).run()
+    assert a.status == 0 and a.iterations > 256 and a.n_modes == 1
+    ex, stream = L.ExecContext(), torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        b = L.EvidenceRunner(prob, cfg, exec=ex).run(stream)
+        c = L.EvidenceRunner(prob, cfg, exec=ex).run(stream)
+    for r in (b, c):
+        _same_result(a, r)
+    ex.close()
+
+
 @pytest.mark.parametrize("m", [2, 3, 5])
 def test_lbfgs_refused_pairs(L, m):
     """FP64, short memories on the heavy-tailed t: the curvature test refuses pairs while the
