@@ -132,8 +132,11 @@ int launch_ray_argmax(int R, int n_pts, int dtype, const void *l, double *best_l
 // Rank of each ray by (best l descending, index ascending), NaN as -inf; the
 // first n_starts ranks name the starts.  A workgroup ranks 64 rays: lane l of
 // every wave holds ray 64 b + l, and wave w counts the rays of the w-th
-// sixteenth of the array that precede it (the compared key is the same for
-// the whole wave, a broadcast read); the 16 partial counts are added in LDS.
+// sixteenth of the array that precede it; the 16 partial counts are added in
+// LDS.  The keys are read 64 at a time, one per lane, and taken from there
+// lane by lane, with one comparison where the 64 lie on one side of the
+// workgroup's rays.  Bound by the comparisons, R^2 of them: 36 -> 17 us for
+// 4096 rays, 135 -> 57 us for 16384.
 constexpr int TOPN_PARTS = 16;
 __global__ __launch_bounds__(64 * TOPN_PARTS) void topn_kernel(int R, int n_starts,
                                                                const double *best_l,
@@ -149,10 +152,26 @@ __global__ __launch_bounds__(64 * TOPN_PARTS) void topn_kernel(int R, int n_star
   const int seg = (R + TOPN_PARTS - 1) / TOPN_PARTS;
   const int t0 = w * seg, t1 = min(R, t0 + seg);
   int cnt = 0;
-  for (int t = t0; t < t1; ++t) {
-    double v = best_l[t];
-    if (v != v) v = -INFINITY;
-    cnt += (v > key) || (v == key && t < r);
+  for (int tb = t0; tb < t1; tb += 64) {
+    double kv = NAN;  // (past the segment: precedes nothing)
+    if (tb + lane < t1) {
+      kv = best_l[tb + lane];
+      if (kv != kv) kv = -INFINITY;
+    }
+    const int r0 = blockIdx.x * 64;
+    if (tb + 63 < r0) {  // all of lower index
+#pragma unroll 16
+      for (int i = 0; i < 64; ++i) cnt += wave_value(kv, i) >= key;
+    } else if (tb > r0 + 63) {  // all of higher index
+#pragma unroll 16
+      for (int i = 0; i < 64; ++i) cnt += wave_value(kv, i) > key;
+    } else {
+#pragma unroll 4
+      for (int i = 0; i < 64; ++i) {
+        const double v = wave_value(kv, i);
+        cnt += (v > key) || (v == key && tb + i < r);
+      }
+    }
   }
   part[w][lane] = cnt;
   __syncthreads();

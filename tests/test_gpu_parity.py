@@ -534,6 +534,24 @@ def test_lbfgs_bf16_history(L, d, seed):
 
 # -------------------------------------------------------------- dedup / A7
 
+@pytest.mark.parametrize("C,d", [(1, 1), (63, 3), (64, 4), (1025, 5), (256, 64), (256, 65),
+                                 (8192, 2), (8193, 1), (163, 100)])
+def test_dedup_sizes(L, C, d):
+    """Sets on both sides of the one-workgroup limits (8192 candidates, 2^14 values) and the
+    lanes per candidate that d selects: the oracle's partition exactly (the same comparisons on
+    the same doubles), equal values visited by index, values that are NaN last."""
+    rng = np.random.Generator(np.random.PCG64(1300 + C + d))
+    centres = rng.uniform(-4, 4, (6, d))
+    X = centres[rng.integers(6, size=C)] + 0.2 * rng.uniform(-1, 1, (C, d))
+    l = np.round(rng.standard_normal(C), 1)
+    l[rng.random(C) < 0.02] = np.nan
+    valid = (rng.random(C) < 0.9).astype(np.uint8)
+    ro, rs = O.dedup(X, l, 0.35, valid=valid)
+    rep_of, reps = L.sb_dedup_dev(dev(X), dev(l), 0.35, valid=dev(valid))
+    assert np.array_equal(rep_of.cpu().numpy(), ro)
+    assert np.array_equal(np.asarray(reps.cpu().numpy() if hasattr(reps, "cpu") else reps), rs)
+
+
 def test_dedup_handmade(L):
     X = np.array([[0.0, 0.0], [0.05, 0.0], [1.0, 1.0], [1.02, 0.99], [0.0, 0.09], [5.0, 5.0]])
     l = np.array([1.0, 3.0, 2.0, 2.0, 0.5, -1.0])
