@@ -236,8 +236,8 @@ int32_t sb_evidence_chisao_dev(const sb_loglik *ll_dev, const sb_box *box_dev,
  * batching form: an iteration block of the L-BFGS bulk, 8 steps of step,
  * compaction, contraction and epilogue launches, or the one launch that takes
  * up to 256 steps of a small FP64 problem, replayed as one HIP graph).
- * sb_exec_create allocates, on the current device, a pinned host word for
- * the per-block count readback, ten timing events and room for four
+ * sb_exec_create allocates, on the current device, a small pinned host buffer
+ * for the readbacks of a call, ten timing events and room for four
  * instantiated block graphs; sb_exec_destroy frees them.
  * sb_evidence_exec_dev is sb_evidence_dev with that state: the block graph
  * for this call's buffers, model and box pointers, configuration, stream

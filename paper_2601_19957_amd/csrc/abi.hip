@@ -354,7 +354,7 @@ int32_t sb_exec_create(sb_exec **out) {
   ExecCtx *ex = new (std::nothrow) ExecCtx();
   if (!ex) return fail(SB_E_NOMEM, "out of host memory");
   (void)hipGetDevice(&ex->device);
-  if (hipHostMalloc((void **)&ex->pinned, sizeof(int32_t) * 16, hipHostMallocDefault) !=
+  if (hipHostMalloc(&ex->pinned, ExecCtx::kPinnedBytes, hipHostMallocDefault) !=
       hipSuccess) {
     delete ex;
     return fail(SB_E_NOMEM, "pinned host allocation failed");

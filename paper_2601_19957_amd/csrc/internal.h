@@ -454,14 +454,16 @@ struct BlockKey {
   TileCfg tile, tile1, tile2;
 };
 
-// Execution state a caller keeps across whole-path calls (sb_exec): a pinned
-// host word for the per-block active-count readback, phase-timing events,
+// Execution state a caller keeps across whole-path calls (sb_exec): a small
+// pinned host buffer for the readbacks, phase-timing events,
 // and instantiated graphs of the L-BFGS iteration block, looked up by
 // BlockKey (a miss captures the block and updates the least recently used
 // executable in place, or instantiates one).  Used by one call at a time.
 struct ExecCtx {
   int device = -1;
-  int32_t *pinned = nullptr;  // [16], hipHostMalloc
+  // what a call reads back on its way lands here: small, and one at a time
+  static constexpr size_t kPinnedBytes = 16384;
+  void *pinned = nullptr;
   hipEvent_t ev[10];
   bool ev_ok = false;
   static constexpr int kSlots = 4;

@@ -1221,8 +1221,9 @@ int lbfgs_carve(Arena &ar, LbfgsBuffers &b) {
   b.rowid = ar.take<int32_t>(B);
   b.active = ar.take<int32_t>(B);
   b.idx = ar.take<int32_t>(B);
-  b.count = ar.take<int32_t>(4);
-  b.evals = ar.take<int64_t>(2);
+  // (evaluations and active count side by side: one readback takes both)
+  b.evals = ar.take<int64_t>(4);
+  b.count = (int32_t *)(b.evals + 1);
   return ar.ok() ? SB_OK : SB_E_NOMEM;
 }
 

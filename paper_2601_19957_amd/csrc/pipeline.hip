@@ -447,6 +447,9 @@ static RunCfg resolve(const sb_loglik *ll, const sb_config *c,
   return r;
 }
 
+constexpr int kNewtonSteps = 20;  // polish steps at most
+constexpr int kOutHead = 8;
+
 // Workspace layout (measured with a null arena, carved with the real one).
 struct Layout {
   // prep
@@ -472,18 +475,23 @@ struct Layout {
   int32_t *status = nullptr, *counts = nullptr;
   uint8_t *valid = nullptr;
   int32_t *rep_of = nullptr, *reps = nullptr;
-  // polish (chunk)
+  // polish (chunk); its points, l, log dets and flags lie in the arrays of all
+  // polished reps.  done [n], rejected [n] and the counts of the steps follow one
+  // another for a chunk of n, so one launch clears them.
   Evaluator pol;
   double *Xp = nullptr, *lp = nullptr, *Gp = nullptr, *auxp = nullptr, *H = nullptr, *dx = nullptr, *ldh = nullptr;
-  int32_t *pinfo = nullptr, *done = nullptr, *rejected = nullptr, *nact = nullptr;
+  int32_t *pinfo = nullptr, *done = nullptr;
   uint8_t *okp = nullptr;
   // all polished reps (cap_pre)
   double *XA = nullptr, *lA = nullptr, *ldhA = nullptr;
   uint8_t *okA = nullptr;
   int32_t *rep2 = nullptr, *rep2_of = nullptr;
   // modes
-  double *Xm = nullptr, *lm = nullptr, *ldm = nullptr, *mlz = nullptr, *logz = nullptr,
-         *Xs = nullptr, *ls_ = nullptr, *lds = nullptr;
+  double *Xm = nullptr, *lm = nullptr, *ldm = nullptr;
+  // everything the call returns, in one piece for one readback: counts (8
+  // integers), log Z, and from kOutHead on log Z, l and log det of the modes
+  // and the modes
+  double *out = nullptr, *logz = nullptr;
   int32_t *order = nullptr;
   Arena dedup_ar;
   // ChiSao cycle: slot flags, l of the active slots, end gradients, dedup
@@ -541,10 +549,13 @@ static int carve_layout(Arena &ar, Layout &L, const sb_loglik *ll, const RunCfg 
   L.Lprep = ar.take<double>((size_t)K * d * d);
   L.logdetP = ar.take<double>(K);
   L.beta = ar.take<double>(K);
-  L.mx = ar.take<double>(K);
-  L.info = ar.take<int32_t>(K);
-  L.flags = ar.take<int32_t>(16);
-  L.boxinfo = ar.take<double>(4);
+  // what the host checks of the preparation, side by side: one readback
+  L.boxinfo = ar.take<double>(4 + 2 * (size_t)K + 8);
+  if (L.boxinfo) {
+    L.mx = L.boxinfo + 4;
+    L.info = (int32_t *)(L.mx + K);  // [2 K]
+    L.flags = L.info + 2 * K;        // [16]
+  }
   if (mixed) {
     L.P32 = ar.take<float>((size_t)K * d * d);
     L.Pbf = ar.take<bf16_t>((size_t)K * d * d);
@@ -597,7 +608,6 @@ static int carve_layout(Arena &ar, Layout &L, const sb_loglik *ll, const RunCfg 
   L.Xend = ar.take<char>(bes * (size_t)B * d);
   L.lend = ar.take<double>((size_t)B);
   L.status = ar.take<int32_t>(B);
-  L.counts = ar.take<int32_t>(8);
   L.valid = ar.take<uint8_t>(B);
   L.rep_of = ar.take<int32_t>(B);
   L.reps = ar.take<int32_t>(rc.cap_pre);
@@ -608,18 +618,12 @@ static int carve_layout(Arena &ar, Layout &L, const sb_loglik *ll, const RunCfg 
   L.pol.m.d = d;
   L.pol.m.K = K;
   if (L.pol.carve(ar)) return SB_E_NOMEM;
-  L.Xp = ar.take<double>((size_t)PC * d);
-  L.lp = ar.take<double>(PC);
   L.Gp = ar.take<double>((size_t)PC * d);
   L.auxp = ar.take<double>((size_t)PC * K);
   L.H = ar.take<double>((size_t)PC * d * d);
   L.dx = ar.take<double>((size_t)PC * d);
-  L.ldh = ar.take<double>(PC);
   L.pinfo = ar.take<int32_t>(PC);
-  L.done = ar.take<int32_t>(PC);
-  L.rejected = ar.take<int32_t>(PC);
-  L.nact = ar.take<int32_t>(4);
-  L.okp = ar.take<uint8_t>(PC);
+  L.done = ar.take<int32_t>(2 * (size_t)PC + kNewtonSteps);
   const int CA = rc.cap_pre;
   L.XA = ar.take<double>((size_t)CA * d);
   L.lA = ar.take<double>(CA);
@@ -630,12 +634,12 @@ static int carve_layout(Arena &ar, Layout &L, const sb_loglik *ll, const RunCfg 
   L.Xm = ar.take<double>((size_t)CA * d);
   L.lm = ar.take<double>(CA);
   L.ldm = ar.take<double>(CA);
-  L.mlz = ar.take<double>(CA);
-  L.logz = ar.take<double>(4);
   L.order = ar.take<int32_t>(CA);
-  L.Xs = ar.take<double>((size_t)CA * d);
-  L.ls_ = ar.take<double>(CA);
-  L.lds = ar.take<double>(CA);
+  L.out = ar.take<double>(kOutHead + (size_t)CA * (d + 3));
+  if (L.out) {
+    L.counts = (int32_t *)L.out;
+    L.logz = L.out + 4;
+  }
   void *dd = ar.take<char>(dedup_ws_bytes(0) * 2);
   L.dedup_ar = Arena(dd, dedup_ws_bytes(0) * 2);
   if (ar.measure) L.dedup_ar.measure = true;
@@ -797,10 +801,12 @@ static int run_bulk(Layout &L, const RunCfg &rc, double tol, hipStream_t s,
     if (r) return r;
     return ev.run(at, lb.B, lb.count, lb.F, lb.G, d, lb.idx, nullptr, true, s);
   };
-  // the per-block active count lands in pinned memory of the context, else
-  // in a host stack word (the copy then completes before the synchronise)
-  int32_t hstack[4] = {0, 0, 0, 0};
-  int32_t *hcount = ex ? ex->pinned : hstack;
+  // the evaluations and the active count after each block land in pinned
+  // memory of the context, else on the stack (the copy then completes before
+  // the synchronise)
+  int64_t hstack[2] = {0, 0};
+  int64_t *hev = ex ? (int64_t *)ex->pinned : hstack;
+  const int32_t *hcount = (const int32_t *)(hev + 1);
   const bool graphs = ex && rc.use_graph && s != nullptr;
   hipGraphExec_t exec = nullptr;
   int steps = 0;
@@ -835,7 +841,7 @@ static int run_bulk(Layout &L, const RunCfg &rc, double tol, hipStream_t s,
       }
     }
     steps = bulk ? std::min(steps + kBulkSteps, step_cap) : steps + rc.blk;
-    if (hipMemcpyAsync(hcount, lb.count, sizeof(int32_t), hipMemcpyDeviceToHost, s) !=
+    if (hipMemcpyAsync(hev, lb.evals, 2 * sizeof(int64_t), hipMemcpyDeviceToHost, s) !=
             hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess) {
       set_error("count readback failed: %s", hipGetErrorString(hipGetLastError()));
@@ -850,14 +856,7 @@ static int run_bulk(Layout &L, const RunCfg &rc, double tol, hipStream_t s,
     }
     if (hcount[0] == 0) break;
   }
-  int64_t ev_h = 0;
-  if (rc_st == SB_OK) {
-    if (hipMemcpyAsync(&ev_h, lb.evals, sizeof(int64_t), hipMemcpyDeviceToHost, s) !=
-            hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess)
-      rc_st = SB_E_DEVICE;
-  }
-  *evals_out = ev_h;
+  *evals_out = rc_st == SB_OK ? hev[0] : 0;
   *steps_out = steps;
   if (rc_st) return rc_st;
   return launch_lbfgs_gather(lb, L.Xend, L.lend, true, grad_out, L.status, nullptr, s);
@@ -865,7 +864,7 @@ static int run_bulk(Layout &L, const RunCfg &rc, double tol, hipStream_t s,
 
 // FP64 Newton polish + final Hessian/Cholesky/filters for reps [c0, c0+n).
 static int polish_chunk(Layout &L, const Model &m64, const DevProblem &P, int n, hipStream_t s,
-                        int64_t *grad_evals, int64_t *hess_evals) {
+                        ExecCtx *ex, int64_t *grad_evals, int64_t *hess_evals) {
   const int d = m64.d, K = m64.K;
   Evaluator &ev = L.pol;
   ev.m = m64;
@@ -883,10 +882,11 @@ static int polish_chunk(Layout &L, const Model &m64, const DevProblem &P, int n,
     ev.tile = autotune_tiles(DT_F64, m64, n, s, &pr);
   }
   int st;
-  if ((st = launch_fill_i32(n, 0, L.done, s))) return st;
-  if ((st = launch_fill_i32(n, 0, L.rejected, s))) return st;
-  int32_t nact_h = 0;
-  for (int it = 0; it < 20; ++it) {
+  int32_t *done = L.done, *rejected = done + n, *nact = rejected + n;
+  if ((st = launch_fill_i32(2 * (int64_t)n + kNewtonSteps, 0, done, s))) return st;
+  int32_t hstack = 0;
+  int32_t *nact_h = ex ? (int32_t *)ex->pinned : &hstack;
+  for (int it = 0; it < kNewtonSteps; ++it) {
     if ((st = ev.run(a, n, nullptr, L.lp, L.Gp, d, nullptr, L.auxp, true, s))) return st;
     *grad_evals += n;
     if ((st = launch_hessian_assemble(m64, n, (const double *)ev.Y, ev.ldy, L.auxp, L.Gp, L.H, s)))
@@ -894,13 +894,12 @@ static int polish_chunk(Layout &L, const Model &m64, const DevProblem &P, int n,
     *hess_evals += n;
     if ((st = chol_batched(n, d, L.H, L.H, L.pinfo, s))) return st;
     if ((st = launch_chol_solve(n, d, L.H, L.Gp, L.dx, L.pinfo, s))) return st;
-    if ((st = launch_fill_i32(1, 0, L.nact, s))) return st;
     hipLaunchKernelGGL(newton_update_kernel, dim3(n), dim3(256), 0, s, d, L.Xp, L.dx, L.pinfo,
-                       L.done, L.rejected, L.nact);
+                       done, rejected, nact + it);
     SB_LAUNCH_CHECK();
-    SB_HIP(hipMemcpyAsync(&nact_h, L.nact, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+    SB_HIP(hipMemcpyAsync(nact_h, nact + it, sizeof(int32_t), hipMemcpyDeviceToHost, s));
     SB_HIP(hipStreamSynchronize(s));
-    if (nact_h == 0) break;
+    if (*nact_h == 0) break;
   }
   // final point: l, grad, Hessian, Cholesky, log det, filters
   if ((st = ev.run(a, n, nullptr, L.lp, L.Gp, d, nullptr, L.auxp, true, s))) return st;
@@ -911,7 +910,7 @@ static int polish_chunk(Layout &L, const Model &m64, const DevProblem &P, int n,
   if ((st = chol_batched(n, d, L.H, L.H, L.pinfo, s))) return st;
   if ((st = launch_logdet(n, d, L.H, L.pinfo, L.ldh, s))) return st;
   hipLaunchKernelGGL(filter_kernel, dim3(n), dim3(256), 0, s, d, L.Xp, L.lp, L.Gp, P.lo, P.hi,
-                     L.rejected, L.pinfo, L.okp, L.counts + 4);
+                     rejected, L.pinfo, L.okp, L.counts + 4);
   SB_LAUNCH_CHECK();
   (void)K;
   return SB_OK;
@@ -1163,14 +1162,17 @@ int run_evidence(const DevProblem &P, const sb_config *cfg, sb_result *res, void
     }
   }
   {
-    int32_t hflag[1];
-    int32_t hinfo[kMaxComp];
-    double hmx[kMaxComp], hbox[4];
-    SB_HIP(hipMemcpyAsync(hflag, L.flags, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    SB_HIP(hipMemcpyAsync(hinfo, L.info, sizeof(int32_t) * K, hipMemcpyDeviceToHost, s));
-    SB_HIP(hipMemcpyAsync(hmx, L.mx, sizeof(double) * K, hipMemcpyDeviceToHost, s));
-    SB_HIP(hipMemcpyAsync(hbox, L.boxinfo, sizeof(double) * 3, hipMemcpyDeviceToHost, s));
+    const size_t nstat = 8 * (4 + 2 * (size_t)K + 8);
+    double stat[4 + 2 * kMaxComp + 8];
+    const double *hp = ex ? (const double *)ex->pinned : stat;
+    SB_HIP(hipMemcpyAsync((void *)hp, L.boxinfo, nstat, hipMemcpyDeviceToHost, s));
     SB_HIP(hipStreamSynchronize(s));
+    double hbox[3], hmx[kMaxComp];
+    int32_t hflag[1], hinfo[kMaxComp];
+    memcpy(hbox, hp, sizeof(hbox));
+    memcpy(hmx, hp + 4, sizeof(double) * K);
+    memcpy(hinfo, hp + 4 + K, sizeof(int32_t) * K);
+    memcpy(hflag, (const int32_t *)(hp + 4 + K) + 2 * K, sizeof(hflag));
     if (hbox[0] != 0.0) {
       set_error("box: need finite lo_i < hi_i in every coordinate");
       res->log_z = NAN;
@@ -1379,6 +1381,10 @@ int run_evidence(const DevProblem &P, const sb_config *cfg, sb_result *res, void
     int64_t pol_evals = 0, hess_evals = 0;
     for (int c0 = 0; c0 < nrep; c0 += rc.polish_chunk) {
       const int n = std::min(rc.polish_chunk, nrep - c0);
+      L.Xp = L.XA + (size_t)c0 * d;
+      L.lp = L.lA + c0;
+      L.ldh = L.ldhA + c0;
+      L.okp = L.okA + c0;
       if (mixed)
         hipLaunchKernelGGL(gather_reps_kernel<float>, dim3(n), dim3(256), 0, s, d, L.reps + c0,
                            (const float *)L.Xend, L.Xp);
@@ -1386,12 +1392,7 @@ int run_evidence(const DevProblem &P, const sb_config *cfg, sb_result *res, void
         hipLaunchKernelGGL(gather_reps_kernel<double>, dim3(n), dim3(256), 0, s, d, L.reps + c0,
                            (const double *)L.Xend, L.Xp);
       SB_LAUNCH_CHECK();
-      if ((st = polish_chunk(L, m64, P, n, s, &pol_evals, &hess_evals))) return st;
-      SB_HIP(hipMemcpyAsync(L.XA + (size_t)c0 * d, L.Xp, sizeof(double) * n * d,
-                            hipMemcpyDeviceToDevice, s));
-      SB_HIP(hipMemcpyAsync(L.lA + c0, L.lp, sizeof(double) * n, hipMemcpyDeviceToDevice, s));
-      SB_HIP(hipMemcpyAsync(L.ldhA + c0, L.ldh, sizeof(double) * n, hipMemcpyDeviceToDevice, s));
-      SB_HIP(hipMemcpyAsync(L.okA + c0, L.okp, n, hipMemcpyDeviceToDevice, s));
+      if ((st = polish_chunk(L, m64, P, n, s, ex, &pol_evals, &hess_evals))) return st;
     }
     tm.mark(s);  // 5
     // ---------------- A7 final dedup
@@ -1403,9 +1404,33 @@ int run_evidence(const DevProblem &P, const sb_config *cfg, sb_result *res, void
                    rc.cap_pre, &nm, ar2, s);
     if (st && st != SB_E_CAPACITY) return st;
     // ---------------- A10 combine
-    int32_t hcounts[8];
-    SB_HIP(hipMemcpyAsync(hcounts, L.counts, sizeof(hcounts), hipMemcpyDeviceToHost, s));
+    const bool modes = nm > 0 && nm <= rc.max_modes;
+    double *mlz = L.out + kOutHead, *ml = mlz + nm, *mld = ml + nm, *mx = mld + nm;
+    if (modes) {
+      hipLaunchKernelGGL(gather_rows_kernel, dim3(nm), dim3(256), 0, s, d, L.rep2, L.XA, L.Xm);
+      hipLaunchKernelGGL(gather_scalars_kernel, dim3((unsigned)ceil_div(nm, 256)), dim3(256), 0,
+                         s, nm, L.rep2, L.lA, L.ldhA, L.lm, L.ldm);
+      SB_LAUNCH_CHECK();
+      if ((st = launch_combine(nm, d, P.lo, P.hi, L.lm, L.ldm, L.Xm, L.order, mlz, L.logz, s)))
+        return st;
+      hipLaunchKernelGGL(gather_rows_kernel, dim3(nm), dim3(256), 0, s, d, L.order, L.Xm, mx);
+      hipLaunchKernelGGL(gather_scalars_kernel, dim3((unsigned)ceil_div(nm, 256)), dim3(256), 0,
+                         s, nm, L.order, L.lm, L.ldm, ml, mld);
+      SB_LAUNCH_CHECK();
+      tm.mark(s);  // 6
+    }
+    // counts and, with modes, the whole result in one readback
+    const size_t nout = kOutHead + (modes ? (size_t)nm * (d + 3) : 0);
+    std::vector<double> hv;
+    double *h = ex && nout * 8 <= ExecCtx::kPinnedBytes ? (double *)ex->pinned : nullptr;
+    if (!h) {
+      hv.resize(nout);
+      h = hv.data();
+    }
+    SB_HIP(hipMemcpyAsync(h, L.out, nout * 8, hipMemcpyDeviceToHost, s));
     SB_HIP(hipStreamSynchronize(s));
+    int32_t hcounts[8];
+    memcpy(hcounts, h, sizeof(hcounts));
     res->n_logl_evals = (int64_t)rc.R * (rc.n_pts + (rc.cyc ? rc.cc.n_ref : 0)) + cyc_logl_evals;
     res->n_grad_evals = bulk_evals + pol_evals + cyc_grad_evals;
     res->n_hess_evals = hess_evals;
@@ -1424,31 +1449,12 @@ int run_evidence(const DevProblem &P, const sb_config *cfg, sb_result *res, void
       set_error("%d modes found, max_modes = %d", nm, rc.max_modes);
       ret = SB_E_CAPACITY;
     } else {
-      hipLaunchKernelGGL(gather_rows_kernel, dim3(nm), dim3(256), 0, s, d, L.rep2, L.XA, L.Xm);
-      hipLaunchKernelGGL(gather_scalars_kernel, dim3((unsigned)ceil_div(nm, 256)), dim3(256), 0,
-                         s, nm, L.rep2, L.lA, L.ldhA, L.lm, L.ldm);
-      SB_LAUNCH_CHECK();
-      if ((st = launch_combine(nm, d, P.lo, P.hi, L.lm, L.ldm, L.Xm, L.order, L.mlz, L.logz, s)))
-        return st;
-      hipLaunchKernelGGL(gather_rows_kernel, dim3(nm), dim3(256), 0, s, d, L.order, L.Xm, L.Xs);
-      hipLaunchKernelGGL(gather_scalars_kernel, dim3((unsigned)ceil_div(nm, 256)), dim3(256), 0,
-                         s, nm, L.order, L.lm, L.ldm, L.ls_, L.lds);
-      SB_LAUNCH_CHECK();
-      tm.mark(s);  // 6
-      SB_HIP(hipMemcpyAsync(&res->log_z, L.logz, sizeof(double), hipMemcpyDeviceToHost, s));
-      if (res->modes)
-        SB_HIP(hipMemcpyAsync(res->modes, L.Xs, sizeof(double) * nm * d, hipMemcpyDeviceToHost,
-                              s));
-      if (res->mode_log_z)
-        SB_HIP(hipMemcpyAsync(res->mode_log_z, L.mlz, sizeof(double) * nm,
-                              hipMemcpyDeviceToHost, s));
-      if (res->mode_logl)
-        SB_HIP(hipMemcpyAsync(res->mode_logl, L.ls_, sizeof(double) * nm, hipMemcpyDeviceToHost,
-                              s));
-      if (res->log_det_h)
-        SB_HIP(hipMemcpyAsync(res->log_det_h, L.lds, sizeof(double) * nm, hipMemcpyDeviceToHost,
-                              s));
-      SB_HIP(hipStreamSynchronize(s));
+      res->log_z = h[4];
+      const double *r = h + kOutHead;
+      if (res->mode_log_z) memcpy(res->mode_log_z, r, sizeof(double) * nm);
+      if (res->mode_logl) memcpy(res->mode_logl, r + nm, sizeof(double) * nm);
+      if (res->log_det_h) memcpy(res->log_det_h, r + 2 * nm, sizeof(double) * nm);
+      if (res->modes) memcpy(res->modes, r + 3 * nm, sizeof(double) * (size_t)nm * d);
     }
     const double total =
         std::chrono::duration<double>(std::chrono::steady_clock::now() - t_start).count();
