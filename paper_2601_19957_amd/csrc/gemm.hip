@@ -735,67 +735,45 @@ __device__ inline double clamp0(double v) {  // max(v, 0), NaN stays NaN
   return v > 0.0 ? v : (v <= 0.0 ? 0.0 : (double)NAN);
 }
 
-// One wave per row: |x - x_ref|^2 over the row, the decision (the row's
-// component mask), the dropped components' widened bounds and q partials,
-// |x - mu_k|^2 of the listed ones, and x_ref = x.  NX > 0 (d <= 256 NX): the
-// row's x and x_ref sit in registers, NX 16-byte chunks per lane, their loads
-// and the bounds' issued together, and x is read once; NX = 0: any d, the row
-// streamed twice.  Both forms sum in the same order.
+// One wave per row: the decision (the row's component mask), the dropped
+// components' widened bounds and q partials, and |x - mu_k|^2 of the listed
+// ones.  x_ref is what the trial's slot held before the optimiser's step wrote
+// x there, and the step, which has both in registers, gives their distance
+// squared (moved): with x_ref kept and compared here the kernel was bound by
+// the two reads and the write of a vector per row, 42 us a step at d = 1024, K =
+// 8, 16384 starts (with a round trip per listed component and chunk of mu), now
+// 18.  NX > 0 (d <= 256 NX): the row's x sits in
+// registers, NX 16-byte chunks per lane, their loads and the bounds' issued
+// together; NX = 0: any d, the row streamed.
 template <int NX>
 __global__ __launch_bounds__(256) void mixture_screen_kernel(Model m, ScreenArgs a) {
   // the list pass (the next launch) counts into cnt: zero it here
   if (blockIdx.x == 0 && threadIdx.x < m.K) a.cnt[threadIdx.x] = 0;
   const int64_t Mr = a.count ? (int64_t)(*a.count) : a.M;
-  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int64_t row = (int64_t)blockIdx.x * 4 + uniform((int)(threadIdx.x >> 6));
   const int lane = threadIdx.x & 63;
   if (row >= Mr) return;
   const int d = m.d, K = m.K;
   const int32_t xr = a.rowmap ? a.rowmap[row] : (int32_t)row;
   const float *x = a.X + (int64_t)xr * a.ldx;
-  float *xref = a.xref + (int64_t)xr * d;
-  const bool href = a.hasref[xr] > 0;
+  // (bounds and distance are read beside the flag that says if they are set)
+  const int href_v = a.hasref[xr];
+  const float dd = a.moved[xr];
+  double *lb = a.bnd + (int64_t)xr * 2 * K, *ub = lb + K;
+  const bool act = lane < K;  // component k's bounds in lane k
+  const double L0 = act ? lb[lane] : 0.0, U0 = act ? ub[lane] : 0.0;
   constexpr int NR = NX > 0 ? NX : 1;
-  f4v xv[NR], rv[NR];
+  f4v xv[NR];
   if constexpr (NX > 0) {
 #pragma unroll
     for (int i = 0; i < NX; ++i) {
       const int j = 4 * lane + 256 * i;  // (d % 8 == 0: a chunk is whole or absent)
-      xv[i] = rv[i] = f4v{0.f, 0.f, 0.f, 0.f};
-      if (j < d) {
-        xv[i] = *(const f4v *)(x + j);
-        if (href) rv[i] = __builtin_nontemporal_load((const f4v *)(xref + j));
-      }
+      xv[i] = f4v{0.f, 0.f, 0.f, 0.f};
+      if (j < d) xv[i] = *(const f4v *)(x + j);
     }
   }
   uint32_t keep = (1u << K) - 1u;  // (K <= 16) no reference yet: every component
-  if (href) {
-    // component k's bounds in lane k
-    double *lb = a.bnd + (int64_t)xr * 2 * K, *ub = lb + K;
-    const bool act = lane < K;
-    const double L0 = act ? lb[lane] : 0.0, U0 = act ? ub[lane] : 0.0;
-    float dd = 0.f;
-    if constexpr (NX > 0) {
-#pragma unroll
-      for (int i = 0; i < NX; ++i)
-        if (4 * lane + 256 * i < d)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float t = xv[i][e] - rv[i][e];
-            dd += t * t;
-          }
-    } else {
-      for (int j = 4 * lane; j < d; j += 256) {  // (d % 8 == 0, 16-byte rows)
-        const f4v xw = *(const f4v *)(x + j);
-        const f4v rw = __builtin_nontemporal_load((const f4v *)(xref + j));
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float t = xw[e] - rw[e];
-          dd += t * t;
-        }
-      }
-    }
-    // (the butterfly leaves the same sum in every lane: the decision is uniform)
-    dd = wave_sum(dd);
+  if (uniform(href_v > 0)) {
     const double D = sqrt((double)dd * (1.0 + screen_rq(d))) * (1.0 + 0x1p-40);
     double Lk = 0.0, Uk = 0.0, hi = -INFINITY;
     if (act) {
@@ -815,36 +793,52 @@ __global__ __launch_bounds__(256) void mixture_screen_kernel(Model m, ScreenArgs
       ub[lane] = Uk;
     }
   }
-  // |x - mu_k|^2 of the listed components (for their new bounds) and x_ref = x
-  float nrm[kMaxK];
+  // |x - mu_k|^2 of the listed components (for their new bounds), the next
+  // one's mu on its way while one is summed
+  keep = (uint32_t)uniform((int)keep);
+  float nk = 0.f;  // lane k's
+  auto mu_chunk = [&](int k, int j) {
+    return j < d ? *(const f4v *)(m.mu32 + (int64_t)k * d + j) : f4v{0.f, 0.f, 0.f, 0.f};
+  };
+  auto add = [&](float &t2, const f4v &xw, const f4v &mw) {
 #pragma unroll
-  for (int k = 0; k < kMaxK; ++k) nrm[k] = 0.f;
-  auto chunk = [&](int j, const f4v &xw) {
-    __builtin_nontemporal_store(xw, (f4v *)(xref + j));
-#pragma unroll
-    for (int k = 0; k < kMaxK; ++k)
-      if (k < K && ((keep >> k) & 1u)) {
-        const f4v mv = *(const f4v *)(m.mu32 + (int64_t)k * d + j);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float t = xw[e] - mv[e];  // delta as the contraction forms it
-          nrm[k] += t * t;
-        }
-      }
+    for (int e = 0; e < 4; ++e) {
+      const float t = xw[e] - mw[e];  // delta as the contraction forms it
+      t2 += t * t;
+    }
   };
   if constexpr (NX > 0) {
+    f4v mv[NX], nx[NX];
+    uint32_t todo = keep;
+    auto fetch = [&](f4v (&w)[NX]) {
+      if (!todo) return;
+      const int k = __builtin_ctz(todo);
 #pragma unroll
-    for (int i = 0; i < NX; ++i)
-      if (4 * lane + 256 * i < d) chunk(4 * lane + 256 * i, xv[i]);
+      for (int i = 0; i < NX; ++i) w[i] = mu_chunk(k, 4 * lane + 256 * i);
+    };
+    fetch(mv);
+    while (todo) {
+      const int k = __builtin_ctz(todo);
+      todo &= todo - 1;
+      fetch(nx);
+      float t2 = 0.f;
+#pragma unroll
+      for (int i = 0; i < NX; ++i) add(t2, xv[i], mv[i]);
+      t2 = wave_sum(t2);
+      if (lane == k) nk = t2;
+#pragma unroll
+      for (int i = 0; i < NX; ++i) mv[i] = nx[i];
+    }
   } else {
-    for (int j = 4 * lane; j < d; j += 256) chunk(j, *(const f4v *)(x + j));
+    for (uint32_t todo = keep; todo; todo &= todo - 1) {
+      const int k = __builtin_ctz(todo);
+      float t2 = 0.f;
+      for (int j = 4 * lane; j < d; j += 256) add(t2, *(const f4v *)(x + j), mu_chunk(k, j));
+      t2 = wave_sum(t2);
+      if (lane == k) nk = t2;
+    }
   }
-#pragma unroll
-  for (int k = 0; k < kMaxK; ++k)
-    if (k < K && ((keep >> k) & 1u)) nrm[k] = wave_sum(nrm[k]);
-#pragma unroll
-  for (int k = 0; k < kMaxK; ++k)
-    if (k == lane && k < K) a.nrm[row * K + k] = nrm[k];
+  if (act) a.nrm[row * K + lane] = nk;
   if (lane == 0) a.mask[row] = keep;
   // a dropped component's q partials: +inf, 0, ... (one coalesced row block)
   float *q2 = a.qpart + (size_t)row * K * a.ntn;
@@ -972,7 +966,7 @@ static int screen_check(const Model &m, const ScreenArgs &a, const char *what) {
     return SB_E_INVAL;
   }
   if (m.d % 8 != 0 || (uintptr_t)a.X % 16 != 0 || a.ldx % 4 != 0 ||
-      (uintptr_t)m.mu32 % 16 != 0 || (uintptr_t)a.xref % 16 != 0 || !a.rho || !a.bnd ||
+      (uintptr_t)m.mu32 % 16 != 0 || !a.moved || !a.rho || !a.bnd ||
       !a.hasref || !a.nrm || !a.qpart || a.ntn < 1 || !a.mask) {
     set_error("%s: needs d %% 8 == 0, 16-byte rows and the screening state", what);
     return SB_E_INVAL;

@@ -217,9 +217,9 @@ struct ScreenArgs {
   const int32_t *rowmap = nullptr;  // operand row of each row (nullable: the row)
   int64_t nstate = 0;               // operand rows with screening state
   const double *rho = nullptr;      // [K] max_i sum_j |P_k[i][j]| (>= the largest eigenvalue)
-  float *xref = nullptr;            // [nstate][d] last evaluated points
+  const float *moved = nullptr;     // [nstate] |x - x_ref|^2, x_ref the last evaluated point
   double *bnd = nullptr;            // [nstate][2K] lb_k then ub_k
-  int32_t *hasref = nullptr;        // [nstate] 1: x_ref and bounds set, else none yet
+  int32_t *hasref = nullptr;        // [nstate] 1: bounds set (at x_ref), else none yet
   float *nrm = nullptr;             // [cap][K] |x - mu_k|^2 of the listed components
   float *qpart = nullptr;           // [M][K][ntn] q partials of the contraction
   int ntn = 0;
@@ -335,6 +335,9 @@ struct LbfgsBuffers {
   int32_t *status = nullptr, *phase = nullptr, *rowid = nullptr, *active = nullptr;
   int32_t *idx = nullptr, *count = nullptr;       // compacted rows, [B] and [1]
   int64_t *evals = nullptr;                       // [1]
+  // FP32 starts (nullable): [2][B] |trial - what its slot held before|^2, for
+  // the evaluation's screen of mixture components
+  float *moved = nullptr;
   // batches: per-start vector offset/length, total vector length, trial row
   // offsets (per start) and their compacted copy (per compacted row)
   const int64_t *voff = nullptr;
@@ -462,7 +465,7 @@ struct BlockKey {
 struct ExecCtx {
   int device = -1;
   // what a call reads back on its way lands here: small, and one at a time
-  static constexpr size_t kPinnedBytes = 16384;
+  static constexpr size_t kPinnedBytes = 4096;
   void *pinned = nullptr;
   hipEvent_t ev[10];
   bool ev_ok = false;

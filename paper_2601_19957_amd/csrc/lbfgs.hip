@@ -49,6 +49,7 @@ struct LbArgs {
   const int32_t *pmaxit;
   int64_t s_base, s_count;  // starts [s_base, s_base + s_count) of this launch
   int32_t *count_reset;     // compaction count, zeroed by this launch (nullable)
+  float *moved;             // FP32: |trial - its slot's old content|^2 (nullable)
 };
 
 // A thread's chunk [i0, i0 + EPT) of a length-d vector (i0 = tid * EPT), at
@@ -463,13 +464,28 @@ __device__ __forceinline__ void two_loop_stream(const T *Sb, const T *Yb, const 
   for (int e = 0; e < EPT; ++e) p[e] = -q[e];
 }
 
+// |x - o|^2 over a start's threads.
+template <typename T, int TPB, int EPT>
+__device__ __forceinline__ T moved_sq(const T (&x)[EPT], const T (&o)[EPT],
+                                      BlockRed<TPB, T> &red) {
+  T dd = 0;
+#pragma unroll
+  for (int e = 0; e < EPT; ++e) {
+    const T t = x[e] - o[e];
+    dd += t * t;
+  }
+  return red.sum(dd);
+}
+
 // One step of start s by its TPB threads, tid the thread's index among them
 // (every branch is uniform in s).  Returns the row of the trial point to be
 // evaluated, or -1 when the start has stopped.  HREG: the history is held in
 // registers (m <= kMaxHist); otherwise it stays in memory and two_loop_stream
 // reads it (m <= kMaxMem).  HB (FP32, HREG): the ring holds BF16 pairs (s and y
-// rounded to BF16 when formed).
-template <typename T, int TPB, int EPT, bool HREG, bool HB = false>
+// rounded to BF16 when formed).  MV (FP32): the distance that the trial moved its
+// slot is written too; it holds the old point to the end, so only the launches
+// that a screen follows have it.
+template <typename T, int TPB, int EPT, bool HREG, bool HB, bool MV>
 __device__ __forceinline__ int32_t lbfgs_step_one(const LbArgs<T> &a, const int64_t s,
                                                   const int tid, BlockRed<TPB, T> &red) {
   static_assert(!HB || (HREG && sizeof(T) == 4), "BF16 history: FP32, register-resident");
@@ -546,6 +562,12 @@ __device__ __forceinline__ int32_t lbfgs_step_one(const LbArgs<T> &a, const int6
     vload<T, EPT>(pd, i0, d, q);
 #pragma unroll
     for (int e = 0; e < EPT; ++e) c[e] = c[e] + alpha * q[e];
+    if constexpr (MV) {
+      T o[EPT];
+      vload<T, EPT>(xt, i0, d, o);
+      const T dd = moved_sq<T, TPB, EPT>(c, o, red);
+      if (tid == 0) a.moved[(size_t)tr * B + s] = dd;
+    }
     vstore<T, EPT>(xt, i0, d, c);
     if (tid == 0) {
       a.alpha[s] = alpha;
@@ -559,6 +581,7 @@ __device__ __forceinline__ int32_t lbfgs_step_one(const LbArgs<T> &a, const int6
 
   // ---- load the point whose direction we now compute (and, on accept, the old one)
   T x[EPT], gl[EPT], sv[EPT], yv[EPT];
+  [[maybe_unused]] T xold[MV ? EPT : 1];  // (accepted: the old point, in the trial's slot)
   const int newcur = (mode == M_ACCEPT) ? 1 - cur : cur;
   {
     const T *xn = a.X + (size_t)newcur * Lt + vo;
@@ -575,6 +598,7 @@ __device__ __forceinline__ int32_t lbfgs_step_one(const LbArgs<T> &a, const int6
       for (int e = 0; e < EPT; ++e) {
         sv[e] = x[e] - xov[e];
         yv[e] = gov[e] - gl[e];  // grad f(x_t) - grad f(x), grad f = -grad l
+        if constexpr (MV) xold[e] = xov[e];
         if constexpr (HB) {
           sv[e] = bf16_round(sv[e]);
           yv[e] = bf16_round(yv[e]);
@@ -772,6 +796,11 @@ __device__ __forceinline__ int32_t lbfgs_step_one(const LbArgs<T> &a, const int6
   T xtv[EPT];
 #pragma unroll
   for (int e = 0; e < EPT; ++e) xtv[e] = x[e] + p[e];
+  if constexpr (MV) {
+    if (mode != M_ACCEPT) vload<T, EPT>(xt, i0, d, xold);
+    const T dd = moved_sq<T, TPB, EPT>(xtv, xold, red);
+    if (tid == 0) a.moved[(size_t)tr * B + s] = dd;
+  }
   vstore_nt<T, EPT>(pd, i0, d, p);
   vstore<T, EPT>(xt, i0, d, xtv);
   if (tid == 0) {
@@ -797,7 +826,7 @@ __device__ __forceinline__ int32_t lbfgs_step_one(const LbArgs<T> &a, const int6
 // has without spilling (190 registers; with the history in logical order 310,
 // or 256 and spilled).  FP64, m = 8: d = 256, 8192 starts 81 -> 73 us (21
 // vectors moved: 69 us at the copy rate); d = 30, 32768 starts 97 -> 59 us.
-template <typename T, int TPB, int EPT, bool HREG, bool HB = false>
+template <typename T, int TPB, int EPT, bool HREG, bool HB, bool MV>
 __global__ __launch_bounds__(TPB, 2) void lbfgs_step_kernel(LbArgs<T> a) {
   __shared__ T rbuf[2 * BlockRed<TPB, T>::NMAX * (TPB / 64)];
   BlockRed<TPB, T> red{rbuf, 0};
@@ -805,12 +834,19 @@ __global__ __launch_bounds__(TPB, 2) void lbfgs_step_kernel(LbArgs<T> a) {
   // previous count ran before this launch
   if (a.count_reset && blockIdx.x == 0 && threadIdx.x == 0) *a.count_reset = 0;
   if ((int64_t)blockIdx.x < a.s_count)
-    lbfgs_step_one<T, TPB, EPT, HREG, HB>(a, a.s_base + blockIdx.x, threadIdx.x, red);
+    lbfgs_step_one<T, TPB, EPT, HREG, HB, MV>(a, a.s_base + blockIdx.x, threadIdx.x, red);
 }
 
 template <typename T, int TPB, int EPT, bool HREG, bool HB>
 static void step_go(const LbArgs<T> &a, hipStream_t s) {
-  hipLaunchKernelGGL((lbfgs_step_kernel<T, TPB, EPT, HREG, HB>), dim3((unsigned)a.s_count),
+  if constexpr (sizeof(T) == 4) {
+    if (a.moved) {
+      hipLaunchKernelGGL((lbfgs_step_kernel<T, TPB, EPT, HREG, HB, true>),
+                         dim3((unsigned)a.s_count), dim3(TPB), 0, s, a);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((lbfgs_step_kernel<T, TPB, EPT, HREG, HB, false>), dim3((unsigned)a.s_count),
                      dim3(TPB), 0, s, a);
 }
 
@@ -989,6 +1025,7 @@ static LbArgs<T> make_args(const LbfgsBuffers &b, int max_iter, double tol) {
   a.s_base = 0;
   a.s_count = b.B;
   a.count_reset = nullptr;
+  a.moved = sizeof(T) == 4 ? b.moved : nullptr;
   return a;
 }
 
@@ -1088,7 +1125,7 @@ __global__ __launch_bounds__(64 * kBulkWaves<EPT>) void lbfgs_bulk_kernel(BulkAr
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
     int32_t row = -1;
-    if (s < b.lb.B) row = lbfgs_step_one<double, 64, EPT, true, false>(b.lb, s, tid & 63, red);
+    if (s < b.lb.B) row = lbfgs_step_one<double, 64, EPT, true, false, false>(b.lb, s, tid & 63, red);
     asm volatile("" : "+v"(tid));
     if (lane == 0) slot[wave] = row;
     nev += row >= 0;

@@ -207,7 +207,7 @@ struct Evaluator {
   bool screen = false;
   const double *rho = nullptr;  // [K] largest absolute row sum of P_k
   int64_t nstate = 0;           // operand rows with state (both L-BFGS slots)
-  float *xref = nullptr, *nrm = nullptr;
+  float *moved = nullptr, *nrm = nullptr;  // moved: written by the optimiser's step
   double *bnd = nullptr;
   int32_t *hasref = nullptr;
   uint32_t *mask = nullptr;  // [cap]
@@ -230,7 +230,7 @@ struct Evaluator {
       resp = ar.take<float>((size_t)m.K * cap);
       if (screen) {
         nstate = 2 * cap;
-        xref = ar.take<float>((size_t)nstate * m.d);
+        moved = ar.take<float>((size_t)nstate);
         nrm = ar.take<float>((size_t)cap * m.K);
         bnd = ar.take<double>((size_t)nstate * 2 * m.K);
         hasref = ar.take<int32_t>(nstate);
@@ -261,7 +261,7 @@ struct Evaluator {
       sa.rowmap = a.rowmap;
       sa.nstate = nstate;
       sa.rho = rho;
-      sa.xref = xref;
+      sa.moved = moved;
       sa.bnd = bnd;
       sa.hasref = hasref;
       sa.nrm = nrm;
@@ -604,6 +604,7 @@ static int carve_layout(Arena &ar, Layout &L, const sb_loglik *ll, const RunCfg 
   L.bulk.two_stage = bulk_two_stage(ll, rc);
   L.bulk.screen = L.bulk.two_stage && bulk_screen();
   if (L.bulk.carve(ar)) return SB_E_NOMEM;
+  L.lb.moved = L.bulk.moved;
   L.X0b = mixed ? (void *)ar.take<float>((size_t)B * d) : (void *)L.X0;
   L.Xend = ar.take<char>(bes * (size_t)B * d);
   L.lend = ar.take<double>((size_t)B);
