@@ -980,7 +980,7 @@ def sb_combine_dev(lo, hi, logl, logdet, modes):
 
 
 class ExecContext:
-    """sb_exec: pinned readback word, timing events and instantiated block graphs kept
+    """sb_exec: pinned readback buffer, timing events and instantiated block graphs kept
     across whole-path calls on one device (created on the current device)."""
 
     def __init__(self):

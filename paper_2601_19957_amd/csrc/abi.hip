@@ -470,7 +470,7 @@ int32_t sb_evidence(const sb_loglik *ll, const sb_box *box, const sb_config *cfg
   P.nu = ll->nu;
   P.c = ll->logl_offset;
   // a host entry point may allocate: a context of its own for the graphs,
-  // the pinned readback word and the phase timing
+  // the pinned readback buffer and the phase timing
   sb_exec *ex = nullptr;
   if ((st = sb_exec_create(&ex))) {
     (void)hipStreamDestroy(s);

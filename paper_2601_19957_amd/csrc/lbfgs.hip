@@ -16,8 +16,8 @@
 // Points and gradients are double-buffered per start (slots 0/1, `cur` names
 // the accepted point), so accepting a trial swaps a slot index instead of
 // copying.  The history S, Y [B][m][d] is a ring in memory; the kernel loads
-// it into registers in logical order (oldest first) and runs both loops of
-// the recursion with workgroup reductions for the dot products.
+// it into registers by age (newest first) and runs both loops of the recursion
+// with workgroup reductions for the dot products.
 #include <algorithm>
 
 #include "fused_tile.h"
