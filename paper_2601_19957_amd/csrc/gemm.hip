@@ -96,6 +96,7 @@ struct GemmParams {
   int64_t ldy;
   void *qpart;
   GroupView gv;  // grouped mode only
+  int64_t tile0 = 0;  // first row tile of this launch
   int yneg = 0;  // store -Y (a single Gaussian's gradient); q still uses Y
 };
 
@@ -175,7 +176,7 @@ __global__ __launch_bounds__(256, 2) void quad_gemm_vec_kernel(GemmParams g) {
       mt = w / ncol;
     }
     M = g.count ? (int64_t)(*g.count) : g.M;
-    m0 = mt * BM;
+    m0 = (g.tile0 + mt) * BM;
     if (m0 >= M) return;
     ntn = g.ntn;
     k = col / ntn;
@@ -424,22 +425,24 @@ __global__ __launch_bounds__(256, 2) void quad_gemm_vec_kernel(GemmParams g) {
   }
 }
 
+// A launch holds fewer than 2^32 work items, so fewer than 2^24 of these
+// workgroups: more row tiles than that go in several launches (FP64, d = 512, K =
+// 8 in 64 x 128 tiles: past 33.5 million rows).
 template <typename TIn, typename TOp, int BM, int BN, int BK>
-static int launch_t(const GemmParams &p, hipStream_t s) {
-  const int64_t tiles = ceil_div(p.M, BM) * p.K * p.ntn;
-  if (tiles <= 0) return SB_OK;
-  if (tiles > 0x7fffffffll) {
-    set_error("contraction too large for one launch (%lld tiles)", (long long)tiles);
-    return SB_E_UNSUPPORTED;
+static int launch_t(GemmParams p, hipStream_t s) {
+  const int64_t ncol = (int64_t)p.K * p.ntn, rows = ceil_div(p.M, BM);
+  if (ncol <= 0 || rows <= 0) return SB_OK;
+  const int64_t per = ((1 << 24) - 1) / ncol;
+  for (p.tile0 = 0; p.tile0 < rows; p.tile0 += per) {
+    const dim3 grid((unsigned)(std::min(per, rows - p.tile0) * ncol));
+    if (p.a.kind == 0)
+      hipLaunchKernelGGL((quad_gemm_vec_kernel<TIn, TOp, BM, BN, BK, 0, false>), grid, dim3(256),
+                         0, s, p);
+    else
+      hipLaunchKernelGGL((quad_gemm_vec_kernel<TIn, TOp, BM, BN, BK, 1, false>), grid, dim3(256),
+                         0, s, p);
+    SB_LAUNCH_CHECK();
   }
-  const dim3 grid((unsigned)tiles);
-  if (p.a.kind == 0)
-    hipLaunchKernelGGL((quad_gemm_vec_kernel<TIn, TOp, BM, BN, BK, 0, false>), grid,
-                       dim3(256), 0, s, p);
-  else
-    hipLaunchKernelGGL((quad_gemm_vec_kernel<TIn, TOp, BM, BN, BK, 1, false>), grid,
-                       dim3(256), 0, s, p);
-  SB_LAUNCH_CHECK();
   return SB_OK;
 }
 
