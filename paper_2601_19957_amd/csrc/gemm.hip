@@ -266,29 +266,28 @@ __global__ __launch_bounds__(256, 2) void quad_gemm_vec_kernel(GemmParams g) {
     for (int e = 0; e < CE; ++e) v[e] = e < n ? p[e] : (TOp)0;
     return v;
   };
+  // (without mu its values are not used: any row of d values can be read)
+  const TIn *mup = (mu ? mu : X0 + (aoff[0] - ca * NI)) + ca * NI;
+  auto load = [&](int k0) {  // a whole k-tile
 #pragma unroll
-  for (int e = 0; e < NI; ++e) rmu[e] = (TIn)0;
-  auto load = [&](int k0) {
-    if (k0 + BK <= d) {  // (uniform)
-#pragma unroll
-      for (int r = 0; r < NA; ++r) {
-        ra[r] = *(const VI *)(X0 + aoff[r] + k0);
-        if constexpr (KIND == 1) rq[r] = *(const VI *)(X1 + aoff[r] + k0);
-      }
-      if (mu) rmu = *(const VI *)(mu + k0 + ca * NI);
-#pragma unroll
-      for (int r = 0; r < NB; ++r) rb[r] = *(const VO *)(brow[r] + k0);
-    } else {
-      const int na = d - (k0 + ca * NI), nb = d - (k0 + cb * CE);
-#pragma unroll
-      for (int r = 0; r < NA; ++r) {
-        ra[r] = part_i(X0 + aoff[r] + k0, na);
-        if constexpr (KIND == 1) rq[r] = part_i(X1 + aoff[r] + k0, na);
-      }
-      if (mu) rmu = part_i(mu + k0 + ca * NI, na);
-#pragma unroll
-      for (int r = 0; r < NB; ++r) rb[r] = part_o(brow[r] + k0, nb);
+    for (int r = 0; r < NA; ++r) {
+      ra[r] = *(const VI *)(X0 + aoff[r] + k0);
+      if constexpr (KIND == 1) rq[r] = *(const VI *)(X1 + aoff[r] + k0);
     }
+    rmu = *(const VI *)(mup + k0);
+#pragma unroll
+    for (int r = 0; r < NB; ++r) rb[r] = *(const VO *)(brow[r] + k0);
+  };
+  auto load_part = [&](int k0) {  // the one that the rows end in
+    const int na = d - (k0 + ca * NI), nb = d - (k0 + cb * CE);
+#pragma unroll
+    for (int r = 0; r < NA; ++r) {
+      ra[r] = part_i(X0 + aoff[r] + k0, na);
+      if constexpr (KIND == 1) rq[r] = part_i(X1 + aoff[r] + k0, na);
+    }
+    rmu = part_i(mup + k0, na);
+#pragma unroll
+    for (int r = 0; r < NB; ++r) rb[r] = part_o(brow[r] + k0, nb);
   };
   auto store = [&]() {
 #pragma unroll
@@ -305,7 +304,7 @@ __global__ __launch_bounds__(256, 2) void quad_gemm_vec_kernel(GemmParams g) {
 #pragma clang fp contract(off)
           x = ra[r][e] + tpar[r] * (rq[r][e] - ra[r][e]);
         }
-        const TIn v = x - rmu[e];  // (k >= d: both zero)
+        const TIn v = x - (mu ? rmu[e] : (TIn)0);  // (k >= d: both zero)
         if constexpr (sizeof(TOp) == 8)
           w[e] = v;
         else
@@ -342,18 +341,38 @@ __global__ __launch_bounds__(256, 2) void quad_gemm_vec_kernel(GemmParams g) {
         for (int j = 0; j < TN; ++j) acc[i][j] = MF::mma(af[i], bf[j], q, acc[i][j]);
   };
 
-  load(0);
-  for (int k0 = 0; k0 < d; k0 += BK) {
+  // Whole k-tiles, the next one loaded beside the products of one, then the part
+  // behind them.  The loop holds no choice between whole and part: where the two
+  // meet, the registers a load is under way to are copied, and the copy waits for it
+  // ahead of the products (FP32, 16 x 1024, K = 1 36.7 us, without 31.5), and
+  // accumulators go back and forth between register files (128 x 128 x 16 in FP64 26.9 ms
+  // at 16384 x 1024, K = 8).
+  const int kf = d - d % BK;
+  auto mma_all = [&]() {
+#pragma unroll
+    for (int kk = 0; kk < BK; kk += 4 * CE) mma(kk);
+  };
+  if (kf > 0) {
+    load(0);
+    for (int k0 = BK; k0 < kf; k0 += BK) {
+      store();
+      __syncthreads();
+      load(k0);
+      mma_all();
+      __syncthreads();
+    }
     store();
     __syncthreads();
-    if (k0 + BK < d) load(k0 + BK);
-    if (k0 + BK <= d) {
-#pragma unroll
-      for (int kk = 0; kk < BK; kk += 4 * CE) mma(kk);
-    } else {  // (no products of the zeros behind the rows' end)
-      for (int kk = 0; k0 + kk < d; kk += 4 * CE) mma(kk);
-    }
+    if (kf < d) load_part(kf);
+    mma_all();
     __syncthreads();
+  } else {
+    load_part(0);
+  }
+  if (kf < d) {
+    store();
+    __syncthreads();
+    for (int kk = 0; kf + kk < d; kk += 4 * CE) mma(kk);  // (no products of zeros)
   }
 
   // Epilogue: the partial q per row over this tile's columns, then Y.  The
