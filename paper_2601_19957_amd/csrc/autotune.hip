@@ -1,10 +1,10 @@
 // Tile-shape autotuner for the quadratic-form GEMM.
 //
 // The first time a shape class (dtype, d, K, M rounded up to a power of two)
-// is seen, each candidate tile (BM x BN x k-tile: four for FP64 and for FP32,
-// seven with their LDS stages for the BF16 and split contractions) is timed with
-// HIP events, one warm-up and five timed launches, and the fastest is cached
-// for the process.  The launches run on the caller's probe (its operands and
+// is seen, each candidate tile (BM x BN x k-tile: four for FP64, for FP32 and
+// for BF16 at d % 8 != 0, seven with their LDS stages for the BF16 and split
+// contractions) is timed with HIP events, one warm-up and five timed launches,
+// and the fastest is cached for the process.  The launches run on the caller's probe (its operands and
 // scratch outputs, which the real launch overwrites).  Timing synchronises the
 // stream, so a stream under graph capture gets the heuristic choice (not
 // cached).  SB_TILE=BMxBN[xBK[xSTAGES]] forces a shape; SB_AUTOTUNE=0 uses the
@@ -55,23 +55,29 @@ bool time_launches(int dtype, const Model &m, const ASrc &a, QuadOut o, int64_t 
   float best_ms = 0.f;
   bool have = false;
   // (BM, BN, k-tile, stages) of the matrix-core kernels: FP64 and FP32 (32 rows:
-  // FP64 only), BF16.  FP64 at 16384 x 1024, K = 8: 64 x 128 x 16 4.37 ms, 128 x
-  // 128 x 16 4.42, 64 x 64 x 32 4.56, 128 x 64 x 32 4.82, 32 x 64 x 32 5.17; at
-  // 1000 x 203, K = 3: 32 x 64 x 32 14.5 us, 64 x 64 x 32 16.5, 64 x 128 x 16 24.
-  // FP32 at 16384 x 1024, K = 8: 64 x 128 x 16 2.20 ms, 64 x 128 x 32 2.25, 128 x
-  // 64 x 32 2.27, 64 x 64 x 32 2.48; at 8192 x 256: 16.9 us for 64 x 64 x 32, 17.2
-  // for 64 x 128 x 32.
+  // FP64 only), BF16 where d % 8 != 0 (one k-tile), BF16.  FP64 at 16384 x 1024, K =
+  // 8: 128 x 128 x 16 4.19 ms, 64 x 128 x 32 4.31, 64 x 64 x 32 4.34, 64 x 128 x 16
+  // 4.41, 128 x 64 x 32 4.42, 32 x 64 x 32 4.90; with K = 1 0.540, 0.550, 0.545, 0.559,
+  // 0.564, 0.649; at 1000 x 203, K = 3: 32 x 64 x 32 15.0 us, 64 x 64 x 32 15.9, 64 x
+  // 128 x 16 23.1.  FP32 at 16384 x 1024, K = 8: 64 x 128 x 16 2.08 ms, 128 x 128 x 16
+  // 2.10, 64 x 128 x 32 2.17, 64 x 64 x 32 2.23; at 8192 x 256: 64 x 64 x 32 16.2 us,
+  // 64 x 128 x 32 16.4, 64 x 128 x 16 16.6.
   const int cands_f64[4][4] = {{32, 64, 32, 1}, {64, 64, 32, 1}, {64, 128, 16, 1},
                                {128, 128, 16, 1}};
   const int cands_f32[4][4] = {{64, 64, 32, 1}, {64, 128, 16, 1}, {64, 128, 32, 1},
                                {128, 128, 16, 1}};
+  const int cands_b16[4][4] = {{64, 64, 32, 1}, {128, 64, 32, 1}, {64, 128, 32, 1},
+                               {128, 128, 32, 1}};
   const int cands_bf[7][4] = {{128, 128, 32, 1}, {128, 128, 64, 1}, {256, 128, 32, 1},
                               {128, 256, 32, 1}, {256, 256, 32, 1}, {128, 128, 32, 2},
                               {256, 256, 32, 2}};
   const int nc = bf ? 7 : 4;
   for (int c = 0; c < nc && ok; ++c) {
     TileCfg t;
-    const int *cd = bf ? cands_bf[c] : (dtype == DT_F64 ? cands_f64[c] : cands_f32[c]);
+    const int *cd = bf                   ? cands_bf[c]
+                    : dtype == DT_F64  ? cands_f64[c]
+                    : dtype == DT_BF16 ? cands_b16[c]
+                                       : cands_f32[c];
     t.bm = cd[0];
     t.bn = cd[1];
     t.bk = cd[2];

@@ -114,12 +114,12 @@ int quad_gemm_ntn(int dtype, int d, TileCfg t) { return (int)ceil_div(d, t.bn); 
 // row and fragment reads down eight rows both touch every bank once, and a
 // fragment read feeds two (FP64) or four (FP32) MFMAs.  Against rows padded by
 // 16 bytes, read one value at a time, and an element-by-element form for odd d:
-// FP64 16384 x 1024, K = 8 5.24 -> 4.37 ms (63 of the 73 TFLOP/s a large library
-// product reaches here); 1000 x 203, K = 3 26.9 -> 14.5 us; BF16 ray points at
+// FP64 16384 x 1024, K = 8 5.16 -> 4.19 ms (66 of the 73 TFLOP/s a large library
+// product reaches here); 1000 x 203, K = 3 28.3 -> 15.0 us; BF16 ray points at
 // d = 500 2.1 -> 0.65 ms.  A second LDS stage (one barrier per k-tile) cost more
-// occupancy than it saved waits: 4.50 ms and 15.7 us at the same shapes.  Large
-// shapes are bound by the matrix cores; small ones (8192 x 256: 27.5 us, 13.7 us
-// of MFMAs) by the fill and drain of their one round of workgroups.
+// occupancy than it saved waits: 4.50 against 4.37 ms and 15.7 against 14.5 us at the
+// same shapes.  Large shapes are bound by the matrix cores; small ones (8192 x 256:
+// 26.9 us, 13.7 us of MFMAs) by the fill and drain of their one round of workgroups.
 template <typename T, int N>
 struct VecU {  // N values of T at T's own alignment
   typedef T v __attribute__((ext_vector_type(N), aligned(sizeof(T))));
