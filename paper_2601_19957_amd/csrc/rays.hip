@@ -132,24 +132,26 @@ int launch_ray_argmax(int R, int n_pts, int dtype, const void *l, double *best_l
 // Rank of each ray by (best l descending, index ascending), NaN as -inf; the
 // first n_starts ranks name the starts.  A workgroup ranks 64 rays: lane l of
 // every wave holds ray 64 b + l, and wave w counts the rays of the w-th
-// sixteenth of the array that precede it; the 16 partial counts are added in
-// LDS.  The keys are read 64 at a time, one per lane, and taken from there
-// lane by lane, with one comparison where the 64 lie on one side of the
-// workgroup's rays.  Bound by the comparisons, R^2 of them: 36 -> 17 us for
+// sixteenth of the array (in whole 64s) that precede it; the 16 partial counts
+// are added in LDS.  The keys are read 64 at a time, one per lane, and taken from
+// there lane by lane, with one comparison where the 64 lie on one side of the
+// workgroup's rays.  Up to 512 rays a sixteenth is its exact share and only its
+// own keys are compared (64 rays: 7.0 us with 64 comparisons a wave, 2.2 with four).  Bound by the comparisons, R^2 of them: 36 -> 17 us for
 // 4096 rays, 135 -> 57 us for 16384.
 constexpr int TOPN_PARTS = 16;
 __global__ __launch_bounds__(64 * TOPN_PARTS) void topn_kernel(int R, int n_starts,
                                                                const double *best_l,
                                                                int32_t *start_ray) {
   __shared__ int part[TOPN_PARTS][64];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, w = uniform((int)(threadIdx.x >> 6));
   const int r = blockIdx.x * 64 + lane;
   double key = -INFINITY;
   if (r < R) {
     key = best_l[r];
     if (key != key) key = -INFINITY;
   }
-  const int seg = (R + TOPN_PARTS - 1) / TOPN_PARTS;
+  const int unit = R <= 32 * TOPN_PARTS ? 1 : 64;
+  const int seg = (R + unit * TOPN_PARTS - 1) / (unit * TOPN_PARTS) * unit;
   const int t0 = w * seg, t1 = min(R, t0 + seg);
   int cnt = 0;
   for (int tb = t0; tb < t1; tb += 64) {
@@ -159,7 +161,12 @@ __global__ __launch_bounds__(64 * TOPN_PARTS) void topn_kernel(int R, int n_star
       if (kv != kv) kv = -INFINITY;
     }
     const int r0 = blockIdx.x * 64;
-    if (tb + 63 < r0) {  // all of lower index
+    if (unit == 1) {
+      for (int i = 0; i < t1 - tb; ++i) {
+        const double v = wave_value(kv, i);
+        cnt += (v > key) || (v == key && tb + i < r);
+      }
+    } else if (tb + 63 < r0) {  // all of lower index
 #pragma unroll 16
       for (int i = 0; i < 64; ++i) cnt += wave_value(kv, i) >= key;
     } else if (tb > r0 + 63) {  // all of higher index

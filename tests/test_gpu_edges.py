@@ -38,3 +38,19 @@ def test_contraction_past_one_launch(L, monkeypatch):
         p0, p1 = out["P0"][r].cpu().numpy(), out["P1"][r].cpu().numpy()
         want = np.max(O.logl(prob, p0 + t * (p1 - p0), grad=False))
         assert abs(bl[r] - want) <= 1e-11 * max(1.0, abs(want)), r
+
+
+@pytest.mark.parametrize("R", [1, 5, 64, 65, 130, 512, 513, 1000, 1024, 1040, 3001])
+def test_ray_ranking_by_size(L, R):
+    """Shares of single keys (up to 512 rays) and of whole 64s (the last of them part empty, and
+    waves without any), with many equal maxima: the start rays are those of a stable sort of
+    the rays' best l, descending, ties to the lower index."""
+    d, npts = 4, 8
+    prob = synth.Problem(family=synth.FAMILY_GAUSS_MIX, norm=synth.NORM_DENSITY, d=d, K=1,
+                         log_w=np.zeros(1), mu=np.zeros((1, d)),
+                         prec=(1e-15 * np.eye(d))[None], nu=0.0, logl_offset=0.0,
+                         lo=-np.ones(d), hi=np.ones(d), sum_log_lambda=np.array([d * 34.5]))
+    out = L.sb_discover_dev(L.DeviceModel(prob), R, npts, R, 5)
+    bl = out["ray_best_l"].cpu().numpy()
+    assert R < 64 or len(np.unique(bl)) < R // 2
+    assert np.array_equal(out["start_ray"].cpu().numpy(), np.argsort(-bl, kind="stable"))
