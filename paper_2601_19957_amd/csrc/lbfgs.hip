@@ -54,8 +54,13 @@ struct LbArgs {
 
 // A thread's chunk [i0, i0 + EPT) of a length-d vector (i0 = tid * EPT), at
 // whatever element the vector starts: a whole chunk is one access of 16-byte
-// pieces (global memory takes them at any alignment); the chunk that crosses
-// the end takes its whole pieces and the values behind them one by one.
+// pieces (global memory takes them at any alignment), the chunk that crosses
+// the end is taken one value at a time, and chunks past it are zero.  What the
+// loads cost is their waits, so nothing in them may ask for one: zeros come first (in
+// the branch that takes them they would wait for the load of the other lanes), and
+// the byte offset is formed once (formed at each load it lands in the load's own
+// destination).  FP64, m = 8, 4096 starts of d = 203: 46.8 -> 37.9 us, d = 401
+// 97 -> 66; FP32 d = 1000 94 -> 66.
 // NT: the streaming form, for the history ring and the direction, which are
 // read and written once per step and not again before the whole batch has moved
 // several times the size of the last-level cache: non-temporal accesses keep
@@ -93,58 +98,63 @@ __device__ inline void piece_store(T *p, const T *v) {
       *(vt *)p = w;
   }
 }
+// Where a thread's chunk begins: its first element, and the byte offset in a vector
+// of T, which the compiler is kept from forming anew at each load (not with eight
+// values a thread, whose registers are the shorter: 16384 starts of d = 1024 with
+// the history in BF16 lost 7% by it).
+struct ChunkAt {
+  int i0;
+  uint32_t off;
+  template <int EPT, typename T>
+  __device__ const T *at(const T *p) const {
+    return EPT > 4 ? p + i0 : (const T *)((const char *)p + off);
+  }
+};
 template <typename T, int EPT>
-constexpr int kPiece = EPT < (int)(16 / sizeof(T)) ? EPT : (int)(16 / sizeof(T));
+__device__ inline ChunkAt chunk_at(int tid) {
+  ChunkAt a{tid * EPT, (uint32_t)(tid * EPT) * (uint32_t)sizeof(T)};
+  if constexpr (EPT <= 4) asm volatile("" : "+v"(a.off));
+  return a;
+}
 template <typename T, int EPT, bool NT>
-__device__ inline void chunk_load(const T *p, int i0, int d, T (&v)[EPT]) {
-  constexpr int N = kPiece<T, EPT>;
-  if (i0 + EPT <= d) {
-    piece_load<T, EPT, NT>(p + i0, v);
-    return;
-  }
+__device__ inline void chunk_load(const T *p, ChunkAt at, int d, T (&v)[EPT]) {
+  const T *q = at.template at<EPT>(p);
 #pragma unroll
-  for (int q = 0; q < EPT; q += N) {
-    if (i0 + q + N <= d) {
-      piece_load<T, N, NT>(p + i0 + q, &v[q]);
-    } else {
+  for (int e = 0; e < EPT; ++e) v[e] = (T)0;
+  if (at.i0 + EPT <= d) piece_load<T, EPT, NT>(q, v);
+  if (d % EPT != 0) {  // (uniform)
+    const bool part = at.i0 + EPT > d;
 #pragma unroll
-      for (int e = q; e < q + N; ++e) v[e] = (i0 + e < d) ? p[i0 + e] : (T)0;
-    }
+    for (int e = 0; e < EPT; ++e)
+      if (part && at.i0 + e < d) v[e] = q[e];
   }
 }
 template <typename T, int EPT, bool NT>
-__device__ inline void chunk_store(T *p, int i0, int d, const T (&v)[EPT]) {
-  constexpr int N = kPiece<T, EPT>;
-  if (i0 + EPT <= d) {
-    piece_store<T, EPT, NT>(p + i0, v);
-    return;
-  }
+__device__ inline void chunk_store(T *p, ChunkAt at, int d, const T (&v)[EPT]) {
+  T *q = (T *)at.template at<EPT>(p);
+  if (at.i0 + EPT <= d) piece_store<T, EPT, NT>(q, v);
+  if (d % EPT != 0) {
+    const bool part = at.i0 + EPT > d;
 #pragma unroll
-  for (int q = 0; q < EPT; q += N) {
-    if (i0 + q + N <= d) {
-      piece_store<T, N, NT>(p + i0 + q, &v[q]);
-    } else {
-#pragma unroll
-      for (int e = q; e < q + N; ++e)
-        if (i0 + e < d) p[i0 + e] = v[e];
-    }
+    for (int e = 0; e < EPT; ++e)
+      if (part && at.i0 + e < d) q[e] = v[e];
   }
 }
 template <typename T, int EPT>
-__device__ inline void vload(const T *p, int i0, int d, T (&v)[EPT]) {
-  chunk_load<T, EPT, false>(p, i0, d, v);
+__device__ inline void vload(const T *p, ChunkAt at, int d, T (&v)[EPT]) {
+  chunk_load<T, EPT, false>(p, at, d, v);
 }
 template <typename T, int EPT>
-__device__ inline void vstore(T *p, int i0, int d, const T (&v)[EPT]) {
-  chunk_store<T, EPT, false>(p, i0, d, v);
+__device__ inline void vstore(T *p, ChunkAt at, int d, const T (&v)[EPT]) {
+  chunk_store<T, EPT, false>(p, at, d, v);
 }
 template <typename T, int EPT>
-__device__ inline void vload_nt(const T *p, int i0, int d, T (&v)[EPT]) {
-  chunk_load<T, EPT, true>(p, i0, d, v);
+__device__ inline void vload_nt(const T *p, ChunkAt at, int d, T (&v)[EPT]) {
+  chunk_load<T, EPT, true>(p, at, d, v);
 }
 template <typename T, int EPT>
-__device__ inline void vstore_nt(T *p, int i0, int d, const T (&v)[EPT]) {
-  chunk_store<T, EPT, true>(p, i0, d, v);
+__device__ inline void vstore_nt(T *p, ChunkAt at, int d, const T (&v)[EPT]) {
+  chunk_store<T, EPT, true>(p, at, d, v);
 }
 
 // The history ring in BF16 (FP32 starts): a thread's EPT values as EPT
@@ -227,18 +237,18 @@ __device__ inline void hload_raw_nt(const uint16_t *p, int i0, uint32_t (&w)[EPT
 }
 // Ring access for history type HB (BF16 when true, else T).
 template <typename T, int EPT, bool HB>
-__device__ inline void ring_load(const T *base, size_t off, int i0, int d, T (&v)[EPT]) {
+__device__ inline void ring_load(const T *base, size_t off, ChunkAt at, int d, T (&v)[EPT]) {
   if constexpr (HB)
-    hload_nt<EPT>((const uint16_t *)base + off, i0, d, v);
+    hload_nt<EPT>((const uint16_t *)base + off, at.i0, d, v);
   else
-    vload_nt<T, EPT>(base + off, i0, d, v);
+    vload_nt<T, EPT>(base + off, at, d, v);
 }
 template <typename T, int EPT, bool HB>
-__device__ inline void ring_store(T *base, size_t off, int i0, int d, const T (&v)[EPT]) {
+__device__ inline void ring_store(T *base, size_t off, ChunkAt at, int d, const T (&v)[EPT]) {
   if constexpr (HB)
-    hstore_nt<EPT>((uint16_t *)base + off, i0, d, v);
+    hstore_nt<EPT>((uint16_t *)base + off, at.i0, d, v);
   else
-    vstore_nt<T, EPT>(base + off, i0, d, v);
+    vstore_nt<T, EPT>(base + off, at, d, v);
 }
 
 // A thread's slices of the kMaxHist register-resident history vectors:
@@ -384,7 +394,7 @@ __device__ __forceinline__ void two_loop_stream(const T *Sb, const T *Yb, const 
                                        int head, int cnt, bool reg_new,
                                        const T (&sn)[EPT], const T (&yn)[EPT], T rn, T gamma,
                                        const T (&g)[EPT], T (&p)[EPT], BlockRed<TPB, T> &red) {
-  const int i0 = threadIdx.x * EPT;
+  const ChunkAt at = chunk_at<T, EPT>(threadIdx.x);
   T q[EPT], al[kMaxMem];
 #pragma unroll
   for (int e = 0; e < EPT; ++e) q[e] = g[e];
@@ -402,35 +412,47 @@ __device__ __forceinline__ void two_loop_stream(const T *Sb, const T *Yb, const 
     }
     const int ph = slot(j);
     if (last) {
-      vload_nt<T, EPT>(Sb + (size_t)ph * d, i0, d, sv);
-      vload_nt<T, EPT>(Yb + (size_t)ph * d, i0, d, yv);
+      vload_nt<T, EPT>(Sb + (size_t)ph * d, at, d, sv);
+      vload_nt<T, EPT>(Yb + (size_t)ph * d, at, d, yv);
     } else {
-      vload<T, EPT>(Sb + (size_t)ph * d, i0, d, sv);
-      vload<T, EPT>(Yb + (size_t)ph * d, i0, d, yv);
+      vload<T, EPT>(Sb + (size_t)ph * d, at, d, sv);
+      vload<T, EPT>(Yb + (size_t)ph * d, at, d, yv);
     }
     rv = rho[ph];
   };
-  T cs[EPT], cy[EPT], cr = 0;
-  if (cnt > 0) fetch(cnt - 1, cs, cy, cr, false);
+  // Two buffers by turns: a copy from one to the other would wait for the pair
+  // under way ahead of the current one's reduction (FP64, m = 32, 1024 starts of
+  // d = 199: 74 us against 56).  FP64 copies all the same where the registers of two
+  // buffers cost a wave per SIMD that tells more: m = 12, 4096 starts of d = 128 44 us
+  // against 36, d = 402 129 against 112.
+  constexpr bool TURNS = sizeof(T) == 4 || (EPT > 2 && TPB == 64);
+  T sb[2][EPT], yb[2][EPT], rb[2] = {0, 0};
+  if (cnt > 0) {
+    if (TURNS && cnt % 2 == 0)
+      fetch(cnt - 1, sb[1], yb[1], rb[1], false);
+    else
+      fetch(cnt - 1, sb[0], yb[0], rb[0], false);
+  }
 #pragma unroll
   for (int j = kMaxMem - 1; j >= 0; --j) {
     if (j < cnt) {
+      const int c = TURNS ? j % 2 : 0, n = 1 - c;
       T ns[EPT], ny[EPT], nr = 0;
-      if (j > 0) fetch(j - 1, ns, ny, nr, false);
+      if (j > 0) fetch(j - 1, TURNS ? sb[n] : ns, TURNS ? yb[n] : ny, TURNS ? rb[n] : nr, false);
       T dd = 0;
 #pragma unroll
-      for (int e = 0; e < EPT; ++e) dd += cs[e] * q[e];
+      for (int e = 0; e < EPT; ++e) dd += sb[c][e] * q[e];
       dd = red.sum(dd);
-      al[j] = cr * dd;
+      al[j] = rb[c] * dd;
 #pragma unroll
-      for (int e = 0; e < EPT; ++e) q[e] -= al[j] * cy[e];
-      if (j > 0) {
+      for (int e = 0; e < EPT; ++e) q[e] -= al[j] * yb[c][e];
+      if (!TURNS && j > 0) {
 #pragma unroll
         for (int e = 0; e < EPT; ++e) {
-          cs[e] = ns[e];
-          cy[e] = ny[e];
+          sb[0][e] = ns[e];
+          yb[0][e] = ny[e];
         }
-        cr = nr;
+        rb[0] = nr;
       }
     } else {
       al[j] = 0;
@@ -438,25 +460,27 @@ __device__ __forceinline__ void two_loop_stream(const T *Sb, const T *Yb, const 
   }
 #pragma unroll
   for (int e = 0; e < EPT; ++e) q[e] *= gamma;
-  if (cnt > 0) fetch(0, cs, cy, cr, true);
+  if (cnt > 0) fetch(0, sb[0], yb[0], rb[0], true);
 #pragma unroll
   for (int j = 0; j < kMaxMem; ++j) {
     if (j < cnt) {
+      const int c = TURNS ? j % 2 : 0, n = 1 - c;
       T ns[EPT], ny[EPT], nr = 0;
-      if (j + 1 < cnt) fetch(j + 1, ns, ny, nr, true);
+      if (j + 1 < cnt)
+        fetch(j + 1, TURNS ? sb[n] : ns, TURNS ? yb[n] : ny, TURNS ? rb[n] : nr, true);
       T bb = 0;
 #pragma unroll
-      for (int e = 0; e < EPT; ++e) bb += cy[e] * q[e];
-      bb = cr * red.sum(bb);
+      for (int e = 0; e < EPT; ++e) bb += yb[c][e] * q[e];
+      bb = rb[c] * red.sum(bb);
 #pragma unroll
-      for (int e = 0; e < EPT; ++e) q[e] += (al[j] - bb) * cs[e];
-      if (j + 1 < cnt) {
+      for (int e = 0; e < EPT; ++e) q[e] += (al[j] - bb) * sb[c][e];
+      if (!TURNS && j + 1 < cnt) {
 #pragma unroll
         for (int e = 0; e < EPT; ++e) {
-          cs[e] = ns[e];
-          cy[e] = ny[e];
+          sb[0][e] = ns[e];
+          yb[0][e] = ny[e];
         }
-        cr = nr;
+        rb[0] = nr;
       }
     }
   }
@@ -513,7 +537,7 @@ __device__ __forceinline__ int32_t lbfgs_step_one(const LbArgs<T> &a, const int6
   const int d = dv;
   const int64_t vo = vov;
   const int64_t Lt = a.Ltot;
-  const int i0 = tid * EPT;  // this thread's chunk of every vector
+  const ChunkAt at = chunk_at<T, EPT>(tid);  // this thread's chunk of every vector
   T tol = a.tol;
   int max_iter = a.max_iter;
   if (a.sprob) {
@@ -558,17 +582,17 @@ __device__ __forceinline__ int32_t lbfgs_step_one(const LbArgs<T> &a, const int6
     T *xt = a.X + (size_t)tr * Lt + vo;
     const T *pd = a.Pd + vo;
     T c[EPT], q[EPT];
-    vload<T, EPT>(xc, i0, d, c);
-    vload<T, EPT>(pd, i0, d, q);
+    vload<T, EPT>(xc, at, d, c);
+    vload<T, EPT>(pd, at, d, q);
 #pragma unroll
     for (int e = 0; e < EPT; ++e) c[e] = c[e] + alpha * q[e];
     if constexpr (MV) {
       T o[EPT];
-      vload<T, EPT>(xt, i0, d, o);
+      vload<T, EPT>(xt, at, d, o);
       const T dd = moved_sq<T, TPB, EPT>(c, o, red);
       if (tid == 0) a.moved[(size_t)tr * B + s] = dd;
     }
-    vstore<T, EPT>(xt, i0, d, c);
+    vstore<T, EPT>(xt, at, d, c);
     if (tid == 0) {
       a.alpha[s] = alpha;
       a.ls[s] = lsn;
@@ -588,12 +612,12 @@ __device__ __forceinline__ int32_t lbfgs_step_one(const LbArgs<T> &a, const int6
     const T *gn = a.G + (size_t)newcur * Lt + vo;
     const T *xo = a.X + (size_t)cur * Lt + vo;
     const T *go = a.G + (size_t)cur * Lt + vo;
-    vload<T, EPT>(xn, i0, d, x);
-    vload<T, EPT>(gn, i0, d, gl);
+    vload<T, EPT>(xn, at, d, x);
+    vload<T, EPT>(gn, at, d, gl);
     if (mode == M_ACCEPT) {
       T xov[EPT], gov[EPT];
-      vload<T, EPT>(xo, i0, d, xov);
-      vload<T, EPT>(go, i0, d, gov);
+      vload<T, EPT>(xo, at, d, xov);
+      vload<T, EPT>(go, at, d, gov);
 #pragma unroll
       for (int e = 0; e < EPT; ++e) {
         sv[e] = x[e] - xov[e];
@@ -630,7 +654,7 @@ __device__ __forceinline__ int32_t lbfgs_step_one(const LbArgs<T> &a, const int6
   if constexpr (HREG) {
     // packed BF16 history in whole chunks: the raw words go straight
     // to registers, every load issued before the first use
-    const bool raw = PK && i0 + EPT <= d;
+    const bool raw = PK && at.i0 + EPT <= d;
     if (mode == M_ACCEPT) nset = cnt < m ? cnt : m - 1;
 #pragma unroll
     for (int j = 1; j < kMaxHist; ++j) {
@@ -638,18 +662,18 @@ __device__ __forceinline__ int32_t lbfgs_step_one(const LbArgs<T> &a, const int6
         const size_t off = hist0 + (uint32_t)(slot(j - 1) * d);  // (m, d <= 32, 4096)
         if constexpr (PK) {
           if (raw) {
-            hload_raw_nt<EPT>((const uint16_t *)a.S + off, i0, Sr.w[j]);
-            hload_raw_nt<EPT>((const uint16_t *)a.Yh + off, i0, Yr.w[j]);
+            hload_raw_nt<EPT>((const uint16_t *)a.S + off, at.i0, Sr.w[j]);
+            hload_raw_nt<EPT>((const uint16_t *)a.Yh + off, at.i0, Yr.w[j]);
           } else {
             T t[EPT];
-            ring_load<T, EPT, HB>(a.S, off, i0, d, t);
+            ring_load<T, EPT, HB>(a.S, off, at, d, t);
             Sr.set(j, t);
-            ring_load<T, EPT, HB>(a.Yh, off, i0, d, t);
+            ring_load<T, EPT, HB>(a.Yh, off, at, d, t);
             Yr.set(j, t);
           }
         } else {
-          ring_load<T, EPT, HB>(a.S, off, i0, d, Sr.v[j]);
-          ring_load<T, EPT, HB>(a.Yh, off, i0, d, Yr.v[j]);
+          ring_load<T, EPT, HB>(a.S, off, at, d, Sr.v[j]);
+          ring_load<T, EPT, HB>(a.Yh, off, at, d, Yr.v[j]);
         }
       }
     }
@@ -676,8 +700,8 @@ __device__ __forceinline__ int32_t lbfgs_step_one(const LbArgs<T> &a, const int6
     if (uniform(sy > (T)1e-10 * sqrt(ss) * sqrt(yy))) {
       const T rnew = (T)1 / sy;
       // store the pair in the ring and append it to the logical history
-      ring_store<T, EPT, HB>(a.S, (size_t)m * vo + (size_t)head * d, i0, d, sv);
-      ring_store<T, EPT, HB>(a.Yh, (size_t)m * vo + (size_t)head * d, i0, d, yv);
+      ring_store<T, EPT, HB>(a.S, (size_t)m * vo + (size_t)head * d, at, d, sv);
+      ring_store<T, EPT, HB>(a.Yh, (size_t)m * vo + (size_t)head * d, at, d, yv);
       if (tid == 0) {
         a.rho[(size_t)s * m + head] = rnew;
         a.yy[(size_t)s * m + head] = yy;
@@ -700,9 +724,9 @@ __device__ __forceinline__ int32_t lbfgs_step_one(const LbArgs<T> &a, const int6
         // (its slot is the one that the refused pair would have taken)
         old0 = true;
         T t[EPT];
-        ring_load<T, EPT, HB>(a.S, hist0 + (size_t)head * d, i0, d, t);
+        ring_load<T, EPT, HB>(a.S, hist0 + (size_t)head * d, at, d, t);
         Sr.set(0, t);
-        ring_load<T, EPT, HB>(a.Yh, hist0 + (size_t)head * d, i0, d, t);
+        ring_load<T, EPT, HB>(a.Yh, hist0 + (size_t)head * d, at, d, t);
         Yr.set(0, t);
         if (lane == 0) rh = rho_s[head];
       }
@@ -797,12 +821,12 @@ __device__ __forceinline__ int32_t lbfgs_step_one(const LbArgs<T> &a, const int6
 #pragma unroll
   for (int e = 0; e < EPT; ++e) xtv[e] = x[e] + p[e];
   if constexpr (MV) {
-    if (mode != M_ACCEPT) vload<T, EPT>(xt, i0, d, xold);
+    if (mode != M_ACCEPT) vload<T, EPT>(xt, at, d, xold);
     const T dd = moved_sq<T, TPB, EPT>(xtv, xold, red);
     if (tid == 0) a.moved[(size_t)tr * B + s] = dd;
   }
-  vstore_nt<T, EPT>(pd, i0, d, p);
-  vstore<T, EPT>(xt, i0, d, xtv);
+  vstore_nt<T, EPT>(pd, at, d, p);
+  vstore<T, EPT>(xt, at, d, xtv);
   if (tid == 0) {
     a.alpha[s] = (T)1;
     a.gtp[s] = gtp;
@@ -892,15 +916,15 @@ __global__ __launch_bounds__(TPB) void two_loop_kernel(int d, int m, const int32
     // rho_j and gamma from one pass over the pairs, then the streamed
     // recursion (logical order is the slot order: head = cnt mod m)
     __shared__ T rho_s[kMaxMem];
-    const int i0 = tid * EPT;
+    const ChunkAt at = chunk_at<T, EPT>(tid);
     T g[EPT], p[EPT], z[EPT], gamma = 1;
 #pragma unroll
     for (int e = 0; e < EPT; ++e) z[e] = 0;
-    vload<T, EPT>(G + (size_t)b * d, i0, d, g);
+    vload<T, EPT>(G + (size_t)b * d, at, d, g);
     for (int j = 0; j < cnt; ++j) {
       T sv[EPT], yv[EPT];
-      vload<T, EPT>(S + ((size_t)b * m + j) * d, i0, d, sv);
-      vload<T, EPT>(Y + ((size_t)b * m + j) * d, i0, d, yv);
+      vload<T, EPT>(S + ((size_t)b * m + j) * d, at, d, sv);
+      vload<T, EPT>(Y + ((size_t)b * m + j) * d, at, d, yv);
       T v2[2] = {0, 0};
 #pragma unroll
       for (int e = 0; e < EPT; ++e) {
@@ -914,19 +938,19 @@ __global__ __launch_bounds__(TPB) void two_loop_kernel(int d, int m, const int32
     __syncthreads();
     two_loop_stream<T, TPB, EPT>(S + (size_t)b * m * d, Y + (size_t)b * m * d, rho_s, d, m,
                                  cnt % m, cnt, false, z, z, (T)0, gamma, g, p, red);
-    vstore<T, EPT>(P + (size_t)b * d, i0, d, p);
+    vstore<T, EPT>(P + (size_t)b * d, at, d, p);
     return;
   }
   HistReg<T, EPT, false> Sr, Yr;
   T rh = 0, g[EPT], p[EPT];
   T gamma = 1;
-  const int i0 = tid * EPT;
-  vload<T, EPT>(G + (size_t)b * d, i0, d, g);
+  const ChunkAt at = chunk_at<T, EPT>(tid);
+  vload<T, EPT>(G + (size_t)b * d, at, d, g);
 #pragma unroll
   for (int j = 0; j < kMaxHist; ++j) {
     if (j < cnt) {
-      vload<T, EPT>(S + ((size_t)b * m + (cnt - 1 - j)) * d, i0, d, Sr.v[j]);
-      vload<T, EPT>(Y + ((size_t)b * m + (cnt - 1 - j)) * d, i0, d, Yr.v[j]);
+      vload<T, EPT>(S + ((size_t)b * m + (cnt - 1 - j)) * d, at, d, Sr.v[j]);
+      vload<T, EPT>(Y + ((size_t)b * m + (cnt - 1 - j)) * d, at, d, Yr.v[j]);
       T v2[2] = {0, 0};
 #pragma unroll
       for (int e = 0; e < EPT; ++e) {
@@ -939,7 +963,7 @@ __global__ __launch_bounds__(TPB) void two_loop_kernel(int d, int m, const int32
     }
   }
   two_loop<T, TPB, EPT>(Sr, Yr, rh, gamma, cnt, cnt > 0 ? cnt - 1 : 0, false, g, p, red);
-  vstore<T, EPT>(P + (size_t)b * d, i0, d, p);
+  vstore<T, EPT>(P + (size_t)b * d, at, d, p);
 }
 
 // ------------------------------------------------------------- dispatch

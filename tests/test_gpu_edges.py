@@ -54,3 +54,32 @@ def test_ray_ranking_by_size(L, R):
     bl = out["ray_best_l"].cpu().numpy()
     assert R < 64 or len(np.unique(bl)) < R // 2
     assert np.array_equal(out["start_ray"].cpu().numpy(), np.argsort(-bl, kind="stable"))
+
+
+@pytest.mark.parametrize("d,m,steps", [(129, 8, 20), (203, 8, 20), (203, 12, 24), (255, 8, 20),
+                                       (402, 12, 24), (509, 8, 20), (1021, 8, 20), (1022, 12, 24)])
+def test_lbfgs_path_of_ragged_rows(L, d, m, steps):
+    """L-BFGS on rows that end inside a thread's chunk, one wave and several, history in
+    registers and streamed: the FP64 points after `steps` accepted steps are the oracle's (whose own
+    paths move by at most 1.4e-14 relative under 1e-15 perturbations of these starts; 1e-10 leaves
+    room for d-term sums in another order at each step).  In FP32 and with the BF16 history the
+    iterations to |grad| <= 2e-4 stay within 1.5 and 2 times the oracle's 43 to 47 (steepest descent
+    at this condition number, 50, needs about 290)."""
+    rng = np.random.Generator(np.random.PCG64(760 + d))
+    P, _ = synth.random_precision(rng, d, 0.02, 1.0)
+    mu = rng.uniform(-2, 2, (1, d))
+    prob = synth.Problem(0, 0, d, 1, np.zeros(1), mu, P[None], 0.0, 0.0, -9 * np.ones(d),
+                         9 * np.ones(d), np.zeros(1))
+    X0 = mu + rng.uniform(-3, 3, (4, d))
+    md = L.DeviceModel(prob, low_precision=True)
+    out = L.sb_lbfgs_dev(md, dev(X0), m=m, max_iter=steps, grad_tol=1e-14)
+    x = out["x"].cpu().numpy()
+    op = O.OracleProblem(prob)
+    for s in range(4):
+        r = O.lbfgs(prob, X0[s], m=m, max_iter=steps, grad_tol=1e-14, op=op)
+        assert np.max(np.abs(x[s] - r["x"])) <= 1e-10 * max(1.0, np.max(np.abs(r["x"]))), s
+    want = max(O.lbfgs(prob, x0, m=m, max_iter=400, grad_tol=2e-4, op=op)["iters"] for x0 in X0)
+    for h16 in (False, True) if m == 8 else (False,):
+        it = L.sb_lbfgs_dev(md, dev(X0).float(), m=m, grad_tol=2e-4, max_iter=400,
+                            hist_bf16=h16)["iters"]
+        assert int(it.max()) <= (2.0 if h16 else 1.5) * want
