@@ -51,7 +51,8 @@ template <int CTRL>
 __device__ inline int dpp_mov(int v) {
   return __builtin_amdgcn_mov_dpp(v, CTRL, 0xf, 0xf, true);
 }
-constexpr int kDppRor8 = 0x128, kDppRor4 = 0x124, kDppXor2 = 0x4e, kDppXor1 = 0xb1, kDppHalfMirror = 0x141, kDppShl1 = 0x101;
+constexpr int kDppRor8 = 0x128, kDppRor4 = 0x124, kDppXor2 = 0x4e, kDppXor1 = 0xb1,
+              kDppHalfMirror = 0x141;
 template <int CTRL>
 __device__ inline float dpp_val(float v) {
   return __int_as_float(dpp_mov<CTRL>(__float_as_int(v)));

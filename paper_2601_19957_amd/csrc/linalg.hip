@@ -5,19 +5,21 @@
 // positive definite, i.e. the candidate is not a maximum (saddle filter of
 // GreenDragon, generalised).
 //
-// Blocked right-looking factorisation with 64-wide panels, one launch per panel
-// for every matrix of the batch, of one size or of their own.  What bounds a
-// factorisation of few matrices is the chain of its panels, so a launch does all
-// of a panel at once: the workgroup of each trailing tile (I, J) solves the
+// Blocked right-looking factorisation with 64-wide panels, one or two launches per
+// panel for every matrix of the batch, of one size or of their own.  What bounds a
+// factorisation of few matrices is the chain of its panels, so there one launch does
+// all of a panel at once: the workgroup of each trailing tile (I, J) solves the
 // panel rows of I and J itself (L's 64 x 64 block by 16 x 16 blocks, their
 // inverses and the products on the FP64 matrix cores) and subtracts X_I X_J^T;
 // the workgroup of the first trailing tile goes on to factor it, the next
 // panel's diagonal block.  Other workgroups still read the unsolved panel rows,
 // so the solved ones go to the mirrored block of the upper triangle first and
-// are moved by the next launch.  n = 1024, 8 matrices: 0.66 ms (27 us a panel
-// where few tiles are left, of which the pivots take 16); three launches
-// per panel (diagonal block, panel solve, trailing update, each element updated
-// one column at a time) took 1.08 ms.
+// are moved by the next launch.  Where a panel has more tiles than the chip has CUs, a
+// launch of its own solves its rows once, in place, and the tiles read them; the
+// arithmetic and the results are the same.  n = 1024: 1 matrix 0.45 ms (27 us a panel
+// where few tiles are left, of which the pivots take 16), 8 0.57, 64 1.71; three
+// launches per panel (diagonal block, panel solve, trailing update, each element
+// updated one column at a time) took 0.90, 1.09 and 2.40 ms.
 #include <algorithm>
 
 #include "internal.h"
@@ -58,10 +60,6 @@ __device__ inline void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-__device__ inline double lane_value(double v, int l) {  // lane l's value (l uniform)
-  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
-                          __builtin_amdgcn_readlane(__double2loint(v), l));
 }
 
 // Column j of sub-block b by LDS and the library's root and division, a row per
@@ -111,14 +109,14 @@ __device__ int factor_block(double *T, int nb, int *fail_s) {
       bool odd = false;
 #pragma unroll
       for (int j = 0; j < 16; ++j) {
-        const double p = lane_value(a[j], 16 * b + j);
+        const double p = wave_value(a[j], 16 * b + j);
         odd |= !(p > 0x1p-900 && p < 0x1p900);
         double r = __builtin_amdgcn_rsq(p);
         r = fma(0.5 * r, fma(-p * r, r, 1.0), r);
         r = fma(0.5 * r, fma(-p * r, r, 1.0), r);
         const double l = a[j] * r;
 #pragma unroll
-        for (int k = j + 1; k < 16; ++k) a[k] = fma(-l, lane_value(l, 16 * b + k), a[k]);
+        for (int k = j + 1; k < 16; ++k) a[k] = fma(-l, wave_value(l, 16 * b + k), a[k]);
         const double d = p * r;
         a[j] = lane == 16 * b + j ? fma(0.5 * r, fma(-d, d, p), d) : l;
       }
@@ -185,12 +183,104 @@ __global__ __launch_bounds__(256) void chol_first_kernel(CholBatch g) {
     put_block(T, L, n, 0, nb);
 }
 
-// Panel p.  Workgroups below `gt` (the tile count of the largest matrix) take a
-// trailing tile each, the others move the solved rows of panel p - 1 into place.
-__global__ __launch_bounds__(256, 1) void chol_panel_kernel(CholBatch g, int p, int gt) {
-  __shared__ __attribute__((aligned(16))) double Ls[NB * LD], XI[NB * LD], XJ[NB * LD];
-  __shared__ double Di[4 * 16 * LDD];  // inverses of L_jj's diagonal 16 x 16 blocks
+// Inverses of L_jj's diagonal 16 x 16 blocks (column lc per lane of wave `wave`'s
+// block): as each x_k is known, its products leave the entries below.
+__device__ __forceinline__ void invert_blocks(const double *Ls, double *Di) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane >> 4, lc = lane & 15;
+  const double *D = Ls + (16 * wave) * LD + 16 * wave;
+  const double rp = 1.0 / D[lc * LD + lc];
+  double x[16];
+#pragma unroll
+  for (int k = 0; k < 16; ++k) x[k] = k == lc ? 1.0 : 0.0;
+#pragma unroll
+  for (int k = 0; k < 16; ++k) {
+    x[k] *= wave_value(rp, k);
+#pragma unroll
+    for (int m = k + 1; m < 16; ++m) x[m] = fma(-D[m * LD + k], x[k], x[m]);
+  }
+  if (lr == 0)
+#pragma unroll
+    for (int k = 0; k < 16; ++k) Di[(16 * wave + k) * LDD + lc] = x[k];
+}
+
+// X = A L_jj^-T for this wave's 16 rows of I and (two) of J, 16 columns at a time:
+// the rows in pi and pj, the results in XI and XJ.
+__device__ __forceinline__ void solve_rows(const double *Ls, const double *Di, const d4v (&pi)[4],
+                                           const d4v (&pj)[4], double *XI, double *XJ, bool two) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane >> 4, lc = lane & 15;
+#pragma unroll
+  for (int b = 0; b < 4; ++b) {
+    const int row = 16 * wave + lc;
+    d4v si = {0.0, 0.0, 0.0, 0.0}, sj = si;
+#pragma unroll
+    for (int kk = 0; kk < 16 * b; kk += 4) {
+      const double l = Ls[(16 * b + lc) * LD + kk + lr];
+      si = mfma(XI[row * LD + kk + lr], l, si);
+      if (two) sj = mfma(XJ[row * LD + kk + lr], l, sj);
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      XI[(16 * wave + lr + 4 * v) * LD + 16 * b + lc] = pi[b][v] - si[v];
+      if (two) XJ[(16 * wave + lr + 4 * v) * LD + 16 * b + lc] = pj[b][v] - sj[v];
+    }
+    wave_lds_sync();
+    d4v xi = {0.0, 0.0, 0.0, 0.0}, xj = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int kk = 0; kk < 16; kk += 4) {
+      const double w = Di[(16 * b + lc) * LDD + kk + lr];
+      xi = mfma(XI[row * LD + 16 * b + kk + lr], w, xi);
+      if (two) xj = mfma(XJ[row * LD + 16 * b + kk + lr], w, xj);
+    }
+    wave_lds_sync();
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      XI[(16 * wave + lr + 4 * v) * LD + 16 * b + lc] = xi[v];
+      if (two) XJ[(16 * wave + lr + 4 * v) * LD + 16 * b + lc] = xj[v];
+    }
+    wave_lds_sync();
+  }
+}
+
+// This thread's 16 elements of a 64 x 64 tile in memory: row wave + 4 u, column lane.
+template <class In>
+__device__ __forceinline__ void tile_load(const double *A, int n, int i0, int j0, In in,
+                                          double (&v)[16]) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int u = 0; u < 16; ++u) {
+    const int r = wave + 4 * u;
+    v[u] = in(r, lane) ? A[(size_t)(i0 + r) * n + j0 + lane] : 0.0;
+  }
+}
+__device__ __forceinline__ void tile_put(double *T, const double (&v)[16]) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int u = 0; u < 16; ++u) T[(wave + 4 * u) * LD + lane] = v[u];
+}
+// This wave's 16 rows of a panel, item v of block b: row lr + 4 v, column 16 b + lc.
+__device__ __forceinline__ void rows_load(const double *A, int n, int i0, int j0, bool on,
+                                          d4v (&p)[4]) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane >> 4, lc = lane & 15;
+#pragma unroll
+  for (int b = 0; b < 4; ++b)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int r = 16 * wave + lr + 4 * v;
+      p[b][v] = on && i0 + r < n ? A[(size_t)(i0 + r) * n + j0 + 16 * b + lc] : 0.0;
+    }
+}
+
+// Panel p.  ONE: workgroups below `gt` (the tile count of the largest matrix) solve
+// their panel rows and take a trailing tile each, the others move the solved rows of
+// panel p - 1 into place.  Otherwise the panel rows are solved in place
+// (chol_rows_kernel) and a workgroup takes its tile's from there.
+template <bool ONE>
+__global__ __launch_bounds__(256, ONE ? 1 : 2) void chol_panel_kernel(CholBatch g, int p, int gt) {
+  __shared__ __attribute__((aligned(16))) double XI[NB * LD], XJ[NB * LD];
+  __shared__ __attribute__((aligned(16))) double Lp[ONE ? NB * LD : 1];
+  __shared__ double Di[ONE ? 4 * 16 * LDD : 1];  // inverses of L_jj's diagonal 16 x 16 blocks
   __shared__ int fail_s;
+  double *Ls = ONE ? Lp : XJ;  // the next diagonal block (and with ONE L_jj's before it)
   const int c = blockIdx.y, n = chol_n(g, c), nblk = (n + NB - 1) / NB;
   double *A = g.L + chol_off(g, c);
   // A failed pivot stops its matrix at block q: panels before q are solved.
@@ -198,7 +288,7 @@ __global__ __launch_bounds__(256, 1) void chol_panel_kernel(CholBatch g, int p, 
   // stops none of its workgroups.)
   const int inf = g.info[c], q = inf ? (inf - 1) / NB : nblk;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if ((int)blockIdx.x >= gt) {
+  if (ONE && (int)blockIdx.x >= gt) {
     const int I = p + (int)blockIdx.x - gt, pp = p - 1;
     if (pp < 0 || I >= nblk || pp >= q) return;
     const int i0 = I * NB, j0 = pp * NB, nr = min(NB, n - i0);
@@ -232,23 +322,19 @@ __global__ __launch_bounds__(256, 1) void chol_panel_kernel(CholBatch g, int p, 
   const int wm = wave >> 1, wn = wave & 1;
 
   // Sums of products are formed from zero and subtracted once: rounded at their
-  // own size and not at that of what they leave.  Every load first: L_jj's block, this wave's 16 panel rows of I and J and its
-  // 32 x 32 quadrant of the tile (accumulator item v: row lr + 4 v, column lc)
-  double lv[16];
-#pragma unroll
-  for (int u = 0; u < 16; ++u) {
-    const int r = wave + 4 * u;
-    lv[u] = lane <= r ? A[(size_t)(j0 + r) * n + j0 + lane] : 0.0;
-  }
+  // own size and not at that of what they leave.  Every load first: the panel rows
+  // of I and J (ONE: L_jj's block and this wave's 16 of each) and this wave's 32 x 32
+  // quadrant of the tile (accumulator item v: row lr + 4 v, column lc)
+  double lv[16], lw[16];
   d4v pi[4], pj[4], old[2][2], acc[2][2];
-#pragma unroll
-  for (int b = 0; b < 4; ++b)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int r = 16 * wave + lr + 4 * v;
-      pi[b][v] = i0 + r < n ? A[(size_t)(i0 + r) * n + j0 + 16 * b + lc] : 0.0;
-      pj[b][v] = (I != J && k0 + r < n) ? A[(size_t)(k0 + r) * n + j0 + 16 * b + lc] : 0.0;
-    }
+  if constexpr (ONE) {
+    tile_load(A, n, j0, j0, [&](int r, int k) { return k <= r; }, lv);
+    rows_load(A, n, i0, j0, true, pi);
+    rows_load(A, n, k0, j0, I != J, pj);
+  } else {
+    tile_load(A, n, i0, j0, [&](int r, int) { return i0 + r < n; }, lv);
+    if (I != J) tile_load(A, n, k0, j0, [&](int r, int) { return k0 + r < n; }, lw);
+  }
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -259,59 +345,15 @@ __global__ __launch_bounds__(256, 1) void chol_panel_kernel(CholBatch g, int p, 
         old[i][j][v] = (r < n && k <= r) ? A[(size_t)r * n + k] : 0.0;
         acc[i][j][v] = 0.0;
       }
-#pragma unroll
-  for (int u = 0; u < 16; ++u) Ls[(wave + 4 * u) * LD + lane] = lv[u];
-  __syncthreads();
-  // inverse of diagonal 16 x 16 block `wave`, column lc per lane: as each x_k is
-  // known, its products leave the entries below
-  {
-    const double *D = Ls + (16 * wave) * LD + 16 * wave;
-    const double rp = 1.0 / D[lc * LD + lc];
-    double x[16];
-#pragma unroll
-    for (int k = 0; k < 16; ++k) x[k] = k == lc ? 1.0 : 0.0;
-#pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      x[k] *= lane_value(rp, k);
-#pragma unroll
-      for (int m = k + 1; m < 16; ++m) x[m] = fma(-D[m * LD + k], x[k], x[m]);
-    }
-    if (lr == 0)
-#pragma unroll
-      for (int k = 0; k < 16; ++k) Di[(16 * wave + k) * LDD + lc] = x[k];
-  }
-  __syncthreads();
-  // X = A L_jj^-T for 16 rows of I and of J per wave, 16 columns at a time
-#pragma unroll
-  for (int b = 0; b < 4; ++b) {
-    const int row = 16 * wave + lc;
-    d4v si = {0.0, 0.0, 0.0, 0.0}, sj = si;
-#pragma unroll
-    for (int kk = 0; kk < 16 * b; kk += 4) {
-      const double l = Ls[(16 * b + lc) * LD + kk + lr];
-      si = mfma(XI[row * LD + kk + lr], l, si);
-      if (I != J) sj = mfma(XJ[row * LD + kk + lr], l, sj);
-    }
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      XI[(16 * wave + lr + 4 * v) * LD + 16 * b + lc] = pi[b][v] - si[v];
-      if (I != J) XJ[(16 * wave + lr + 4 * v) * LD + 16 * b + lc] = pj[b][v] - sj[v];
-    }
-    wave_lds_sync();
-    d4v xi = {0.0, 0.0, 0.0, 0.0}, xj = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int kk = 0; kk < 16; kk += 4) {
-      const double w = Di[(16 * b + lc) * LDD + kk + lr];
-      xi = mfma(XI[row * LD + 16 * b + kk + lr], w, xi);
-      if (I != J) xj = mfma(XJ[row * LD + 16 * b + kk + lr], w, xj);
-    }
-    wave_lds_sync();
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      XI[(16 * wave + lr + 4 * v) * LD + 16 * b + lc] = xi[v];
-      if (I != J) XJ[(16 * wave + lr + 4 * v) * LD + 16 * b + lc] = xj[v];
-    }
-    wave_lds_sync();
+  if constexpr (ONE) {
+    tile_put(Ls, lv);
+    __syncthreads();
+    invert_blocks(Ls, Di);
+    __syncthreads();
+    solve_rows(Ls, Di, pi, pj, XI, XJ, I != J);
+  } else {
+    tile_put(XI, lv);
+    if (I != J) tile_put(XJ, lw);
   }
   __syncthreads();
   const double *B = I != J ? XJ : XI;
@@ -330,7 +372,7 @@ __global__ __launch_bounds__(256, 1) void chol_panel_kernel(CholBatch g, int p, 
         for (int j = 0; j < 2; ++j) acc[i][j] = mfma(af[i], bf[j], acc[i][j]);
     }
   }
-  if (I == J)  // the solved rows, transposed into block (p, I) of the upper triangle
+  if (ONE && I == J)  // the solved rows, transposed into block (p, I) of the upper triangle
 #pragma unroll
     for (int u = 0; u < 16; ++u) {
       const int r = wave + 4 * u;
@@ -348,7 +390,8 @@ __global__ __launch_bounds__(256, 1) void chol_panel_kernel(CholBatch g, int p, 
         }
     return;
   }
-  // the next diagonal block (Ls is free: every wave has passed its products)
+  // the next diagonal block (Ls is free: tile 0 is a diagonal one, without XJ, and
+  // with ONE every wave has passed its products with L_jj's block)
   const int nb = min(NB, n - i0);
 #pragma unroll
   for (int i = 0; i < 2; ++i)
@@ -368,6 +411,32 @@ __global__ __launch_bounds__(256, 1) void chol_panel_kernel(CholBatch g, int p, 
   put_block(Ls, A, n, i0, nb);
 }
 
+// The rows of panel p solved in place, 64 of them a workgroup.
+__global__ __launch_bounds__(256, 2) void chol_rows_kernel(CholBatch g, int p) {
+  __shared__ __attribute__((aligned(16))) double Ls[NB * LD], XI[NB * LD];
+  __shared__ double Di[4 * 16 * LDD];
+  const int c = blockIdx.y, n = chol_n(g, c), nblk = (n + NB - 1) / NB;
+  double *A = g.L + chol_off(g, c);
+  const int inf = g.info[c], q = inf ? (inf - 1) / NB : nblk;
+  const int I = p + 1 + blockIdx.x, i0 = I * NB, j0 = p * NB;
+  if (I >= nblk || p >= q) return;
+  double lv[16];
+  d4v pi[4];
+  tile_load(A, n, j0, j0, [&](int r, int k) { return k <= r; }, lv);
+  rows_load(A, n, i0, j0, true, pi);
+  tile_put(Ls, lv);
+  __syncthreads();
+  invert_blocks(Ls, Di);
+  __syncthreads();
+  solve_rows(Ls, Di, pi, pi, XI, nullptr, false);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int u = 0; u < 16; ++u) {  // (this wave's own rows)
+    const int r = 16 * wave + u;
+    if (i0 + r < n) A[(size_t)(i0 + r) * n + j0 + lane] = XI[r * LD + lane];
+  }
+}
+
 int chol_run(int C, int n_max, const CholBatch &g, hipStream_t s) {
   const int64_t total = (int64_t)n_max * n_max;
   const unsigned copies =
@@ -376,12 +445,28 @@ int chol_run(int C, int n_max, const CholBatch &g, hipStream_t s) {
   SB_LAUNCH_CHECK();
   const int nblk = (int)ceil_div(n_max, NB);
   if (nblk < 2) return SB_OK;
+  bool mirrored = false;  // panel p - 1's rows are still in the upper triangle
   for (int p = 0; p < nblk; ++p) {
     const int T = nblk - 1 - p, gt = T * (T + 1) / 2;
-    const int moves = p > 0 ? nblk - p : 0;  // rows of blocks p .. of panel p - 1
-    hipLaunchKernelGGL(chol_panel_kernel, dim3((unsigned)(gt + moves), C), dim3(256), 0, s, g, p,
-                       gt);
+    const int moves = mirrored ? nblk - p : 0;  // rows of blocks p .. of panel p - 1
+    // More tiles than CUs: a tile's workgroup that solves its panel rows itself has
+    // a CU's LDS alone, so a second round of them costs more than the launch that
+    // solves each row once (us, one launch a panel : two): n = 512, 8 matrices (224
+    // tiles in the first panel) 244 : 255, 16 (448) 285 : 266, 512 3946 : 2029; n =
+    // 320, 16 (160) 155 : 159, 32 (320) 174 : 165; n = 2048, 64 21579 : 9041.
+    if ((int64_t)C * gt > 256) {
+      hipLaunchKernelGGL(chol_rows_kernel, dim3((unsigned)T, C), dim3(256), 0, s, g, p);
+      SB_LAUNCH_CHECK();
+      hipLaunchKernelGGL(chol_panel_kernel<false>, dim3((unsigned)gt, C), dim3(256), 0, s, g, p,
+                         gt);
+      SB_LAUNCH_CHECK();
+      continue;
+    }
+    if (gt + moves == 0) break;
+    hipLaunchKernelGGL(chol_panel_kernel<true>, dim3((unsigned)(gt + moves), C), dim3(256), 0, s, g,
+                       p, gt);
     SB_LAUNCH_CHECK();
+    mirrored = true;
   }
   return SB_OK;
 }
@@ -478,7 +563,7 @@ __global__ __launch_bounds__(SV_T) void chol_solve_kernel(CholBatch g, const dou
       const double rp = lane < nb ? 1.0 / TD[lane * SV_LD + lane] : 1.0;
 #pragma unroll 8
       for (int cc = 0; cc < nb; ++cc) {  // (unrolled: the reads of TD leave the chain)
-        const double xc = lane_value(val * rp, cc);
+        const double xc = wave_value(val * rp, cc);
         if (lane == cc) val = xc;
         if (lane > cc) val -= TD[lane * SV_LD + cc] * xc;
       }
@@ -541,7 +626,7 @@ __global__ __launch_bounds__(SV_T) void chol_solve_kernel(CholBatch g, const dou
       const double rp = lane < nb ? 1.0 / TD[lane * SV_LD + lane] : 1.0;
 #pragma unroll 8
       for (int cc = nb - 1; cc >= 0; --cc) {
-        const double xc = lane_value(val * rp, cc);
+        const double xc = wave_value(val * rp, cc);
         if (lane == cc) val = xc;
         if (lane < cc) val -= TD[cc * SV_LD + lane] * xc;
       }

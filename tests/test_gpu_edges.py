@@ -83,3 +83,24 @@ def test_lbfgs_path_of_ragged_rows(L, d, m, steps):
         it = L.sb_lbfgs_dev(md, dev(X0).float(), m=m, grad_tol=2e-4, max_iter=400,
                             hist_bf16=h16)["iters"]
         assert int(it.max()) <= (2.0 if h16 else 1.5) * want
+
+
+@pytest.mark.parametrize("n,C", [(65, 300), (129, 100), (200, 60), (320, 33), (450, 12), (1024, 4)])
+def test_cholesky_batch_equals_single(L, n, C):
+    """Batches whose first panels have more tiles than the chip has CUs (their rows solved by a
+    launch of their own, the last panels' not) against the same matrices one at a time: the
+    same bits, with matrices among them whose pivot fails in the first, a middle and the last
+    column (info is that column in both)."""
+    A = np.repeat(synth.random_spd(n, 70 + n, cond=1e3, batch=4), -(-C // 4), axis=0)[:C].copy()
+    A *= np.linspace(1.0, 3.0, C)[:, None, None]
+    fails = {1: 0, 2: n // 2, 3: n - 1}
+    for c, k in fails.items():
+        A[c, k, k] = -1.0
+    Lb, ld, info = L.sb_cholesky_logdet_dev(dev(A))
+    assert [int(info[c]) for c in fails] == [k + 1 for k in fails.values()]
+    for c in list(range(min(C, 5))) + [C // 2, C - 1]:
+        L1, ld1, info1 = L.sb_cholesky_logdet_dev(dev(A[c:c + 1]))
+        assert int(info1[0]) == int(info[c])
+        if c not in fails:
+            assert int(info[c]) == 0
+            assert torch.equal(Lb[c], L1[0]) and torch.equal(ld[c], ld1[0])
