@@ -13,7 +13,7 @@
 //   1 + 2d, 2+2d  x + eps v, x - eps v, v = (1..1)/sqrt(d)  (rotation probe)
 //   3 + 2d + 4t   x +- eps e_i +- eps e_j, t-th pair i < j  (full Hessian only)
 // are evaluated in one launch (each row formed in LDS where the function reads
-// it, or in memory when it is too long for that), and a combine kernel forms
+// it, or in memory where that is the better), and a combine kernel forms
 // the central differences: g_i = (f+ - f-)/(2 eps), H_ii = (f+ - 2 f0 + f-)/eps^2,
 // H_ij = (f++ - f+- - f-+ + f--)/(4 eps^2), and the probe
 // b = (v^T H v - mean H_ii)/(d - 1).
@@ -591,16 +591,46 @@ void sb_user_release(sb_user_fn *fn) {
 // Points per workgroup of the staged kernel and the LDS row stride: 64 rows, or
 // as many as kStageBytes hold.  Rows keep the alignment they have in memory (16
 // bytes for even d) at a stride whose 16-byte pieces are odd in number (odd
-// for odd d), so that a column of rows spreads over the banks.  0: the row is
-// too long (fewer than four would fit: below that the direct kernel, all its
-// lanes on rows in memory, is as fast) or the source's own LDS leaves no room.
+// for odd d), so that a column of rows spreads over the banks.  0: the direct
+// kernel, its points in memory.
+//
+// Staged or direct: rows read from LDS cost less, but the LDS of 64 rows leaves few
+// waves per SIMD (four workgroups per CU up to d = 78, two at 126), and longer rows
+// leave lanes idle, where the direct kernel keeps all lanes and hides the latency of
+// arithmetic behind up to eight waves.  Staged time over direct time for a sum of
+// squares, for logarithms, exponentials and a cosine per coordinate, and for a quadratic
+// form ("light", "heavy", "form"), W workgroups where S run at once:
+//  - l at given points, W <= S: d = 16, 262144 points 0.57 light, 1.02 heavy, 0.10 form;
+//    d = 126, 32768 0.53, 0.91, 0.29.  W > S: d = 64, 131072 0.58, 1.74, 0.32; d = 96,
+//    65536 1.21, 2.42, 0.79: direct.  From 6144 waves on the direct kernel's rows
+//    fall out of the caches: d = 64, 524288 0.20, 0.81, 0.09; d = 16, 393216 0.15,
+//    0.77, 0.02; but d = 12, 393216 0.39, 1.25, 0.08 and d = 96, 524288 0.26, 1.04.
+//    Lanes idle: d = 128, 4096 0.65, 1.25, 0.49; d = 512, 65536 2.31, 15.9: direct.
+//  - finite differences, whose rows need not pass through memory when staged: d <= 78
+//    at most 1.03 (d = 64, 4096 base points 0.11, 0.50, 0.07).  d = 96, 1560 workgroups
+//    (S = 768) 0.36, 1.05, 0.40; d = 126, 2040 (S = 512) 0.31, 1.15, 0.41, 4080 0.16,
+//    1.04.  Half the lanes: d = 160, 646 (S = 768) 0.39, 0.69, 0.42, 1292 0.44, 1.62.
+//    Fewer: d = 510, 256 workgroups 0.37, 0.89, 1023 0.40, 2.22; d = 2046, 1024 0.33,
+//    2.29.
 constexpr int kStageBytes = 64 * 1024;
-static int stage_points(const sb_user_fn *fn, int d, int *stride) {
+constexpr int64_t kCUs = 256, kCULds = 160 * 1024;
+static int stage_points(const sb_user_fn *fn, int64_t N, int d, bool fd, int *stride) {
   const int64_t ds = d % 2 ? d : (d % 4 == 2 ? d : (int64_t)d + 2);
   *stride = (int)ds;
   int n = 64;
   while (n >= 4 && n * ds * 8 + fn->lds_static > kStageBytes) n >>= 1;
-  return n >= 4 ? n : 0;
+  if (n < 4) return 0;
+  const int64_t per_cu = std::min<int64_t>(32, kCULds / (n * ds * 8 + fn->lds_static));
+  const int64_t W = ceil_div(N, n), S = kCUs * per_cu;
+  if (W >= (int64_t)1 << 26) return 0;  // (2^32 work items: past one launch)
+  bool staged;
+  if (n < 64)
+    staged = fd && W <= (n == 32 ? S : kCUs);
+  else if (fd)
+    staged = per_cu >= 4 || W <= S || W >= 8 * S;
+  else
+    staged = d >= 4 && (W <= S || d <= 8 || (d >= 16 && per_cu >= 4 && W >= 24 * kCUs));
+  return staged ? n : 0;
 }
 
 static int check_device(const sb_user_fn *fn) {
@@ -627,14 +657,12 @@ static int user_eval_staged(const sb_user_fn *fn, int64_t N, int d, int64_t R, i
   return SB_OK;
 }
 
-static int user_eval(const sb_user_fn *fn, int64_t B, int d, const double *X, int64_t ldx,
-                     const double *params, double *l, hipStream_t s) {
-  int stride = 0;
-  const int npt = stage_points(fn, d, &stride);
-  if (npt && ldx == d) return user_eval_staged(fn, B, d, 0, npt, stride, X, 0.0, params, l, s);
+// l at the rows of X [B][d], read where they are.
+static int user_eval_direct(const sb_user_fn *fn, int64_t B, int d, const double *X,
+                            const double *params, double *l, hipStream_t s) {
   int st = check_device(fn);
   if (st) return st;
-  long long b = (long long)B, lx = (long long)ldx;
+  long long b = (long long)B, lx = d;
   int dd = d;
   void *args[] = {&b, &dd, &X, &lx, &params, &l};
   const unsigned grid = (unsigned)ceil_div(B, 256);
@@ -643,12 +671,20 @@ static int user_eval(const sb_user_fn *fn, int64_t B, int d, const double *X, in
   return SB_OK;
 }
 
+static int user_eval(const sb_user_fn *fn, int64_t B, int d, const double *X,
+                     const double *params, double *l, hipStream_t s) {
+  int stride = 0;
+  const int npt = stage_points(fn, B, d, false, &stride);
+  if (npt) return user_eval_staged(fn, B, d, 0, npt, stride, X, 0.0, params, l, s);
+  return user_eval_direct(fn, B, d, X, params, l, s);
+}
+
 int32_t sb_user_logl_dev(const sb_user_fn *fn, int64_t B, int32_t d, const double *X,
                          const double *params, double *l, void *stream) {
   if (!fn || B < 0 || d < 1 || (B > 0 && (!X || !l)))
     return fail(SB_E_INVAL, "bad user likelihood arguments");
   if (B == 0) return SB_OK;
-  return user_eval(fn, B, d, X, d, params, l, (hipStream_t)stream);
+  return user_eval(fn, B, d, X, params, l, (hipStream_t)stream);
 }
 
 size_t sb_user_fd_workspace_bytes(int64_t B, int32_t d, int32_t full) {
@@ -672,14 +708,14 @@ int32_t sb_user_fd_dev(const sb_user_fn *fn, int64_t B, int32_t d, const double 
   double *P = ar.take<double>((size_t)(B * R * d));
   double *F = ar.take<double>((size_t)(B * R));
   int stride = 0, st;
-  const int npt = stage_points(fn, d, &stride);
+  const int npt = stage_points(fn, B * R, d, true, &stride);
   if (npt) {
     st = user_eval_staged(fn, B * R, d, R, npt, stride, X, eps, params, F, s);
   } else {
     hipLaunchKernelGGL(fd_points_kernel, dim3((unsigned)ceil_div(B * R, 256)), dim3(256), 0, s,
                        B, d, R, X, eps, P);
     SB_LAUNCH_CHECK();
-    st = user_eval(fn, B * R, d, P, d, params, F, s);
+    st = user_eval_direct(fn, B * R, d, P, params, F, s);
   }
   if (st) return st;
   hipLaunchKernelGGL(fd_combine_kernel, dim3((unsigned)ceil_div(B * d, 256)), dim3(256), 0, s, B,
@@ -1039,7 +1075,7 @@ int32_t sb_user_evidence_dev(const sb_user_fn *fn, int32_t d, const double *para
   hipLaunchKernelGGL(ray_points_kernel, dim3((unsigned)ceil_div(NP * d, 256)), dim3(256), 0, s, R,
                      NPTS, d, U.P0, U.P1, U.Xpts);
   SB_LAUNCH_CHECK();
-  if ((st = user_eval(fn, NP, d, U.Xpts, d, params, U.lpts, s))) return st;
+  if ((st = user_eval(fn, NP, d, U.Xpts, params, U.lpts, s))) return st;
   if ((st = launch_ray_argmax(R, NPTS, SB_DTYPE_F64, U.lpts, U.best_l, U.best_j, s))) return st;
   if ((st = launch_topn(R, B, U.best_l, U.start_ray, s))) return st;
   if ((st = launch_gather_starts(d, NPTS, B, U.start_ray, U.best_j, U.P0, U.P1, U.X0, s)))

@@ -104,3 +104,45 @@ def test_cholesky_batch_equals_single(L, n, C):
         if c not in fails:
             assert int(info[c]) == 0
             assert torch.equal(Lb[c], L1[0]) and torch.equal(ld[c], ld1[0])
+
+
+SIZE_SRC = "__device__ double size(const double *x, int d, const double *p) { return blockDim.x; }"
+SUM_SRC = r"""
+__device__ double wsum(const double *x, int d, const double *p) {
+  double s = 0.0;
+  for (int i = 0; i < d; ++i) s += p[i] * x[i];
+  return s;
+}
+"""
+
+
+@pytest.mark.parametrize("d,n,staged", [(2, 4096, False), (8, 1 << 20, True), (12, 1 << 20, False),
+                                        (64, 65536, True), (64, 65600, False),
+                                        (64, 393216, True), (96, 49152, True),
+                                        (96, 49216, False), (128, 64, False), (512, 4096, False),
+                                        (1022, 64, False)])
+def test_user_points_staged_where_it_gains(L, d, n, staged):
+    """Which kernel takes l at given points (the workgroup's size tells: 64 staged, 256 direct)
+    on both sides of the rule's lines, and the values there: a weighted sum within d roundings."""
+    X = torch.rand((n, d), dtype=torch.float64, device="cuda") - 0.5
+    assert float(L.UserLogL(SIZE_SRC, "size").logl(X[:1].expand(n, d).contiguous())[n - 1]) == (
+        64.0 if staged else 256.0)
+    p = torch.rand(d, dtype=torch.float64, device="cuda") + 0.5
+    l = L.UserLogL(SUM_SRC, "wsum").logl(X, p)
+    assert float((l - X @ p).abs().max()) <= 2 * d * 2.0 ** -52 * d
+
+
+@pytest.mark.parametrize("d,B,staged", [(78, 600, True), (96, 251, True), (96, 256, False),
+                                        (96, 2100, True), (160, 76, True), (160, 77, False),
+                                        (510, 4, True), (510, 5, False), (2046, 1, False)])
+def test_user_differences_staged_where_it_gains(L, d, B, staged):
+    """The same for the rows of finite differences, formed in LDS or in memory, and the
+    gradient of a weighted sum on either side: its differences round d times each."""
+    X = torch.rand((B, d), dtype=torch.float64, device="cuda") - 0.5
+    l = L.UserLogL(SIZE_SRC, "size").fd(X, 1e-3)["l"]
+    assert float(l[B - 1]) == (64.0 if staged else 256.0)
+    p = torch.rand(d, dtype=torch.float64, device="cuda") + 0.5
+    out = L.UserLogL(SUM_SRC, "wsum").fd(X, 1e-3, p)
+    tol = 2 * d * 2.0 ** -52 * d
+    assert float((out["l"] - X @ p).abs().max()) <= tol
+    assert float((out["grad"] - p).abs().max()) <= 2 * tol / 1e-3
