@@ -463,8 +463,9 @@ static bool valid_name(const char *name) {
   return true;
 }
 
-// The staged evaluation kernel, completed with the user function's call.  One
-// wave per workgroup, npt <= 64 points, a point per lane.  The function reads
+// The staged evaluation kernel's body, ahead of the user's source, whose macros and
+// names it therefore does not meet; F::at calls the user function.  One wave per
+// workgroup, npt <= 64 points, a point per lane.  The function reads
 // its point at one coordinate after the other: from rows in memory the lanes
 // of a wave touch 64 cache lines a coordinate and the L2 sets the pace (d = 64,
 // 4096 points x 131 rows: 27.8 ms), so the rows are brought into LDS first,
@@ -474,12 +475,13 @@ static bool valid_name(const char *name) {
 // d = 64, 4096 points: 30.7 -> 1.7 ms a call.  Bound now by latency: four waves
 // of 64 rows fill a CU's LDS, so one wave per SIMD waits for its own scalar
 // loads of params and its chain of dependent FP64 additions.
-static const char kStagedHead[] = R"hip(
-extern "C" __global__ __launch_bounds__(64) void sb_user_staged_kernel(
-    long long N, int d, int ds, int npt, long long R, const double *X, double eps,
-    const double *params, double *l) {
+static const char kStagedBody[] = R"hip(
+template <class F>
+__device__ __forceinline__ void sb_user_staged(long long N, int d, int ds, int npt, long long R,
+                                               const double *X, double eps,
+                                               const double *params, double *l,
+                                               double *sb_user_rows) {
 #pragma clang fp contract(off)
-  extern __shared__ __attribute__((aligned(16))) double sb_user_rows[];
   const int lane = threadIdx.x;
   const long long e0 = (long long)blockIdx.x * npt;
   const int n = N - e0 < npt ? (int)(N - e0) : npt;
@@ -529,7 +531,33 @@ extern "C" __global__ __launch_bounds__(64) void sb_user_staged_kernel(
       x[j] = (sgn % 2 == 0) ? x[j] + eps : x[j] - eps;
     }
   }
-  l[e0 + lane] = )hip";
+  l[e0 + lane] = F::at(x, d, params);
+}
+#line 1
+)hip";
+// The kernels, behind the user's source: every name of theirs starts with sb_user_.
+static std::string kernel_source(const char *name) {
+  std::string call = name;
+  call += "(sb_user_x, sb_user_d, sb_user_p)";
+  return "\nstruct sb_user_call {\n"
+         "  static __device__ __forceinline__ double at(const double *sb_user_x, int sb_user_d,\n"
+         "                                              const double *sb_user_p) {\n"
+         "    return " + call + ";\n  }\n};\n"
+         "extern \"C\" __global__ void sb_user_eval_kernel(\n"
+         "    long long sb_user_B, int sb_user_d, const double *sb_user_X, long long sb_user_ldx,\n"
+         "    const double *sb_user_p, double *sb_user_l) {\n"
+         "  const long long sb_user_b = (long long)blockIdx.x * blockDim.x + threadIdx.x;\n"
+         "  const double *sb_user_x = sb_user_X + sb_user_b * sb_user_ldx;\n"
+         "  if (sb_user_b < sb_user_B) sb_user_l[sb_user_b] = " + call + ";\n}\n"
+         "extern \"C\" __global__ __launch_bounds__(64) void sb_user_staged_kernel(\n"
+         "    long long sb_user_N, int sb_user_d, int sb_user_ds, int sb_user_npt,\n"
+         "    long long sb_user_R, const double *sb_user_X, double sb_user_eps,\n"
+         "    const double *sb_user_p, double *sb_user_l) {\n"
+         "  extern __shared__ __attribute__((aligned(16))) double sb_user_rows[];\n"
+         "  sb_user_staged<sb_user_call>(sb_user_N, sb_user_d, sb_user_ds, sb_user_npt, sb_user_R,\n"
+         "                               sb_user_X, sb_user_eps, sb_user_p, sb_user_l,\n"
+         "                               sb_user_rows);\n}\n";
+}
 
 extern "C" {
 
@@ -537,16 +565,9 @@ int32_t sb_user_compile(const char *source, const char *name, sb_user_fn **out) 
   if (!source || !out) return fail(SB_E_INVAL, "NULL source or output");
   *out = nullptr;
   if (!valid_name(name)) return fail(SB_E_INVAL, "the function name must be a C identifier");
-  std::string code(source);
-  code += "\nextern \"C\" __global__ void sb_user_eval_kernel(long long B, int d, const double *X,"
-          " long long ldx, const double *params, double *l) {\n"
-          "  const long long b = (long long)blockIdx.x * blockDim.x + threadIdx.x;\n"
-          "  if (b < B) l[b] = ";
-  code += name;
-  code += "(X + b * ldx, d, params);\n}\n";
-  code += kStagedHead;
-  code += name;
-  code += "(x, d, params);\n}\n";
+  std::string code(kStagedBody);
+  code += source;
+  code += kernel_source(name);
   hiprtcProgram prog;
   if (hiprtcCreateProgram(&prog, code.c_str(), "sb_user.hip", 0, nullptr, nullptr) !=
       HIPRTC_SUCCESS)
