@@ -1420,15 +1420,22 @@ int run_evidence(const DevProblem &P, const sb_config *cfg, sb_result *res, void
       SB_LAUNCH_CHECK();
       tm.mark(s);  // 6
     }
-    // counts and, with modes, the whole result in one readback
+    // counts and, with modes, the result: small ones in one readback, larger ones
+    // straight to where the caller wants them (nothing is allocated here)
+    double hstack[ExecCtx::kPinnedBytes / 8];
+    double *h = ex ? (double *)ex->pinned : hstack;
     const size_t nout = kOutHead + (modes ? (size_t)nm * (d + 3) : 0);
-    std::vector<double> hv;
-    double *h = ex && nout * 8 <= ExecCtx::kPinnedBytes ? (double *)ex->pinned : nullptr;
-    if (!h) {
-      hv.resize(nout);
-      h = hv.data();
+    const bool whole = nout * 8 <= ExecCtx::kPinnedBytes;
+    auto fetch = [&](double *dst, const double *src, size_t n) {
+      return dst ? hipMemcpyAsync(dst, src, 8 * n, hipMemcpyDeviceToHost, s) : hipSuccess;
+    };
+    SB_HIP(fetch(h, L.out, whole ? nout : (size_t)kOutHead));
+    if (!whole) {
+      SB_HIP(fetch(res->mode_log_z, mlz, nm));
+      SB_HIP(fetch(res->mode_logl, ml, nm));
+      SB_HIP(fetch(res->log_det_h, mld, nm));
+      SB_HIP(fetch(res->modes, mx, (size_t)nm * d));
     }
-    SB_HIP(hipMemcpyAsync(h, L.out, nout * 8, hipMemcpyDeviceToHost, s));
     SB_HIP(hipStreamSynchronize(s));
     int32_t hcounts[8];
     memcpy(hcounts, h, sizeof(hcounts));
@@ -1451,11 +1458,13 @@ int run_evidence(const DevProblem &P, const sb_config *cfg, sb_result *res, void
       ret = SB_E_CAPACITY;
     } else {
       res->log_z = h[4];
-      const double *r = h + kOutHead;
-      if (res->mode_log_z) memcpy(res->mode_log_z, r, sizeof(double) * nm);
-      if (res->mode_logl) memcpy(res->mode_logl, r + nm, sizeof(double) * nm);
-      if (res->log_det_h) memcpy(res->log_det_h, r + 2 * nm, sizeof(double) * nm);
-      if (res->modes) memcpy(res->modes, r + 3 * nm, sizeof(double) * (size_t)nm * d);
+      if (whole) {
+        const double *r = h + kOutHead;
+        if (res->mode_log_z) memcpy(res->mode_log_z, r, sizeof(double) * nm);
+        if (res->mode_logl) memcpy(res->mode_logl, r + nm, sizeof(double) * nm);
+        if (res->log_det_h) memcpy(res->log_det_h, r + 2 * nm, sizeof(double) * nm);
+        if (res->modes) memcpy(res->modes, r + 3 * nm, sizeof(double) * (size_t)nm * d);
+      }
     }
     const double total =
         std::chrono::duration<double>(std::chrono::steady_clock::now() - t_start).count();

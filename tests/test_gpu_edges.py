@@ -1,4 +1,6 @@
 """GPU: calls at the far ends of what the entry points take."""
+import ctypes as C
+
 import numpy as np
 import pytest
 
@@ -146,3 +148,31 @@ def test_user_differences_staged_where_it_gains(L, d, B, staged):
     tol = 2 * d * 2.0 ** -52 * d
     assert float((out["l"] - X @ p).abs().max()) <= tol
     assert float((out["grad"] - p).abs().max()) <= 2 * tol / 1e-3
+
+
+@pytest.mark.parametrize("d", [165, 166])
+def test_result_readback_sizes(L, d):
+    """Three modes of d = 165 fill the small readback buffer (4096 bytes) exactly, of d = 166 they
+    go to the caller's arrays: the same numbers through a context, without one and, where
+    only some arrays are wanted, in those; the modes are the oracle's."""
+    rng = np.random.Generator(np.random.PCG64(9))
+    prob = synth.gaussian_mixture(rng, d, 3, -8.0, 8.0, 0.1, 1.0, 0.0, box_half=12.0)
+    cfg = synth.RunConfig(n_rays=256, n_points=32, n_starts=256, seed=3, precision=0)
+    ex = L.ExecContext()
+    a, b = L.EvidenceRunner(prob, cfg).run(), L.EvidenceRunner(prob, cfg, exec=ex).run()
+    ex.close()
+    ref = O.reference_modes(prob)
+    assert a.n_modes == b.n_modes == ref.n_modes == 3
+    assert a.log_z == b.log_z
+    for k in ("modes", "mode_log_z", "mode_logl", "log_det_h"):
+        assert np.array_equal(getattr(a, k), getattr(b, k)), k
+    r, arrs = L._new_result(cfg.max_modes, d)
+    r.modes = r.log_det_h = None
+    run = L.EvidenceRunner(prob, cfg)
+    assert L.lib().sb_evidence_dev(C.byref(run.ll), C.byref(run.box), C.byref(run.c), C.byref(r),
+                                   run.ws.data_ptr(), run.ws.numel(), 0) == 0
+    assert r.log_z == a.log_z and np.array_equal(arrs[2][:3], a.mode_logl)
+    assert not arrs[0].any() and not arrs[3].any()
+    want = ref.modes[:3][np.lexsort(ref.modes[:3].T[::-1])]
+    got = a.modes[np.lexsort(a.modes.T[::-1])]
+    assert np.max(np.abs(got - want)) <= 1e-8
