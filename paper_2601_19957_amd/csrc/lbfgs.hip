@@ -19,6 +19,7 @@
 // it into registers by age (newest first) and runs both loops of the recursion
 // with workgroup reductions for the dot products.
 #include <algorithm>
+#include <cstdlib>
 
 #include "fused_tile.h"
 #include "internal.h"
@@ -1192,6 +1193,8 @@ static void bulk_go(const BulkArgs &a, bool fast, hipStream_t s) {
 // K = 4 2808 : 2574 at 8192 and 3998 : 4296 at 16384; d = 128, K = 3 4156 : 3036
 // at 2048, 5004 : 4992 at 4096 and 7155 : 8900 at 8192.
 bool lbfgs_bulk_ok(const LbfgsBuffers &b, const Model &m) {
+  const char *e = getenv("SB_ONE_LAUNCH");  // "0": the step launches (for comparison)
+  if (e && e[0] == '0') return false;
   ASrc a;
   a.X = b.X;
   a.ldx = b.d;
@@ -1326,9 +1329,6 @@ int launch_lbfgs_init(const LbfgsBuffers &b, const void *X0, hipStream_t s) {
   return SB_OK;
 }
 
-// Compaction of the active starts into idx (their trial row ids), in start
-// order; count[0] = number active, evals[0] += count.  One workgroup: each
-// thread owns a contiguous chunk, exclusive scan of the chunk counts in LDS.
 // Active starts' trial rows into idx[0, count).  Each wave ballots its
 // starts and reserves its slice with one atomic: the order of the list
 // depends on wave timing, the rows' results do not (every row of the

@@ -176,3 +176,43 @@ def test_result_readback_sizes(L, d):
     want = ref.modes[:3][np.lexsort(ref.modes[:3].T[::-1])]
     got = a.modes[np.lexsort(a.modes.T[::-1])]
     assert np.max(np.abs(got - want)) <= 1e-8
+
+
+ONE_LAUNCH = [(1, 1, 1, 0), (4, 2, 15, 0), (31, 12, 17, 0), (33, 3, 16, 0), (64, 6, 130, 0),
+              (64, 4, 4096, 0), (65, 3, 9, 0), (96, 4, 100, 0), (128, 3, 2048, 0),
+              (64, 4, 100, 3), (100, 3, 33, 5)]
+
+
+@pytest.mark.parametrize("d,K,B,cut", ONE_LAUNCH)
+def test_one_launch_is_the_step_launches(L, d, K, B, cut, monkeypatch):
+    """The bulk in one launch against step, compaction and evaluation launches of the same
+    kernels' arithmetic: evaluations, iterations, the states of the starts and every number of the result
+    are the same, also where the iterations are cut short, and with starts that fill no workgroup.
+    A context tells which ran: one block graph for up to 256 steps, or one for eight."""
+    rng = np.random.Generator(np.random.PCG64(1700 + d))
+    span = 30.0 if K > 1 else 8.0
+    prob = synth.gaussian_mixture(rng, d, K, -span, span, 0.05, 1.0, 0.0, box_half=1.5 * span)
+    cfg = synth.RunConfig(n_rays=max(B, K), n_points=32, n_starts=B, seed=5, precision=0)
+    if cut:
+        cfg.max_iter = cut
+
+    def run():
+        ex, stream = L.ExecContext(), torch.cuda.Stream()
+        with torch.cuda.stream(stream):
+            r = L.EvidenceRunner(prob, cfg, exec=ex).run(stream)
+        n = ex.stats()["launched"]
+        ex.close()
+        return r, n
+
+    a, na = run()
+    monkeypatch.setenv("SB_ONE_LAUNCH", "0")
+    b, nb = run()
+    assert na == -(-a.iterations // 256) and nb == b.iterations // 8
+    assert a.status == b.status
+    for k in ("n_modes", "n_grad_evals", "n_logl_evals", "n_hess_evals", "iterations",
+              "n_dead_starts", "n_candidates", "n_reps_pre", "n_rejected_nonpd"):
+        assert getattr(a, k) == getattr(b, k), k
+    if a.status == 0:
+        assert a.log_z == b.log_z
+    for k in ("modes", "mode_log_z", "mode_logl", "log_det_h"):
+        assert np.array_equal(getattr(a, k), getattr(b, k)), k
