@@ -92,15 +92,17 @@ __global__ __launch_bounds__(256) void assign_kernel(int C, int d, const T *X, c
 }
 
 // Every round of a small set in one launch: 1024 threads, G lanes per candidate
-// in the distance pass (G a power of two, up to a wave), the candidates still
-// open as flags in LDS.  Bound by its round trips, about 1 us for the leader
-// and 1 us for each 1024 / G candidates, where the rounds as launches, eight
-// pairs to a readback, cost 60 to 80 us however few there are; so up to the
-// values that a round reads in 16 trips (4096 candidates of d = 64, 256 trips,
-// measured 410 us here and 75 us as launches).
+// in the distance pass (G a power of two, up to a wave), NV values of the row a lane
+// (up to eight), the candidates still open as flags in LDS.  Bound by its round trips, about
+// 1.5 us for the leader and 1 to 2 us for each 1024 / G candidates, where a round as
+// launches costs 11 to 15 us, eight of them to a readback and so 100 us however few
+// there are; so up to the values that a round reads in a few trips (4096 candidates of
+// d = 64 measured 410 us here and 75 us as launches).  With a value a lane and so up
+// to 31 trips a round, sets of many representatives were the slower (d = 33, 496
+// candidates all apart 11.5 ms, as launches 6.0, now 4.6).
 constexpr int kDedupSmall = 8192;             // candidates (flags in LDS)
 constexpr int64_t kDedupSmallWork = 1 << 14;  // values
-template <typename T, typename TL>
+template <typename T, typename TL, int NV>
 __global__ __launch_bounds__(1024) void dedup_small_kernel(int C, int d, int G, const T *X,
                                                            const TL *l, const uint8_t *valid,
                                                            double tau, int32_t *rep_of,
@@ -153,7 +155,16 @@ __global__ __launch_bounds__(1024) void dedup_small_kernel(int C, int d, int G, 
       const bool on = c < C && open[c];
       if (on) {
         const T *a = X + (size_t)c * d;
-        for (int i = t & (G - 1); i < d; i += G) m = fmax(m, fabs((double)a[i] - (double)b[i]));
+        for (int i = t & (G - 1); i < d; i += NV * G) {
+          double v[NV];
+#pragma unroll
+          for (int u = 0; u < NV; ++u) {
+            const int j = i + u * G < d ? i + u * G : i;
+            v[u] = (double)a[j] - (double)b[j];
+          }
+#pragma unroll
+          for (int u = 0; u < NV; ++u) m = fmax(m, fabs(v[u]));
+        }
       }
       for (int o = G >> 1; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o, 64));
       if (on && (t & (G - 1)) == 0 && (c == lead || m <= tau)) {
@@ -175,9 +186,15 @@ static void dedup_small(int C, int d, const void *X, const void *l, const uint8_
                         double tau, int32_t *rep_of, int32_t *reps, int max_reps, int32_t *state,
                         hipStream_t s) {
   int G = 1;
-  while (G < 64 && G < d) G *= 2;
-  hipLaunchKernelGGL((dedup_small_kernel<T, TL>), dim3(1), dim3(1024), 0, s, C, d, G, (const T *)X,
-                     (const TL *)l, valid, tau, rep_of, reps, max_reps, state);
+  while (G < 64 && 8 * G < d) G *= 2;
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(1), dim3(1024), 0, s, C, d, G, (const T *)X, (const TL *)l,
+                       valid, tau, rep_of, reps, max_reps, state);
+  };
+  if (d == 1) go(dedup_small_kernel<T, TL, 1>);
+  else if (d == 2) go(dedup_small_kernel<T, TL, 2>);
+  else if (d <= 4) go(dedup_small_kernel<T, TL, 4>);
+  else go(dedup_small_kernel<T, TL, 8>);
 }
 
 size_t dedup_ws_bytes(int C) { return align_up(sizeof(int32_t) * 8) + 256; }

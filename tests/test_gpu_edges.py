@@ -216,3 +216,27 @@ def test_one_launch_is_the_step_launches(L, d, K, B, cut, monkeypatch):
         assert a.log_z == b.log_z
     for k in ("modes", "mode_log_z", "mode_logl", "log_det_h"):
         assert np.array_equal(getattr(a, k), getattr(b, k)), k
+
+
+@pytest.mark.parametrize("C,d,n", [(256, 64, 8), (256, 64, 9), (256, 64, 256), (192, 64, 60),
+                                   (193, 64, 60), (1024, 16, 100), (1024, 17, 3), (4096, 3, 40),
+                                   (4097, 3, 9), (8192, 1, 20), (8192, 2, 300), (3000, 5, 50),
+                                   (496, 33, 496), (100, 100, 100), (16, 1024, 16)])
+def test_dedup_many_representatives(L, C, d, n):
+    """n clusters, few and all candidates apart, at each number of values a lane takes and on
+    both sides of the one-workgroup limits: the oracle's partition exactly, and with room for
+    one less the capacity status."""
+    rng = np.random.Generator(np.random.PCG64(40 + C + d + n))
+    centres = 3.0 * rng.permutation(n)[:, None] * np.ones((1, d)) + rng.uniform(0, 1, (n, d))
+    at = np.concatenate([np.arange(n), rng.integers(n, size=C - n)])
+    X = centres[at] + 0.1 * rng.uniform(-1, 1, (C, d))
+    l = np.round(rng.standard_normal(C), 1)
+    ro, rs = O.dedup(X, l, 0.5)
+    assert len(rs) == n
+    rep_of, reps = L.sb_dedup_dev(dev(X), dev(l), 0.5, max_reps=n)
+    assert np.array_equal(rep_of.cpu().numpy(), ro)
+    assert np.array_equal(reps.cpu().numpy(), rs)
+    if n > 1:
+        with pytest.raises(L.SbError) as e:
+            L.sb_dedup_dev(dev(X), dev(l), 0.5, max_reps=n - 1)
+        assert e.value.status == L.E_CAPACITY
