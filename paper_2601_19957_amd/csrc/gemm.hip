@@ -1412,13 +1412,25 @@ __device__ inline void hess_tiles(const HessSrc &h, int t, double (&S)[2][32][33
       const double rk = h.aux[k];
       if (rk == 0.0) continue;
       const double *P = h.P + (size_t)k * h.ld * h.ld, *u = h.u + (size_t)k * h.ld;
-      for (int w = 0; w < nt; ++w) {
+      // (both tiles' values on their way before the first is used)
+      double p[2][4], ui[2][4], uj[2];
+#pragma unroll
+      for (int w = 0; w < 2; ++w) {
+        if (w >= nt) break;
         const int j = r0[1 - w] + tx;
+        uj[w] = j < d ? u[j] : 0.0;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const int i = r0[w] + ty + 8 * q;
-          if (i < d && j < d) e[w][q] += rk * (P[(size_t)i * h.ld + j] - u[i] * u[j]);
+          p[w][q] = i < d && j < d ? P[(size_t)i * h.ld + j] : 0.0;
+          ui[w][q] = i < d ? u[i] : 0.0;
         }
+      }
+#pragma unroll
+      for (int w = 0; w < 2; ++w) {
+        if (w >= nt) break;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) e[w][q] += rk * (p[w][q] - ui[w][q] * uj[w]);
       }
     }
   }
