@@ -1420,22 +1420,24 @@ int run_evidence(const DevProblem &P, const sb_config *cfg, sb_result *res, void
       SB_LAUNCH_CHECK();
       tm.mark(s);  // 6
     }
-    // counts and, with modes, the result: small ones in one readback, larger ones
-    // straight to where the caller wants them (nothing is allocated here)
-    double hstack[ExecCtx::kPinnedBytes / 8];
+    // counts and, with modes, the result: as much of it as fits in one readback,
+    // the rest straight to where the caller wants it (nothing is allocated here;
+    // each copy of its own costs about 10 us)
+    constexpr size_t kFit = ExecCtx::kPinnedBytes / 8;
+    double hstack[kFit];
     double *h = ex ? (double *)ex->pinned : hstack;
-    const size_t nout = kOutHead + (modes ? (size_t)nm * (d + 3) : 0);
-    const bool whole = nout * 8 <= ExecCtx::kPinnedBytes;
+    const size_t ns = modes ? 3 * (size_t)nm : 0, nx = modes ? (size_t)nm * d : 0;
+    const bool scalars = kOutHead + ns <= kFit, whole = kOutHead + ns + nx <= kFit;
     auto fetch = [&](double *dst, const double *src, size_t n) {
-      return dst ? hipMemcpyAsync(dst, src, 8 * n, hipMemcpyDeviceToHost, s) : hipSuccess;
+      return dst && n ? hipMemcpyAsync(dst, src, 8 * n, hipMemcpyDeviceToHost, s) : hipSuccess;
     };
-    SB_HIP(fetch(h, L.out, whole ? nout : (size_t)kOutHead));
-    if (!whole) {
+    SB_HIP(fetch(h, L.out, kOutHead + (scalars ? ns : 0) + (whole ? nx : 0)));
+    if (!scalars) {
       SB_HIP(fetch(res->mode_log_z, mlz, nm));
       SB_HIP(fetch(res->mode_logl, ml, nm));
       SB_HIP(fetch(res->log_det_h, mld, nm));
-      SB_HIP(fetch(res->modes, mx, (size_t)nm * d));
     }
+    if (!whole) SB_HIP(fetch(res->modes, mx, nx));
     SB_HIP(hipStreamSynchronize(s));
     int32_t hcounts[8];
     memcpy(hcounts, h, sizeof(hcounts));
@@ -1458,13 +1460,13 @@ int run_evidence(const DevProblem &P, const sb_config *cfg, sb_result *res, void
       ret = SB_E_CAPACITY;
     } else {
       res->log_z = h[4];
-      if (whole) {
-        const double *r = h + kOutHead;
+      const double *r = h + kOutHead;
+      if (scalars) {
         if (res->mode_log_z) memcpy(res->mode_log_z, r, sizeof(double) * nm);
         if (res->mode_logl) memcpy(res->mode_logl, r + nm, sizeof(double) * nm);
         if (res->log_det_h) memcpy(res->log_det_h, r + 2 * nm, sizeof(double) * nm);
-        if (res->modes) memcpy(res->modes, r + 3 * nm, sizeof(double) * (size_t)nm * d);
       }
+      if (whole && res->modes) memcpy(res->modes, r + ns, sizeof(double) * nx);
     }
     const double total =
         std::chrono::duration<double>(std::chrono::steady_clock::now() - t_start).count();

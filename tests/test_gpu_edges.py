@@ -240,3 +240,20 @@ def test_dedup_many_representatives(L, C, d, n):
         with pytest.raises(L.SbError) as e:
             L.sb_dedup_dev(dev(X), dev(l), 0.5, max_reps=n - 1)
         assert e.value.status == L.E_CAPACITY
+
+
+def test_result_of_one_mode_too_many(L):
+    """Four modes with room for three: the capacity status, the number found, and the caller's
+    arrays as they were."""
+    rng = np.random.Generator(np.random.PCG64(12))
+    prob = synth.gaussian_mixture(rng, 6, 4, -30.0, 30.0, 0.1, 1.0, 0.0, box_half=40.0)
+    cfg = synth.RunConfig(n_rays=512, n_points=32, n_starts=512, seed=3, precision=0)
+    full = L.EvidenceRunner(prob, cfg, exec=True).run()
+    assert full.status == 0 and full.n_modes == 4
+    cfg.max_modes = 3
+    r, arrs = L._new_result(3, 6)
+    run = L.EvidenceRunner(prob, cfg)
+    st = L.lib().sb_evidence_dev(C.byref(run.ll), C.byref(run.box), C.byref(run.c), C.byref(r),
+                                 run.ws.data_ptr(), run.ws.numel(), 0)
+    assert st == L.E_CAPACITY and r.n_modes == 4 and np.isnan(r.log_z)
+    assert not any(a.any() for a in arrs)
