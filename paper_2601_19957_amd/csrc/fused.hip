@@ -90,8 +90,8 @@ bool fused_logl_grad_ok(const Model &m, const ASrc &a) {
   const char *e = getenv("SB_FUSED");  // "0": the two-launch path (for comparison)
   if (e && e[0] == '0') return false;
   // d <= 128: there one launch beats the GEMM + epilogue pair (c1, d = 64,
-  // K = 4: 18.3 vs 13.3 + 7.4 us); at d = 256 (c2) the 64 x 64-tile GEMM's
-  // staged P outruns the fused kernel's P stream (36.6 + 8.6 vs 48.5 us)
+  // K = 4, 4096 points: 13.8 vs 15.3 us); at d = 256 (c2, 8192 points) the GEMM's
+  // staged P outruns the fused kernel's P stream (28.4 + 7.8 vs 43.9 us)
   const int dp = (m.d + 31) / 32 * 32;
   return a.kind == 0 && !a.zero_mu && m.d >= 1 && dp <= 128 && m.K >= 1 && m.K <= kMaxK &&
          (int64_t)m.K * dp <= 16 * 4 * kMaxSlots && m.P64 && m.mu64 &&

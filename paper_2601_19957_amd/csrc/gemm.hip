@@ -1368,7 +1368,7 @@ int launch_hvp_finish(const Model &m, const HvpArgs &h, hipStream_t s) {
 // workgroup takes the 32 x 32 tiles (I, J) and (J, I) together, so that both
 // halves of every entry are read along rows and meet in LDS; a component whose
 // responsibility is zero adds nothing and its P is not read (as in the row
-// epilogue).  d = 1024, K = 8, 8 points at the modes: 31 us (each entry with
+// epilogue).  d = 1024, K = 8, 8 points at the modes: 29 us (each entry with
 // its mirror image read down a column, and every component: 272 us).
 struct HessSrc {
   int d, ld, K, family;  // ld: row stride of P and of each component's u
