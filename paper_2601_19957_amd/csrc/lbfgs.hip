@@ -390,7 +390,7 @@ __device__ inline void two_loop(const H &Sr, const H &Yr, T rh, T gamma, int cnt
 // pair's reduction so that the load latency overlaps it.  When `reg_new`,
 // the newest pair (logical cnt - 1) is taken from sn, yn, rn instead.  The
 // arithmetic and its order are those of two_loop.
-template <typename T, int TPB, int EPT>
+template <typename T, int TPB, int EPT, bool LATE = false>
 __device__ __forceinline__ void two_loop_stream(const T *Sb, const T *Yb, const T *rho, int d, int m,
                                        int head, int cnt, bool reg_new,
                                        const T (&sn)[EPT], const T (&yn)[EPT], T rn, T gamma,
@@ -401,6 +401,52 @@ __device__ __forceinline__ void two_loop_stream(const T *Sb, const T *Yb, const 
   for (int e = 0; e < EPT; ++e) q[e] = g[e];
   const int slot0 = head >= cnt ? head - cnt : head - cnt + m;
   auto slot = [&](int j) { return slot0 + j < m ? slot0 + j : slot0 + j - m; };
+  // Two buffers by turns: a copy from one to the other would wait for the pair
+  // under way ahead of the current one's reduction (FP64, m = 32, 1024 starts of
+  // d = 199: 74 us against 56).  FP64 copies all the same where the registers of two
+  // buffers cost a wave per SIMD that tells more: m = 12, 4096 starts of d = 128 44 us
+  // against 36, d = 402 129 against 112.  (LATE: always.)
+  constexpr bool TURNS = !LATE && (sizeof(T) == 4 || (EPT > 2 && TPB == 64));
+  // LATE (rows of EPT values at least): the chunk that crosses the rows' end is loaded
+  // whole from their last EPT values and shifted to its place when it is copied.  One mask
+  // for the loads of all lanes, and nothing at the loads that waits for them.
+  static_assert(EPT <= 4 || !LATE, "shifts by up to 3");
+  const int sh = d % EPT ? EPT - d % EPT : 0;
+  const bool cross = at.i0 < d && at.i0 + EPT > d;
+  uint32_t loff = at.off - (cross ? (uint32_t)sh * (uint32_t)sizeof(T) : 0u);
+  if constexpr (LATE) asm volatile("" : "+v"(loff));
+  auto row = [&](const T *r, T (&v)[EPT], bool last) {
+    if constexpr (LATE) {
+      const T *q0 = (const T *)((const char *)r + loff);
+#pragma unroll
+      for (int e = 0; e < EPT; ++e) v[e] = (T)0;
+      if (at.i0 < d) {
+        if (last) piece_load<T, EPT, true>(q0, v);
+        else piece_load<T, EPT, false>(q0, v);
+      }
+    } else if (last) {
+      vload_nt<T, EPT>(r, at, d, v);
+    } else {
+      vload<T, EPT>(r, at, d, v);
+    }
+  };
+  // (reg: the pair from the registers, in place already)
+  auto settle = [&](const T (&v)[EPT], T (&o)[EPT], bool reg) {
+    // (uniform; the branch also keeps the shift from moving up to the loads, whose wait
+    // it would bring: up to 2.7 times the step's time)
+    if (!LATE || sh == 0 || reg) {
+#pragma unroll
+      for (int e = 0; e < EPT; ++e) o[e] = v[e];
+    } else {
+      const bool c1 = cross && (sh & 1), c2 = cross && (sh & 2);
+      T w[EPT + 2];
+      w[EPT] = w[EPT + 1] = (T)0;
+#pragma unroll
+      for (int e = 0; e < EPT; ++e) w[e] = c1 ? (e + 1 < EPT ? v[e + 1] : (T)0) : v[e];
+#pragma unroll
+      for (int e = 0; e < EPT; ++e) o[e] = c2 ? w[e + 2] : w[e];
+    }
+  };
   auto fetch = [&](int j, T (&sv)[EPT], T (&yv)[EPT], T &rv, bool last) {
     if (reg_new && j == cnt - 1) {
 #pragma unroll
@@ -412,27 +458,20 @@ __device__ __forceinline__ void two_loop_stream(const T *Sb, const T *Yb, const 
       return;
     }
     const int ph = slot(j);
-    if (last) {
-      vload_nt<T, EPT>(Sb + (size_t)ph * d, at, d, sv);
-      vload_nt<T, EPT>(Yb + (size_t)ph * d, at, d, yv);
-    } else {
-      vload<T, EPT>(Sb + (size_t)ph * d, at, d, sv);
-      vload<T, EPT>(Yb + (size_t)ph * d, at, d, yv);
-    }
+    row(Sb + (size_t)ph * d, sv, last);
+    row(Yb + (size_t)ph * d, yv, last);
     rv = rho[ph];
   };
-  // Two buffers by turns: a copy from one to the other would wait for the pair
-  // under way ahead of the current one's reduction (FP64, m = 32, 1024 starts of
-  // d = 199: 74 us against 56).  FP64 copies all the same where the registers of two
-  // buffers cost a wave per SIMD that tells more: m = 12, 4096 starts of d = 128 44 us
-  // against 36, d = 402 129 against 112.
-  constexpr bool TURNS = sizeof(T) == 4 || (EPT > 2 && TPB == 64);
   T sb[2][EPT], yb[2][EPT], rb[2] = {0, 0};
   if (cnt > 0) {
     if (TURNS && cnt % 2 == 0)
       fetch(cnt - 1, sb[1], yb[1], rb[1], false);
     else
       fetch(cnt - 1, sb[0], yb[0], rb[0], false);
+    if constexpr (LATE) {
+      settle(sb[0], sb[0], reg_new);
+      settle(yb[0], yb[0], reg_new);
+    }
   }
 #pragma unroll
   for (int j = kMaxMem - 1; j >= 0; --j) {
@@ -448,11 +487,8 @@ __device__ __forceinline__ void two_loop_stream(const T *Sb, const T *Yb, const 
 #pragma unroll
       for (int e = 0; e < EPT; ++e) q[e] -= al[j] * yb[c][e];
       if (!TURNS && j > 0) {
-#pragma unroll
-        for (int e = 0; e < EPT; ++e) {
-          sb[0][e] = ns[e];
-          yb[0][e] = ny[e];
-        }
+        settle(ns, sb[0], false);
+        settle(ny, yb[0], false);
         rb[0] = nr;
       }
     } else {
@@ -462,6 +498,12 @@ __device__ __forceinline__ void two_loop_stream(const T *Sb, const T *Yb, const 
 #pragma unroll
   for (int e = 0; e < EPT; ++e) q[e] *= gamma;
   if (cnt > 0) fetch(0, sb[0], yb[0], rb[0], true);
+  if constexpr (LATE) {
+    if (cnt > 0) {
+      settle(sb[0], sb[0], reg_new && cnt == 1);
+      settle(yb[0], yb[0], reg_new && cnt == 1);
+    }
+  }
 #pragma unroll
   for (int j = 0; j < kMaxMem; ++j) {
     if (j < cnt) {
@@ -476,11 +518,8 @@ __device__ __forceinline__ void two_loop_stream(const T *Sb, const T *Yb, const 
 #pragma unroll
       for (int e = 0; e < EPT; ++e) q[e] += (al[j] - bb) * sb[c][e];
       if (!TURNS && j + 1 < cnt) {
-#pragma unroll
-        for (int e = 0; e < EPT; ++e) {
-          sb[0][e] = ns[e];
-          yb[0][e] = ny[e];
-        }
+        settle(ns, sb[0], reg_new && j + 2 == cnt);
+        settle(ny, yb[0], reg_new && j + 2 == cnt);
         rb[0] = nr;
       }
     }
@@ -510,7 +549,7 @@ __device__ __forceinline__ T moved_sq(const T (&x)[EPT], const T (&o)[EPT],
 // rounded to BF16 when formed).  MV (FP32): the distance that the trial moved its
 // slot is written too; it holds the old point to the end, so only the launches
 // that a screen follows have it.
-template <typename T, int TPB, int EPT, bool HREG, bool HB, bool MV>
+template <typename T, int TPB, int EPT, bool HREG, bool HB, bool MV, bool LATE = false>
 __device__ __forceinline__ int32_t lbfgs_step_one(const LbArgs<T> &a, const int64_t s,
                                                   const int tid, BlockRed<TPB, T> &red) {
   static_assert(!HB || (HREG && sizeof(T) == 4), "BF16 history: FP32, register-resident");
@@ -792,9 +831,9 @@ __device__ __forceinline__ int32_t lbfgs_step_one(const LbArgs<T> &a, const int6
     if constexpr (HREG)
       two_loop<T, TPB, EPT>(Sr, Yr, rh, gamma, cnt, nset, old0, g, p, red);
     else
-      two_loop_stream<T, TPB, EPT>(a.S + (size_t)m * vo, a.Yh + (size_t)m * vo,
-                                   a.rho + (size_t)s * m, d, m, head, cnt, reg_new, sv, yv,
-                                   r_new, gamma, g, p, red);
+      two_loop_stream<T, TPB, EPT, LATE>(a.S + (size_t)m * vo, a.Yh + (size_t)m * vo,
+                                         a.rho + (size_t)s * m, d, m, head, cnt, reg_new, sv,
+                                         yv, r_new, gamma, g, p, red);
     T t = 0;
 #pragma unroll
     for (int e = 0; e < EPT; ++e) t += g[e] * p[e];
@@ -862,6 +901,23 @@ __global__ __launch_bounds__(TPB, 2) void lbfgs_step_kernel(LbArgs<T> a) {
     lbfgs_step_one<T, TPB, EPT, HREG, HB, MV>(a, a.s_base + blockIdx.x, threadIdx.x, red);
 }
 
+// The step of FP64 starts with a long streamed history whose rows end inside a thread's
+// values (two_loop_stream's LATE).  Loaded under a second mask, such a chunk makes each copy
+// there wait more than once, and two buffers by turns cost a wave per SIMD: m = 32, 1024
+// starts of d = 127 49 -> 35 us, d = 203 57 -> 44, d = 331 90 -> 58, d = 402 86 -> 64, d = 511
+// 103 -> 80, d = 1002 222 -> 192, d = 2047 422 -> 344; m = 16, d = 511 53 -> 45.  Up to m = 12
+// the shifts cost as much (m = 10, 1025 starts of d = 257 25 -> 27).
+template <int TPB, int EPT>
+__global__ __launch_bounds__(TPB, TPB == 512 ? 2 : EPT == 4 ? 3 : 4)
+void lbfgs_step_ragged_kernel(LbArgs<double> a) {
+  __shared__ double rbuf[2 * BlockRed<TPB, double>::NMAX * (TPB / 64)];
+  BlockRed<TPB, double> red{rbuf, 0};
+  if (a.count_reset && blockIdx.x == 0 && threadIdx.x == 0) *a.count_reset = 0;
+  if ((int64_t)blockIdx.x < a.s_count)
+    lbfgs_step_one<double, TPB, EPT, false, false, false, true>(a, a.s_base + blockIdx.x,
+                                                                threadIdx.x, red);
+}
+
 template <typename T, int TPB, int EPT, bool HREG, bool HB>
 static void step_go(const LbArgs<T> &a, hipStream_t s) {
   if constexpr (sizeof(T) == 4) {
@@ -878,6 +934,19 @@ static void step_go(const LbArgs<T> &a, hipStream_t s) {
 // Workgroup size and elements per thread by d; HR: history in registers.
 template <typename T, bool HR>
 static void step_by_d(const LbArgs<T> &a, int d, hipStream_t s) {
+  if constexpr (sizeof(T) == 8 && !HR) {
+    if (!a.vdim && d > 64 && d <= 2048 && d % (d <= 128 ? 2 : 4) != 0 && a.m > 12) {
+      auto go = [&](auto kernel, int tpb) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)a.s_count), dim3(tpb), 0, s, a);
+      };
+      if (d <= 128) go(lbfgs_step_ragged_kernel<64, 2>, 64);
+      else if (d <= 256) go(lbfgs_step_ragged_kernel<64, 4>, 64);
+      else if (d <= 512) go(lbfgs_step_ragged_kernel<128, 4>, 128);
+      else if (d <= 1024) go(lbfgs_step_ragged_kernel<256, 4>, 256);
+      else go(lbfgs_step_ragged_kernel<512, 4>, 512);
+      return;
+    }
+  }
   if (d <= 64) step_go<T, 64, 1, HR, false>(a, s);
   else if (d <= 128) step_go<T, 64, 2, HR, false>(a, s);
   else if (d <= 256) step_go<T, 64, 4, HR, false>(a, s);
